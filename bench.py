@@ -448,11 +448,11 @@ def main():
                if args.window_blocks > 0 else {}),
         },
         # Dominant kernel: the segmented store-mode product, launched for a
-        # window's t3 blocks, its lambda3 blocks (before symmetrisation) and
-        # the S intermediate of Y1.
+        # window's t3 blocks and its lambda3 blocks (before symmetrisation) and,
+        # in the reduced precisions, the S intermediate of Y1.
         "roofline": {
             "bound": "mfma",
-            "kernel": "zgemm_seg_f64_kernel<false> (t3, lambda3 and S products)"
+            "kernel": "zgemm_seg_f64_kernel<false> (t3 and lambda3 products)"
             if args.precision == "fp64" else "segmented products (t3, lambda3, S)",
             "achieved": b_achieved,
             "peak": peak,

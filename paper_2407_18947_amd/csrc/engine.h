@@ -53,6 +53,10 @@ class Engine {
   cplx* data(int buf) { return bufs_[buf].p; }
   int64_t size(int buf) { return bufs_[buf].n; }
 
+  // The relayout scratch of the current stream, grown to n elements (what
+  // einsum takes; also to reserve it for a later evaluation).
+  cplx* scratch(int64_t n);
+
   static View slice(View v, int dim, int64_t lo, int64_t hi);
   static View permute(View v, std::vector<int> perm);  // out dim d = in dim perm[d]
   static View diag(View v, int d0, int d1);             // diagonal of dims d0,d1 (equal extents) at d0
@@ -142,7 +146,6 @@ class Engine {
   };
   std::vector<Scratch> scratch_;
 
-  cplx* scratch(int64_t n);
   void einsum_exec(const std::string& spec, cplx alpha, const View& A, const View& B, const View& C);
 };
 

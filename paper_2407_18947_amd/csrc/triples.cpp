@@ -688,13 +688,18 @@ void Triples::blocks(Engine& e, const CCSDResult& r) {
   t = make("tb_G5", {o, o, v, v});  // L_jbxc = 2(jb|xc) - (jc|xb) at [j][x][b][c]
   e.einsum("Pjb,Pxc->jxbc", R(2), B('o', 'v'), B('o', 'v'), t);
   e.einsum("Pjc,Pxb->jxbc", R(-1), B('o', 'v'), B('o', 'v'), t);
+  if (prec_ == RTCC3_PREC_FP64) {  // S is not formed: see window_pass
+    e.tensor("tb_G9", {o, v, v, o});
+    e.tensor("tb_G10", {o, v, v, o});
+    return;
+  }
   t = make("tb_G9", {o, v, v, o});  // (xl|db) at [l][b][d][x]
   e.einsum("Pxl,Pdb->lbdx", ONE, B('o', 'o'), B('v', 'v'), t);
   t = make("tb_G10", {o, v, v, o});  // (dl|xb) at [l][b][d][x]
   e.einsum("Pdl,Pxb->lbdx", ONE, B('v', 'o'), B('o', 'v'), t);
 }
 
-void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_terms, bool density_terms) {
+void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool density_terms) {
   const int o = d_.o, v = d_.v;
   const int64_t v2 = (int64_t)v * v, v3 = v2 * v, ov = (int64_t)o * v, oovv = (int64_t)o * o * v2;
   const int64_t ylen = 2 * (ov + oovv);
@@ -742,6 +747,12 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
   const int* bl = w.d_bl;
   const int* blh = w.bl.data();
   const int pr = prec_;
+  // Terms 9 and 10 of Y1.  In FP64 they come from Z_i (below), which saves the
+  // S product and its segment (4.7 ms a right-hand side at o=15, v=57).  The
+  // reduced precisions keep S, which the split precisions form from bf16 slices:
+  // another grouping of their rounded products would change their results by
+  // as much as those are off.
+  const bool via_s = pr != RTCC3_PREC_FP64;
 
   // Both builds produce W[n][a][(b,c)] in one store-mode product.  A term X
   // whose natural layout is [(a,b)][c] is taken at the cyclically relabelled
@@ -801,7 +812,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
   const int cn = pairwin ? (int)w.owned.size() / 4 : nw;
   const int* obl = pairwin ? w.d_orb_owned : w.d_orb;  // the same entries, grouped by occupied triple
   const int* oblh = pairwin ? w.orb_owned.data() : w.orb.data();
-  if (rhs_terms) {
+  if (via_s) {
     // S needs only t2 and integrals: it goes first on the lambda3 side, beside
     // the t3 symmetrisation (memory bound) rather than beside other products
     RTCC3_HIP(hipStreamWaitEvent(s2, ev_t3b_, 0));
@@ -878,7 +889,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
   RTCC3_HIP(hipEventRecord(ev_l_, s2));  // lambda3 blocks ready
   launches_ += 4;
 
-  if (rhs_terms) {
+  {  // the contractions of the right-hand side
     cplx* X1 = P("tr_X1", {o, v});
     cplx* X2p = P("tr_X2p", {o, o, v, v});
     cplx* Y1 = P("tr_Y1", {o, v});
@@ -889,7 +900,6 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
     cplx* R6 = P("tr_R6", {o, o, v, o});
     cplx* R8 = P("tr_R8", {o, o, v, o});
     cplx* Zi = P("tr_Zi", {o, v, v, v});
-    cplx* R12 = P("tr_R12", {o, o, o, v});
     const int64_t lR = (int64_t)o * o * v * o;
 
     // X1, the f~ term of X2 and Z34 (terms 3 and 4 of Y1): with o <= 15 they ride
@@ -1119,24 +1129,22 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
                    {c6, l2len, lR, l2len, ov}},
                   s);
     }
-    {  // One column-segment product over lambda_n[a][(b,c)] (S is ready: same stream, earlier):
-       //  terms 7, 8: Q[d][j] = sum_bc lambda[(b,c)][d] t2[j][J][(b,c)] into R8[I][K]; with
-       //    lambda[b][c][d] = lambda_KIJ[d][b][c] and the labels renamed ((K,I,J) -> (I,J,K)):
-       //    sum_bc lambda_n[d][(b,c)] t2[j][K][(b,c)] into R8[J][I]
-       //    (the term-7 intermediate R7[K][I] is the same sum with the first two indices swapped);
-       //  Y1[x][a] -= sum_(c,d) lambda_n[a][(c,d)] S[n][(c,d)][x];
-       //  term 12: R12[I][j][J][a] += sum_bc lambda_n[a][(b,c)] t2[j][K][(b,c)]   (block (l,m,k) = (I,J,K)).
+    {  // terms 7, 8, 12 and the last density term: Q[d][j] = sum_bc lambda[(b,c)][d] t2[j][J][(b,c)] into
+       //    R8[I][K]; with lambda[b][c][d] = lambda_KIJ[d][b][c] and the labels renamed ((K,I,J) -> (I,J,K)):
+       //    sum_bc lambda_n[d][(b,c)] t2[j][K][(b,c)] into R8[J][I].
+       // The four terms take the same sum (over the block (l,m,k) = (I,J,K) of term 12 and (j,k,l) = (I,J,K) of
+       // D_ia) under different names, so it is formed once.
       const int64_t ovo = (int64_t)o * v * o, vo = (int64_t)v * o, ov2 = (int64_t)o * v2;
-      const int64_t lS = (int64_t)max_nw_ * v2 * o;
-      const int64_t lR12 = (int64_t)o * o * o * v;
-      seg_product(L,
-                  {{cseg(t2, {0, 0, v2, 0}, 1, ov2, R8, {vo, ovo, 0, 0}, o, 1, 1.0), t2len, lR, 0, 0},
-                   {cseg(S, {0, 0, 0, v2 * o}, o, 1, Y1, {0, 0, 0, 0}, 1, v, -1.0), lS, ov, 0, 0},
-                   {cseg(t2, {0, 0, v2, 0}, 1, ov2, R12, {(int64_t)o * o * v, v, 0, 0}, 1, vo, 1.0), t2len, lR12, 0, 0}},
-                  s2);
+      std::vector<SegSpec> specs = {{cseg(t2, {0, 0, v2, 0}, 1, ov2, R8, {vo, ovo, 0, 0}, o, 1, 1.0), t2len, lR, 0, 0}};
+      // terms 9, 10 from S: Y1[x][a] -= sum_(c,d) lambda_n[a][(c,d)] S[n][(c,d)][x]
+      if (via_s)
+        specs.push_back({cseg(S, {0, 0, 0, v2 * o}, o, 1, Y1, {0, 0, 0, 0}, 1, v, -1.0), (int64_t)max_nw_ * v2 * o, ov,
+                         0, 0});
+      seg_product(L, specs, s2);
     }
-    {  // term 11: Zi[J][b][(d,e)] += sum_c t2[K][I][b][c] lambda[c][(d,e)]   (block (k,i,j) = (I,J,K)),
-       // summed over the blocks of each J
+    {  // term 11, and in FP64 terms 9 and 10: Zi[J][b][(d,e)] += sum_c t2[K][I][b][c] lambda[c][(d,e)]   (block (k,i,j) = (I,J,K)),
+       // summed over the blocks of each J.  Terms 9 and 10 sum t_jk^bc lambda_lkj^acd and t_jk^bc lambda_jkl^acd
+       // over j, k, c, which with lambda_{sigma(ijk)}^{sigma(abc)} = lambda_ijk^abc are Z_l^{bad} and Z_l^{bda}.
       GemmDesc g = base(v, (int)v2, v * w.gJ.max, 0, nullptr, pr);
       g.K0 = v;
       g.A = t2;
@@ -1156,7 +1164,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
       set4(g.cC, 0, v3, 0, 0);
       prod_gather(e, g, w.gJ, t2len, winlen, lOVVV, s2);
     }
-    launches_ += tails ? 9 : 10;
+    launches_ += tails ? 8 : 9;
   }
 
   // the density terms read t3 and lambda3: join the lambda3 side's blocks
@@ -1164,8 +1172,6 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
   if (density_terms && !w.owned.empty()) {
     const int no = (int)w.owned.size() / 4;
     cplx* Dab = P("td_Dab", {v, v});
-    cplx* Z34 = P("td_Z34", {o, v});
-    cplx* Rd = P("td_Rd", {o, o, v, o});
     {  // D_ab += 1/2 sum_{(d,c)} lambda[a][(d,c)] t[b][(d,c)]
       GemmDesc g = base(v, v, (int)v2, no, w.d_owned, pr);
       g.atomic = 1;
@@ -1186,32 +1192,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_te
       g.sCn0 = 1;
       prod(e, g, w.owned.data(), winlen, winlen, v2, s);
     }
-    // D_ia first term: sum_bc (t[a,b,c] - t[b,a,c]) l2[J,K,b,c]; it equals the
-    // Y1 intermediate Z34 when the same pass also evaluates the right-hand side
-    if (!rhs_terms) {
-      RTCC3_CHECK(!e.tangent(), "triples: derivatives of the density need the right-hand side pass");
-      launch_small_t3(T, w.d_owned, no, Lov, F, l2, nullptr, nullptr, Z34, o, v, vp, 2, s);
-    }
-    {  // D_ia second term: Rd[J][I][b][x] += sum_cd lambda[b][(c,d)] t2[x][K][(c,d)]
-      GemmDesc g = base(v, o, (int)v2, no, w.d_owned, pr);
-      g.atomic = 1;
-      g.K0 = v;  // k = (c,d)
-      g.A = L;
-      g.sAm0 = va;
-      g.sAk1 = vp;
-      g.sAk0 = 1;
-      set4(g.cA, 0, 0, 0, vb);
-      g.B = t2;
-      g.sBk1 = v;
-      g.sBk0 = 1;
-      g.sBn0 = (int64_t)o * v2;
-      set4(g.cB, 0, 0, v2, 0);
-      g.C = Rd;
-      g.sCm0 = o;
-      g.sCn0 = 1;
-      set4(g.cC, (int64_t)v * o, (int64_t)o * v * o, 0, 0);
-      prod(e, g, w.owned.data(), winlen, t2len, (int64_t)o * o * v * o, s);
-    }
+    // D_ia: its first term is the Y1 intermediate Z34, its second is contracted from R8
   }
   if (density_terms && !w.slabs.empty()) {
     // D_ij += -1/2 sum_abc t_{ilk} lambda_{jlk}, one batch entry per slab (., l, k);
@@ -1277,20 +1258,18 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   side_done_ = nullptr;
   // accumulators
   const char* names[] = {"tr_X1", "tr_X2p", "tr_Y1", "tr_Y2p", "tr_Z34", "tr_R15",
-                         "tr_R2", "tr_R6", "tr_R8", "tr_Zi",  "tr_R12"};
+                         "tr_R2", "tr_R6", "tr_R8", "tr_Zi"};
   std::vector<std::vector<int64_t>> shapes = {{o, v},       {o, o, v, v}, {o, v},       {o, o, v, v},
                                               {o, v},       {o, o, v, o}, {o, o, v, o}, {o, o, v, o},
-                                              {o, o, v, o}, {o, v, v, v}, {o, o, o, v}};
+                                              {o, o, v, o}, {o, v, v, v}};
   for (size_t i = 0; i < shapes.size(); ++i) e.zero(e.tensor(names[i], shapes[i]));
   if (want_density) {
-    View Dij = e.tensor("td_Dij", {o, o}), Dab = e.tensor("td_Dab", {v, v}), Rd = e.tensor("td_Rd", {o, o, v, o});
-    e.zero(Dij);
-    e.zero(Dab);
-    e.zero(Rd);
+    e.zero(e.tensor("td_Dij", {o, o}));
+    e.zero(e.tensor("td_Dab", {v, v}));
     // one pass over the pair windows: right-hand side for the owned blocks, density terms
-    for (auto& w : den_windows_) window_pass(e, w, y, true, true);
+    for (auto& w : den_windows_) window_pass(e, w, y, true);
   } else {
-    for (auto& w : rhs_windows_) window_pass(e, w, y, true, false);
+    for (auto& w : rhs_windows_) window_pass(e, w, y, false);
   }
 
   if (beside_) {  // no window ran (nothing to overlap): start the side work here
@@ -1317,7 +1296,13 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   e.einsum("lidj,jlda->ia", R(-1), e.tensor("tr_R8", {o, o, v, o}), g_oovv, Y1);
   e.einsum("ildj,dlja->ia", R(-1), e.tensor("tr_R8", {o, o, v, o}), g_voov, Y1);
   e.einsum("ibde,daeb->ia", ONE, e.tensor("tr_Zi", {o, v, v, v}), g_vvvv, Y1);
-  e.einsum("xljm,ljma->xa", ONE, g_oooo, e.tensor("tr_R12", {o, o, o, v}), Y1);
+  if (prec_ == RTCC3_PREC_FP64) {
+    e.einsum("lbad,ildb->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_oovv, Y1);
+    e.einsum("lbda,dlib->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_voov, Y1);
+  } else {  // the relayout space of these two, for a later switch to FP64
+    (void)e.scratch(o * v * v * v + oovv + ov);
+  }
+  e.einsum("xljm,mlaj->xa", ONE, g_oooo, e.tensor("tr_R8", {o, o, v, o}), Y1);
 
   TriplesOut out;
   out.X1 = e.tensor("tr_X1", {o, v});
@@ -1337,13 +1322,13 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   out.Y2 = Y2;
 
   if (want_density) {
-    View Dij = e.tensor("td_Dij", {o, o}), Dab = e.tensor("td_Dab", {v, v}), Rd = e.tensor("td_Rd", {o, o, v, o});
+    View Dij = e.tensor("td_Dij", {o, o}), Dab = e.tensor("td_Dab", {v, v});
     View Z34 = e.tensor("tr_Z34", {o, v});
     View Dia = e.tensor("td_Dia", {o, v});
     e.zero(Dia);
     e.axpy(ONE, Z34, Dia);
     View t2 = Engine::raw(const_cast<cplx*>(y) + ov, {o, o, v, v});
-    e.einsum("kjbx,kjab->xa", R(-1), Rd, t2, Dia);
+    e.einsum("kjbx,kjab->xa", R(-1), e.tensor("tr_R8", {o, o, v, o}), t2, Dia);
     out.Dij = Dij;
     out.Dab = Dab;
     out.Dia = Dia;

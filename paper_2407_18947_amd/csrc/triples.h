@@ -103,8 +103,8 @@ class Triples {
     ms = ms_;
     launches = (double)launches_;
   }
-  // The segmented store-mode products (the t3 and lambda3 builds and the Y1 S
-  // intermediate, one kernel): event-timed milliseconds, launches and
+  // The segmented store-mode products (the t3 and lambda3 builds and, in the
+  // reduced precisions, the Y1 S intermediate; one kernel): event-timed milliseconds, launches and
   // algorithmic flops (8 per complex multiply-add).
   void build_timing(double& ms, double& launches, double& flop) const {
     ms = build_ms_;
@@ -149,7 +149,7 @@ class Triples {
   void upload(Window& w);
   void free_windows();
   void blocks(Engine& e, const CCSDResult& r);
-  void window_pass(Engine& e, const Window& w, const cplx* y, bool rhs_terms, bool density_terms);
+  void window_pass(Engine& e, const Window& w, const cplx* y, bool density_terms);
 };
 
 }  // namespace rtcc3
