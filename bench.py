@@ -452,7 +452,7 @@ def main():
         # in the reduced precisions, the S intermediate of Y1.
         "roofline": {
             "bound": "mfma",
-            "kernel": "zgemm_seg_f64_kernel<false> (t3 and lambda3 products)"
+            "kernel": "frag_seg_kernel<false> (t3 and lambda3 products)"
             if args.precision == "fp64" else "segmented products (t3, lambda3, S)",
             "achieved": b_achieved,
             "peak": peak,

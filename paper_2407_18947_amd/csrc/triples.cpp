@@ -19,6 +19,7 @@
 #include <map>
 #include <tuple>
 
+#include "frag_kernels.h"
 #include "triples_kernels.h"
 
 namespace rtcc3 {
@@ -109,9 +110,10 @@ void checked_gather_gemm(GemmDesc& g, const Groups& gr, int64_t lenA, int64_t le
 }
 
 // A K-segmented product (GemmDesc::seg) after the same check per segment;
-// lenA[s], lenB[s]: lengths of segment s's operand tensors.
-void checked_seg_gemm(const GemmDesc& g, const int* bl_host, const int64_t* lenA, const int64_t* lenB, int64_t lenC,
-                      hipStream_t s) {
+// lenA[s], lenB[s]: lengths of segment s's operand tensors.  FP64 products go
+// to the fragment kernel with the row tiles of their block table.
+void checked_seg_gemm(const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
+                      const int64_t* lenB, int64_t lenC, hipStream_t s) {
   if (g.batch <= 0) return;
   RTCC3_CHECK(g.bl && g.nseg >= 1 && g.nseg <= 4, "triples: segmented product needs a block table");
   const int64_t eC = span(g.M, g.M0, g.sCm1, g.sCm0) + span(g.N, g.N0, g.sCn1, g.sCn0);
@@ -131,7 +133,10 @@ void checked_seg_gemm(const GemmDesc& g, const int* bl_host, const int64_t* lenA
       RTCC3_CHECK(oB >= 0 && oB + eB < lenB[t], "triples: B segment out of bounds");
     }
   }
-  gemm(g, s);
+  if (g.prec == RTCC3_PREC_FP64)
+    frag_seg(g, rt.d, (int)rt.h.size() / 4, s);
+  else
+    gemm(g, s);
 }
 
 // A column-segment product (GemmDesc::cs) after the same check per segment;
@@ -205,8 +210,8 @@ void tangent_gather(Engine& e, const GemmDesc& g, const Groups& gr, int64_t lenA
   }
 }
 
-void tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const int64_t* lenA, const int64_t* lenB,
-                 int64_t lenC, hipStream_t s) {
+void tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
+                 const int64_t* lenB, int64_t lenC, hipStream_t s) {
   struct Term {
     GemmDesc::Seg sg;
     int64_t la, lb;
@@ -247,7 +252,7 @@ void tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const int64_t
       h.store = 0;
       h.atomic = 1;
     }
-    checked_seg_gemm(h, bl_host, la, lb, lenC, s);
+    checked_seg_gemm(h, bl_host, rt, la, lb, lenC, s);
   }
 }
 
@@ -308,10 +313,10 @@ void prod_gather(Engine& e, GemmDesc& g, const Groups& gr, int64_t lenA, int64_t
   checked_gather_gemm(g, gr, lenA, lenB, lenC, s);
   if (e.tangent()) tangent_gather(e, g, gr, lenA, lenB, lenC, s);
 }
-void prod_seg(Engine& e, const GemmDesc& g, const int* bl_host, const int64_t* lenA, const int64_t* lenB,
-              int64_t lenC, hipStream_t s) {
-  checked_seg_gemm(g, bl_host, lenA, lenB, lenC, s);
-  if (e.tangent()) tangent_seg(e, g, bl_host, lenA, lenB, lenC, s);
+void prod_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
+              const int64_t* lenB, int64_t lenC, hipStream_t s) {
+  checked_seg_gemm(g, bl_host, rt, lenA, lenB, lenC, s);
+  if (e.tangent()) tangent_seg(e, g, bl_host, rt, lenA, lenB, lenC, s);
 }
 void prod_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB,
                  const int64_t* lenC, hipStream_t s) {
@@ -372,7 +377,7 @@ void Triples::free_windows() {
   for (auto* ws : {&rhs_windows_, &den_windows_}) {
     for (auto& w : *ws) {
       for (int* p : {w.d_bl, w.d_part, w.d_owned, w.d_canon, w.d_slabs, w.d_orb, w.d_orb_owned, w.d_bk_t3,
-                     w.d_bk_l3, w.d_bk_own})
+                     w.d_bk_l3, w.d_bk_own, w.rt_t3.d, w.rt_l3.d})
         if (p) (void)hipFree(p);
       for (Groups* gr : {&w.gJ, &w.gK})
         for (int* p : {gr->d_key, gr->d_start, gr->d_bl})
@@ -613,6 +618,28 @@ void Triples::upload(Window& w) {
     w.bk_own = sorted(w.owned, 2, 0, 1);
     put(&w.d_bk_own, w.bk_own);
   }
+  // Their row tiles (frag_kernels.h): a run is a stretch of entries that agree
+  // in the two indices the B operands depend on, cut so that the A operands of
+  // its entries (strides up to o v^2 per index) lie within 32-bit byte offsets.
+  auto row_tiles = [&](const std::vector<int>& t, int p0, int p1, int p2) {
+    const int64_t v = d_.v, reach = std::max<int64_t>(0, (((int64_t)1 << 26) - v * v) / (d_.o * v * v));
+    std::vector<int> out;
+    const size_t n = t.size() / 4;
+    for (size_t e = 0; e < n;) {
+      size_t f = e + 1;
+      while (f < n && f - e < (size_t)kFragRun && t[4 * f + p0] == t[4 * e + p0] && t[4 * f + p1] == t[4 * e + p1] &&
+             t[4 * f + p2] - t[4 * e + p2] <= reach)
+        ++f;
+      const int first = (int)out.size() / 4, nt = (int)(((int64_t)(f - e) * v + kFragRows - 1) / kFragRows);
+      for (int q = 0; q < nt; ++q) out.insert(out.end(), {(int)e, (int)(f - e), first, nt});
+      e = f;
+    }
+    return out;
+  };
+  w.rt_t3.h = row_tiles(w.bk_t3, 2, 1, 0);
+  w.rt_l3.h = row_tiles(w.bk_l3, 2, 0, 1);
+  put(&w.rt_t3.d, w.rt_t3.h);
+  put(&w.rt_l3.d, w.rt_l3.h);
   RTCC3_HIP(hipMalloc(&w.d_bl, sizeof(int) * w.bl.size()));
   RTCC3_HIP(hipMemcpy(w.d_bl, w.bl.data(), sizeof(int) * w.bl.size(), hipMemcpyHostToDevice));
   RTCC3_HIP(hipMalloc(&w.d_part, sizeof(int) * w.part.size()));
@@ -794,7 +821,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     set4(g.cC, 0, 0, 0, vb);
     const int64_t lA[2] = {lT2, lOOOV}, lB[2] = {lOVVV_, lT2};
     build_event(s);
-    prod_seg(e, g, w.bk_t3.data(), lA, lB, winlen, s);
+    prod_seg(e, g, w.bk_t3.data(), w.rt_t3, lA, lB, winlen, s);
     build_event(s);
     build_flop_ += 8.0 * nw * v * v2 * (v + o);
   }
@@ -834,7 +861,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       const int64_t lS = (int64_t)max_nw_ * v2 * o;
       const int64_t lA[2] = {t2len, t2len}, lB[2] = {lOOVV, lOOVV};
       build_event(s2);  // same kernel as the builds: timed with them
-      prod_seg(e, g, sblh, lA, lB, lS, s2);
+      prod_seg(e, g, sblh, w.rt_l3, lA, lB, lS, s2);
       build_event(s2);
       build_flop_ += 8.0 * cn * v * (o * v) * (2 * v);
     }
@@ -865,7 +892,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     const int64_t lA[4] = {lLC, lLC, l2len, l2len}, lB[4] = {l2len, l2len, lOVVV_, lOVVV_};
     RTCC3_HIP(hipStreamWaitEvent(s2, ev_t3b_, 0));  // after the t3 build (a no-op when S went first)
     build_event(s2);
-    prod_seg(e, g, w.bk_l3.data(), lA, lB, winlen, s2);
+    prod_seg(e, g, w.bk_l3.data(), w.rt_l3, lA, lB, winlen, s2);
     build_event(s2);
     build_flop_ += 8.0 * nw * v * v2 * (2 * o + 2 * v);
     RTCC3_HIP(hipEventRecord(ev_l3b_, s2));

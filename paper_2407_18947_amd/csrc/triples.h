@@ -27,6 +27,12 @@ struct Groups {
   int* d_bl = nullptr;
 };
 
+// Row tiles of a sorted block table (4 ints each, see frag_kernels.h).
+struct RowTiles {
+  std::vector<int> h;
+  int* d = nullptr;
+};
+
 // A window: a set of ordered occupied triples that is closed under permutation,
 // so every block's P_ijk^abc partners are in it.  The contraction set (all
 // blocks, or the owned ones) is a union of whole permutation orbits as well.
@@ -45,6 +51,7 @@ struct Window {
   // build products: neighbouring entries then share their largest operand
   // blocks, which stay in the L2 cache for them
   std::vector<int> bk_t3, bk_l3, bk_own;
+  RowTiles rt_t3, rt_l3;
   int* d_bl = nullptr;
   int* d_part = nullptr;
   int* d_owned = nullptr;
@@ -104,8 +111,8 @@ class Triples {
     launches = (double)launches_;
   }
   // The segmented store-mode products (the t3 and lambda3 builds and, in the
-  // reduced precisions, the Y1 S intermediate; one kernel): event-timed milliseconds, launches and
-  // algorithmic flops (8 per complex multiply-add).
+  // reduced precisions, the Y1 S intermediate; one kernel): event-timed
+  // milliseconds, launches and algorithmic flops (8 per complex multiply-add).
   void build_timing(double& ms, double& launches, double& flop) const {
     ms = build_ms_;
     launches = (double)build_launches_;
