@@ -17,4 +17,24 @@ constexpr int kFragRun = 64;  // most entries of a run
 // or atomic accumulation, with C contiguous rows of N0 elements at stride sCn1.
 void frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s);
 
+// Products that read the blocks of a window as rows c of v^2 columns and sum
+// over c and over blocks,
+//   C_j[m][n] += alpha_j * sum_blocks sum_c A_j[m][c] B[block][c][n],   n = (p, q) < v^2,
+// A_j at A + cA.(I,J,K) + m*sAm + c, B at B + slot*vb + c*v*vp + p*vp + q and
+// C_j at C + cC.(I,J,K) + m*sCm + n.  Every job reads the same blocks once.
+struct FragJob {
+  const cplx* A;
+  int64_t cA[3], sAm;
+  int64_t lA;  // elements of one block's A operand, (M - 1)*sAm + v
+  int M;
+  cplx* C;
+  int64_t cC[3], sCm;
+  double alpha;
+};
+// bl: nblk block table entries (I, J, K, slot), in an order that keeps each
+// job's output in place over long stretches; group: the usual length of the
+// shortest such stretches.
+void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
+                 hipStream_t s);
+
 }  // namespace rtcc3

@@ -15,6 +15,9 @@
 // a workgroup share.
 #include "frag_kernels.h"
 
+#include <algorithm>
+#include <vector>
+
 namespace rtcc3 {
 
 namespace {
@@ -42,11 +45,13 @@ __device__ __forceinline__ d2v frag_load(__amdgpu_buffer_rsrc_t r, int voff, int
 template <int IB, int JB>
 struct Acc {
   d4 p1[IB][JB], p2[IB][JB], p3[IB][JB];
+  __device__ __forceinline__ void clear(int i) {
+#pragma unroll
+    for (int j = 0; j < JB; ++j) p1[i][j] = p2[i][j] = p3[i][j] = d4{0, 0, 0, 0};
+  }
   __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int i = 0; i < IB; ++i)
-#pragma unroll
-      for (int j = 0; j < JB; ++j) p1[i][j] = p2[i][j] = p3[i][j] = d4{0, 0, 0, 0};
+    for (int i = 0; i < IB; ++i) clear(i);
   }
   __device__ __forceinline__ void step(const d2v* a, const d2v* b) {
     double as[IB], bd[JB], bs[JB];
@@ -77,17 +82,17 @@ struct Acc {
 };
 
 // acc += sum over k < len of A[.][k] B[k][.]: lane offsets ao, bo (bytes, at
-// k = l/16) into ra, rb; sak, sbk bytes per k.  Two register sets alternate as
+// k = l/16) into ra (one resource per row block), rb; sak, sbk bytes per k.  Two register sets alternate as
 // the step in flight.  A last partial step of four reads its missing k at the
 // last valid one and multiplies by a zero A.
 template <int IB, int JB>
-__device__ __forceinline__ void contract(Acc<IB, JB>& acc, __amdgpu_buffer_rsrc_t ra, const int* ao, int sak,
+__device__ __forceinline__ void contract(Acc<IB, JB>& acc, const __amdgpu_buffer_rsrc_t* ra, const int* ao, int sak,
                                          __amdgpu_buffer_rsrc_t rb, const int* bo, int sbk, int len, int kl) {
   d2v a0[IB], b0[JB], a1[IB], b1[JB];
   int sa = 0, sb = 0;
   auto load = [&](d2v* a, d2v* b) {
 #pragma unroll
-    for (int i = 0; i < IB; ++i) a[i] = frag_load(ra, ao[i], sa);
+    for (int i = 0; i < IB; ++i) a[i] = frag_load(ra[i], ao[i], sa);
 #pragma unroll
     for (int j = 0; j < JB; ++j) b[j] = frag_load(rb, bo[j], sb);
     sa += 4 * sak;
@@ -113,7 +118,7 @@ __device__ __forceinline__ void contract(Acc<IB, JB>& acc, __amdgpu_buffer_rsrc_
     const int back = min(kl, rest - 1) - kl;  // 0 where the lane's k is valid
 #pragma unroll
     for (int i = 0; i < IB; ++i) {
-      const d2v z = frag_load(ra, ao[i] + back * sak, sa);
+      const d2v z = frag_load(ra[i], ao[i] + back * sak, sa);
       a1[i] = d2v{back == 0 ? z[0] : 0.0, back == 0 ? z[1] : 0.0};
     }
 #pragma unroll
@@ -205,7 +210,8 @@ __global__ __launch_bounds__(256, 3) void frag_seg_kernel(FragSeg d) {
     for (int j = 0; j < JB; ++j) bo[j] = nc[j] * (int)sizeof(cplx) + kl * sbk;
     // resources from the run's first operand blocks on; every offset is inside
     // the operands (host-checked below 2^31 bytes)
-    const auto ra = rsrc(g.A + g.cA[0] * I0 + g.cA[1] * J0 + g.cA[2] * K0, (1 << 27) - 1);
+    const auto r0 = rsrc(g.A + g.cA[0] * I0 + g.cA[1] * J0 + g.cA[2] * K0, (1 << 27) - 1);
+    const __amdgpu_buffer_rsrc_t ra[IB] = {r0, r0};
     const auto rb = rsrc(g.B + g.cB[0] * I0 + g.cB[1] * J0 + g.cB[2] * K0, (1 << 27) - 1);
     contract<IB, JB>(acc, ra, ao, sak, rb, bo, sbk, g.len, kl);
   }
@@ -247,7 +253,206 @@ __global__ __launch_bounds__(256, 3) void frag_seg_kernel(FragSeg d) {
     }
 }
 
+// A wave's share of frag_gather: two 16-row blocks by 32 columns, or one by 64.
+struct FragUnit {
+  int job[2], row[2];  // row blocks (job, first row); row[1] unused when single
+  int single;
+  int half;  // which 32 of the workgroup's 64 columns (pairs)
+};
+constexpr int kMaxUnits = 64;
+struct FragGather {
+  FragJob job[2];
+  const cplx* B;
+  const int* bl;
+  int v, vp, nblk, chunk, ncol, nunit;
+  FragUnit unit[kMaxUnits];
+};
+
+template <int IB, int JB>
+__device__ __forceinline__ void gather_unit(const FragGather& d, const FragUnit& u, int n0, int p0, int p1) {
+  typedef const __attribute__((address_space(4))) int cint;  // the table is read-only: scalar loads
+  cint* bl = (cint*)(uintptr_t)d.bl;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
+  const int v = d.v, N = v * v;
+  const int64_t va = (int64_t)v * d.vp, vb = va * v;
+  const float inv = 1.0f / (float)v;
+  const FragJob* jb[IB];
+  int ao[IB], bo[JB], row[IB], la[IB];
+  bool nok[JB];
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    jb[i] = &d.job[u.job[i]];
+    row[i] = u.row[i];
+    la[i] = (int)jb[i]->lA;
+    asm volatile("" : "+s"(la[i]));  // held in a register, not loaded again at each use
+    ao[i] = (min(row[i] + l16, jb[i]->M - 1) * (int)jb[i]->sAm + kl) * (int)sizeof(cplx);
+  }
+#pragma unroll
+  for (int j = 0; j < JB; ++j) {
+    const int n = n0 + 16 * j + l16, nn = min(n, N - 1);
+    nok[j] = n < N;
+    bo[j] = (quot(nn, v, inv) * (d.vp - v) + nn + kl * (int)va) * (int)sizeof(cplx);
+  }
+  Acc<IB, JB> acc;
+  acc.clear();
+  // The next D steps (of four c) in registers: the blocks stream from HBM, and
+  // D steps are about 3000 cycles of products per wave.  A slot is refilled as
+  // soon as its step is done, with the block's step D further on or, past its
+  // end, with the next block's step that belongs into the slot: one load with
+  // scalar selects, so that it never waits.  Rows c >= v of B lie beyond the
+  // block's resource and read as zero; A is masked there.
+  constexpr int D = 4;
+  const int ns = (v + 3) >> 2, rest = v & 3;
+  d2v a[D][IB], b[D][JB];
+  const cplx *pa[IB], *qa[IB], *pb, *qb;  // this block's and the next one's operands
+  auto block = [&](int p, const cplx** xa, const cplx*& xb) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+      xa[i] = jb[i]->A + jb[i]->cA[0] * bl[4 * p] + jb[i]->cA[1] * bl[4 * p + 1] + jb[i]->cA[2] * bl[4 * p + 2];
+    xb = d.B + bl[4 * p + 3] * vb;
+  };
+  auto load = [&](int u, const cplx* const* xa, const cplx* xb, int q) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i) a[u][i] = frag_load(rsrc(xa[i], la[i]), ao[i], q * 4 * (int)sizeof(cplx));
+    const auto rb = rsrc(xb, vb);
+#pragma unroll
+    for (int j = 0; j < JB; ++j) b[u][j] = frag_load(rb, bo[j], q * 4 * (int)va * (int)sizeof(cplx));
+  };
+  block(p0, pa, pb);
+#pragma unroll
+  for (int u = 0; u < D; ++u) load(u, pa, pb, u);
+  for (int p = p0; p < p1; ++p) {
+    const bool last = p + 1 == p1;
+    const int q = last ? p : p + 1;
+    block(q, qa, qb);
+    for (int k = 0; k < ns; k += D) {
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        if (k + u >= ns) break;
+        if (k + u + 1 == ns && rest) {
+#pragma unroll
+          for (int i = 0; i < IB; ++i) {
+            a[u][i] = d2v{kl < rest ? a[u][i][0] : 0.0, kl < rest ? a[u][i][1] : 0.0};
+            asm volatile("" : "+v"(a[u][i]));  // a branch: these selects belong to one step of a block only
+          }
+        }
+        acc.step(a[u], b[u]);
+        __builtin_amdgcn_sched_barrier(0);  // the refill follows the products of its slot
+        const bool in = k + u + D < ns;
+        const cplx* xa[IB];
+#pragma unroll
+        for (int i = 0; i < IB; ++i) xa[i] = in ? pa[i] : qa[i];
+        load(u, xa, in ? pb : qb, in ? k + u + D : u);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i) pa[i] = qa[i];
+    pb = qb;
+    const int I = bl[4 * p], J = bl[4 * p + 1], K = bl[4 * p + 2];
+    const int dI = bl[4 * q] - I, dJ = bl[4 * q + 1] - J, dK = bl[4 * q + 2] - K;
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const FragJob& g = *jb[i];
+      if (!last && g.cC[0] * dI + g.cC[1] * dJ + g.cC[2] * dK == 0) continue;  // the next block has the same output
+      cplx* C = g.C + g.cC[0] * I + g.cC[1] * J + g.cC[2] * K;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = row[i] + 4 * r + kl;
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+          if (nok[j]) {
+            const d2v z = acc.value(i, j, r);
+            cplx* c = C + m * g.sCm + (n0 + 16 * j + l16);
+            unsafeAtomicAdd(&c->re, g.alpha * z[0]);
+            unsafeAtomicAdd(&c->im, g.alpha * z[1]);
+          }
+      }
+      acc.clear(i);
+    }
+  }
+}
+
+// The waves of a chunk of the block list and 64 columns are its units: the
+// 16-row blocks of all jobs, two and two by 32 columns or a last one by 64 (12
+// MFMAs a step either way).  They read the same rows of B, which come from HBM
+// once and from the caches for the other units; waves are numbered through, so
+// that four of them fill a workgroup whatever the number of units (as
+// workgroups of a chunk's units, five at o=15, v=57, only one would fit on a
+// CU: 8.5 ms).  At o=15, v=57 Z_i and the Y2 product, 6.9 ms apart, take 5.9 ms,
+// the two X2 products 3.1 instead of 3.85 ms; 0.71 -> 0.48 and 0.39 -> 0.26 ms at
+// o=10, v=38.  Bound by the matrix cores (4.0 ms of MFMAs) and, for the X2
+// pair, by the 10 GB it reads.
+__global__ __launch_bounds__(256, 2) void frag_gather_kernel(FragGather d) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t w = (int64_t)xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * 4 + wave;
+  const int lg = (int)(w / d.nunit);
+  const FragUnit& u = d.unit[w % d.nunit];
+  const int p0 = lg / d.ncol * d.chunk, p1 = min(d.nblk, p0 + d.chunk);
+  const int n0 = lg % d.ncol * 64 + (u.single ? 0 : 32 * u.half);
+  if (p0 >= p1 || n0 >= d.v * d.v) return;
+  if (u.single)
+    gather_unit<1, 4>(d, u, n0, p0, p1);
+  else
+    gather_unit<2, 2>(d, u, n0, p0, p1);
+}
+
 }  // namespace
+
+void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
+                 hipStream_t s) {
+  if (nblk <= 0 || njob <= 0) return;
+  RTCC3_CHECK(njob <= 2 && v >= 1 && vp >= v && group >= 1, "frag: bad gathered product");
+  RTCC3_CHECK((int64_t)v * v * vp < (1LL << 27) && (int64_t)v * v < (1 << 22), "frag: product too large");
+  FragGather d;
+  d.B = B;
+  d.bl = bl;
+  d.v = v;
+  d.vp = vp;
+  d.nblk = nblk;
+  d.ncol = (v * v + 63) / 64;
+  d.nunit = 0;
+  struct RowBlock {
+    int job, row;
+  };
+  std::vector<RowBlock> rb;
+  for (int j = 0; j < njob; ++j) {
+    RTCC3_CHECK(jobs[j].M >= 1 && jobs[j].lA >= (int64_t)(jobs[j].M - 1) * jobs[j].sAm + v && jobs[j].lA + 4 < (1LL << 27),
+                "frag: gathered operand too large");
+    d.job[j] = jobs[j];
+    for (int m = 0; m < jobs[j].M; m += 16) rb.push_back({j, m});
+  }
+  auto launch = [&]() {
+    // Chunks of whole groups (stretches with one output of a job: fewer flushes)
+    // for at least eight rounds of the chip's 2048 waves; below one group a
+    // chunk, shorter ones down to two rounds (Z_i and Y2 at o=10, v=38: chunks of
+    // 1, 5 and 11 blocks took 1.5, 0.50 and 0.48 ms).
+    const int64_t waves = (int64_t)nblk * d.ncol * d.nunit;
+    const int64_t c = waves / (8 * 2048) / group;
+    d.chunk = (int)(c >= 1 ? c * group : std::max<int64_t>(1, std::min<int64_t>(group, waves / (2 * 2048))));
+    const int64_t nw = (int64_t)((nblk + d.chunk - 1) / d.chunk) * d.ncol * d.nunit;
+    RTCC3_CHECK(nw < (1LL << 31), "frag: product too large");
+    hipLaunchKernelGGL(frag_gather_kernel, dim3((unsigned)((nw + 3) / 4)), dim3(256), 0, s, d);
+    RTCC3_HIP(hipGetLastError());
+    d.nunit = 0;
+  };
+  for (size_t q = 0; q < rb.size();) {
+    const bool pair = q + 1 < rb.size();
+    for (int h = 0; h < (pair ? 2 : 1); ++h) {
+      FragUnit& u = d.unit[d.nunit++];
+      u.job[0] = rb[q].job;
+      u.row[0] = rb[q].row;
+      u.job[1] = pair ? rb[q + 1].job : rb[q].job;
+      u.row[1] = pair ? rb[q + 1].row : rb[q].row;
+      u.single = !pair;
+      u.half = h;
+    }
+    q += pair ? 2 : 1;
+    if (d.nunit + 2 > kMaxUnits) launch();
+  }
+  if (d.nunit > 0) launch();
+}
 
 void frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s) {
   if (nrt <= 0) return;

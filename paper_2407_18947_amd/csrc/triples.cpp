@@ -324,6 +324,46 @@ void prod_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA,
   if (e.tangent()) tangent_colseg(e, g, bl_host, lenA, lenB, lenC, s);
 }
 
+// Jobs over the blocks of a window (FragJob), after the same check per job and
+// block, with their derivatives in tangent mode.  lenA, lenC: lengths of each
+// job's tensors; lenB that of the window buffer.
+void prod_frag_gather(Engine& e, const std::vector<FragJob>& jobs, const int64_t* lenA, const int64_t* lenC,
+                      const cplx* B, int64_t lenB, int v, int vp, const std::vector<int>& bl_host, const int* bl,
+                      int group, hipStream_t s) {
+  const int nblk = (int)bl_host.size() / 4;
+  const int64_t vb = (int64_t)v * v * vp;
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    const FragJob& g = jobs[j];
+    const int64_t eA = (int64_t)(g.M - 1) * g.sAm + v - 1, eC = (int64_t)(g.M - 1) * g.sCm + (int64_t)v * v - 1;
+    auto dot = [](const int64_t* c, const int* q) { return c[0] * q[0] + c[1] * q[1] + c[2] * q[2]; };
+    for (int p = 0; p < nblk; ++p) {
+      const int* q = &bl_host[4 * p];
+      const int64_t oA = dot(g.cA, q), oC = dot(g.cC, q);
+      RTCC3_CHECK(oA >= 0 && oA + eA < lenA[j], "triples: A operand out of bounds");
+      RTCC3_CHECK(oC >= 0 && oC + eC < lenC[j], "triples: C operand out of bounds");
+      RTCC3_CHECK(q[3] >= 0 && (q[3] + 1) * vb <= lenB, "triples: B operand out of bounds");
+    }
+  }
+  frag_gather(jobs.data(), (int)jobs.size(), B, v, vp, bl, nblk, group, s);
+  if (!e.tangent()) return;
+  const cplx* bt = e.twin(B);
+  std::vector<const cplx*> at;
+  for (const FragJob& g : jobs) at.push_back(e.twin(g.A));
+  std::vector<FragJob> jb, ja;
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    FragJob h = jobs[j];
+    if (!bt && !at[j]) continue;
+    h.C = e.twin_out(h.C);
+    if (bt) jb.push_back(h);
+    if (at[j]) {
+      h.A = at[j];
+      ja.push_back(h);
+    }
+  }
+  if (bt) frag_gather(jb.data(), (int)jb.size(), bt, v, vp, bl, nblk, group, s);
+  frag_gather(ja.data(), (int)ja.size(), B, v, vp, bl, nblk, group, s);
+}
+
 // The innermost index of a window block padded to a multiple of 8.
 int pad8(int v) { return (v + 7) / 8 * 8; }
 
@@ -377,7 +417,7 @@ void Triples::free_windows() {
   for (auto* ws : {&rhs_windows_, &den_windows_}) {
     for (auto& w : *ws) {
       for (int* p : {w.d_bl, w.d_part, w.d_owned, w.d_canon, w.d_slabs, w.d_orb, w.d_orb_owned, w.d_bk_t3,
-                     w.d_bk_l3, w.d_bk_own, w.rt_t3.d, w.rt_l3.d})
+                     w.d_bk_l3, w.d_bk_own, w.d_gat_t3, w.d_gat_l3, w.rt_t3.d, w.rt_l3.d})
         if (p) (void)hipFree(p);
       for (Groups* gr : {&w.gJ, &w.gK})
         for (int* p : {gr->d_key, gr->d_start, gr->d_bl})
@@ -614,6 +654,11 @@ void Triples::upload(Window& w) {
   w.bk_l3 = sorted(w.bl, 2, 0, 1);
   put(&w.d_bk_t3, w.bk_t3);
   put(&w.d_bk_l3, w.bk_l3);
+  // the contraction blocks in the order of the gathered products' outputs
+  w.gat_t3 = sorted(cb, 0, 2, 1);
+  w.gat_l3 = sorted(cb, 1, 2, 0);
+  put(&w.d_gat_t3, w.gat_t3);
+  put(&w.d_gat_l3, w.gat_l3);
   if (!w.owned.empty()) {
     w.bk_own = sorted(w.owned, 2, 0, 1);
     put(&w.d_bk_own, w.bk_own);
@@ -933,6 +978,8 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     // along with products that read the block anyway (tail columns of the Y1
     // product below; the f~ term inside tb_X2c); else one sweep per block
     const bool tails = o <= 15;
+    // the 16-wide gathered products in FP64 (the split precisions too)
+    const bool frag16 = pr == RTCC3_PREC_FP64 || (pr != RTCC3_PREC_FP32 && o <= 16);
     if (!tails) {
       RTCC3_CHECK(!e.tangent(), "triples: derivatives need o <= 15");
       launch_small_t3(T, cbl, cn, Lov, F, l2, X1, X2p, Z34, o, v, vp, 3, s);
@@ -986,33 +1033,43 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     //   -2 T_KJI G[K][I] -> -2 T_IJK G[I][K]   (I <-> K)
     //      T_KIJ G[K][I] ->    T_IJK G[I][J] into X2p[x][K]   ((K,I,J) -> (I,J,K))
     //      T_IJK G[K][I] stays.
-    // Two gathered products, over the blocks of each J and of each K, without atomics:
-    auto x2b = [&](const cplx* Bp, const int64_t* cb, const int64_t* cc, const Groups& gr) {
-      GemmDesc g = base((int)v2, o, v * gr.max, 0, nullptr, pr);
-      g.K0 = v;
-      g.M0 = v;  // m = (a,b)
-      g.A = T;   // A[(a,b)][c] = T_IJK[a][b][c]
-      g.sAm1 = va;
-      g.sAm0 = vp;
-      g.sAk0 = 1;
-      set4(g.cA, 0, 0, 0, vb);
-      g.B = Bp;
-      g.sBk0 = 1;
-      g.sBn0 = v;
-      std::memcpy(g.cB, cb, sizeof(g.cB));
-      g.C = X2p;
-      g.sCm1 = v;
-      g.sCm0 = 1;
-      g.sCn0 = (int64_t)o * v2;
-      std::memcpy(g.cC, cc, sizeof(g.cC));
-      prod_gather(e, g, gr, winlen, lOOOV, oovv, s);
-    };
-    {
-      // (G[K][I] - 2 G[I][K]) is tb_X2c at [K][I]; G[I][J] is tb_X2b at [I][J]
-      const int64_t cbJ[4] = {(int64_t)o * v, 0, (int64_t)o * o * v, 0}, ccJ[4] = {0, v2, 0, 0};
-      const int64_t cbK[4] = {(int64_t)o * o * v, (int64_t)o * v, 0, 0}, ccK[4] = {0, 0, v2, 0};
-      x2b(gX2c, cbJ, ccJ, w.gJ);
-      x2b(gX2b, cbK, ccK, w.gK);
+    // In FP64 both read the block as T_KIJ[c][(a,b)], once for the two.  (The
+    // bf16 splits run these in FP64 too, up to o = 16.)
+    if (frag16) {
+      const int64_t oov = (int64_t)o * o * v, ovl = (int64_t)o * v, ov2 = (int64_t)o * v2;
+      const std::vector<FragJob> jobs = {{gX2c, {oov, ovl, 0}, v, ovl, o, X2p, {0, 0, v2}, ov2, 1.0},
+                                         {gX2b, {0, oov, ovl}, v, ovl, o, X2p, {v2, 0, 0}, ov2, 1.0}};
+      const int64_t lA[2] = {lOOOV, lOOOV}, lC[2] = {oovv, oovv};
+      prod_frag_gather(e, jobs, lA, lC, T, winlen, v, vp, w.gat_t3, w.d_gat_t3, o, s);
+    } else {
+      // two gathered products, over the blocks of each J and of each K, without atomics
+      auto x2b = [&](const cplx* Bp, const int64_t* cb, const int64_t* cc, const Groups& gr) {
+        GemmDesc g = base((int)v2, o, v * gr.max, 0, nullptr, pr);
+        g.K0 = v;
+        g.M0 = v;  // m = (a,b)
+        g.A = T;   // A[(a,b)][c] = T_IJK[a][b][c]
+        g.sAm1 = va;
+        g.sAm0 = vp;
+        g.sAk0 = 1;
+        set4(g.cA, 0, 0, 0, vb);
+        g.B = Bp;
+        g.sBk0 = 1;
+        g.sBn0 = v;
+        std::memcpy(g.cB, cb, sizeof(g.cB));
+        g.C = X2p;
+        g.sCm1 = v;
+        g.sCm0 = 1;
+        g.sCn0 = (int64_t)o * v2;
+        std::memcpy(g.cC, cc, sizeof(g.cC));
+        prod_gather(e, g, gr, winlen, lOOOV, oovv, s);
+      };
+      {
+        // (G[K][I] - 2 G[I][K]) is tb_X2c at [K][I]; G[I][J] is tb_X2b at [I][J]
+        const int64_t cbJ[4] = {(int64_t)o * v, 0, (int64_t)o * o * v, 0}, ccJ[4] = {0, v2, 0, 0};
+        const int64_t cbK[4] = {(int64_t)o * o * v, (int64_t)o * v, 0, 0}, ccK[4] = {0, 0, v2, 0};
+        x2b(gX2c, cbJ, ccJ, w.gJ);
+        x2b(gX2b, cbK, ccK, w.gK);
+      }
     }
     {  // Y2: sum_de (da|eK)~ lambda[d][b][e] into Y2p[I][J][a][b]; lambda_IJK[d][b][e] =
        // lambda_JIK[b][d][e], read with (d,e) contiguous
@@ -1040,7 +1097,20 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       set4(g.cC, (int64_t)o * v2, v2, 0, 0);
       prod(e, g, cblh, lOVVV, winlen, oovv, s2);
     }
-    {  // Y2: -sum_d lambda[(a,b)][d] (xI|dK)~ into Y2p[x][J], summed over the blocks of each J
+    // Y2: -sum_d lambda[(a,b)][d] (xI|dK)~ into Y2p[x][J] and
+    // Zi[J][b][(d,e)] += sum_c t2[K][I][b][c] lambda[c][(d,e)] (block (k,i,j) = (I,J,K)) for term 11, and in FP64
+    // terms 9 and 10, of Y1: terms 9 and 10 sum t_jk^bc lambda_lkj^acd and t_jk^bc lambda_jkl^acd over j, k, c,
+    // which with lambda_{sigma(ijk)}^{sigma(abc)} = lambda_ijk^abc are Z_l^{bad} and Z_l^{bda}.
+    const int64_t ov2l = (int64_t)o * v2;
+    const FragJob jZ{t2, {v2, 0, ov2l}, v, v2, v, Zi, {0, v3, 0}, v2, 1.0};
+    // the first reads the block as lambda_KIJ[d][(a,b)]
+    const FragJob jY{gY2b, {(int64_t)o * v, (int64_t)o * o * v, 0}, v, ov, o, Y2p, {0, 0, v2}, ov2l, -1.0};
+    if (pr == RTCC3_PREC_FP64) {
+      const int64_t lA[2] = {t2len, lOOOV}, lC[2] = {lOVVV, oovv};
+      prod_frag_gather(e, {jZ, jY}, lA, lC, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
+    } else if (frag16) {
+      prod_frag_gather(e, {jY}, &lOOOV, &oovv, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
+    } else {  // summed over the blocks of each J
       GemmDesc g = base((int)v2, o, v * w.gJ.max, 0, nullptr, pr);
       g.K0 = v;
       g.M0 = v;  // m = (a,b)
@@ -1169,9 +1239,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
                          0, 0});
       seg_product(L, specs, s2);
     }
-    {  // term 11, and in FP64 terms 9 and 10: Zi[J][b][(d,e)] += sum_c t2[K][I][b][c] lambda[c][(d,e)]   (block (k,i,j) = (I,J,K)),
-       // summed over the blocks of each J.  Terms 9 and 10 sum t_jk^bc lambda_lkj^acd and t_jk^bc lambda_jkl^acd
-       // over j, k, c, which with lambda_{sigma(ijk)}^{sigma(abc)} = lambda_ijk^abc are Z_l^{bad} and Z_l^{bda}.
+    if (pr != RTCC3_PREC_FP64) {  // Zi, summed over the blocks of each J
       GemmDesc g = base(v, (int)v2, v * w.gJ.max, 0, nullptr, pr);
       g.K0 = v;
       g.A = t2;

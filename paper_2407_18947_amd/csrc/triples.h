@@ -52,6 +52,9 @@ struct Window {
   // blocks, which stay in the L2 cache for them
   std::vector<int> bk_t3, bk_l3, bk_own;
   RowTiles rt_t3, rt_l3;
+  // the contraction blocks by (I, K, J) and by (J, K, I), for the gathered
+  // products over t3 and over lambda3
+  std::vector<int> gat_t3, gat_l3;
   int* d_bl = nullptr;
   int* d_part = nullptr;
   int* d_owned = nullptr;
@@ -62,6 +65,8 @@ struct Window {
   int* d_bk_t3 = nullptr;
   int* d_bk_l3 = nullptr;
   int* d_bk_own = nullptr;
+  int* d_gat_t3 = nullptr;
+  int* d_gat_l3 = nullptr;
 };
 
 class Triples {
