@@ -217,13 +217,13 @@ View Engine::diag(View v, int d0, int d1) {
   return w;
 }
 
-cplx* Engine::scratch(int64_t n) {
+cplx* Engine::scratch(int64_t n, hipStream_t on) {
   Scratch* sc = nullptr;
   for (auto& x : scratch_)
-    if (x.stream == stream) sc = &x;
+    if (x.stream == on) sc = &x;
   if (!sc) {
     if (sealed_) throw Error(-4, "engine: scratch for a new stream after the context was set up");
-    scratch_.push_back(Scratch{stream, nullptr, 0});
+    scratch_.push_back(Scratch{on, nullptr, 0});
     sc = &scratch_.back();
   }
   if (n > sc->n) {

@@ -53,9 +53,11 @@ class Engine {
   cplx* data(int buf) { return bufs_[buf].p; }
   int64_t size(int buf) { return bufs_[buf].n; }
 
-  // The relayout scratch of the current stream, grown to n elements (what
-  // einsum takes; also to reserve it for a later evaluation).
-  cplx* scratch(int64_t n);
+  // The relayout scratch of the current (or the given) stream, grown to n
+  // elements: what einsum takes, also to reserve it for a later evaluation, and
+  // for operands that a kernel of that stream needs in another order.
+  cplx* scratch(int64_t n) { return scratch(n, stream); }
+  cplx* scratch(int64_t n, hipStream_t on);
 
   static View slice(View v, int dim, int64_t lo, int64_t hi);
   static View permute(View v, std::vector<int> perm);  // out dim d = in dim perm[d]

@@ -37,4 +37,26 @@ struct FragJob {
 void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
                  hipStream_t s);
 
+// Products that read the blocks of a window as rows k < v^2 of v columns b, and
+// whose other operand depends on the block table's K only,
+//   C_j[I][J][m][b] += sum_K sum_k A_j[K][m][k] Z[IJK][k][b],
+// Z one block, or 2 X0 - X1 - X2 of three (nstream = 3), the blocks at slots
+// part[6 n + perm[w]] of entry n's orderings.  A_j at A + K*cAK + m*sAm + k, C_j
+// at C + cC.(I,J) + m*sCm + b*sCb (atomic adds).  The columns of all entries of a
+// K are numbered through and cut into fragments of up to 16 (4 ints each: the
+// first column's entry in bl and its b, the number of columns, 0) whose
+// entries share K and whose blocks lie within 2^31 bytes of each other.
+struct ColsJob {
+  const cplx* A;
+  int64_t cAK, sAm;
+  int M;
+  cplx* C;
+  int64_t cC[2], sCm, sCb;
+};
+// pack: space for frag_cols_pack() elements, used on s only until the product is
+// done; o: the extent of K.
+void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int nstream, int v, int vp,
+               const int* part, const int* bl, const int* frags, int nfrag, int o, cplx* pack, hipStream_t s);
+int64_t frag_cols_pack(const int* rows, int njob, int o, int v);
+
 }  // namespace rtcc3

@@ -398,7 +398,265 @@ __global__ __launch_bounds__(256, 2) void frag_gather_kernel(FragGather d) {
     gather_unit<2, 2>(d, u, n0, p0, p1);
 }
 
+// A operands of frag_cols in the order the waves read them: the panel of K and
+// row block i holds, step of four k by step, the 64 lanes' elements (l%16 the
+// row, l/16 the k), zero beyond the operand.
+struct ColsPack {
+  ColsJob job[2];
+  int nrb[2], njob, n, steps;  // row blocks per job, extent of K, steps with the partial one
+  int64_t v2;
+  cplx* dst;
+};
+__global__ __launch_bounds__(256) void cols_pack_kernel(ColsPack d) {
+  const int nrb = d.nrb[0] + d.nrb[1];
+  const int64_t total = (int64_t)d.n * nrb * d.steps * 64;
+  for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < total; x += (int64_t)gridDim.x * 256) {
+    const int l = (int)(x & 63);
+    const int64_t t = x >> 6;
+    const int q = (int)(t % d.steps);
+    const int64_t p = t / d.steps;
+    const int i = (int)(p % nrb), K = (int)(p / nrb);
+    const ColsJob& g = d.job[i < d.nrb[0] ? 0 : 1];
+    const int m = 16 * (i < d.nrb[0] ? i : i - d.nrb[0]) + (l & 15);
+    const int64_t k = 4 * (int64_t)q + (l >> 4);
+    d.dst[x] = m < g.M && k < d.v2 ? g.A[g.cAK * K + m * g.sAm + k] : cplx{0, 0};
+  }
+}
+
+// A wave's row blocks in frag_cols.
+struct ColsUnit {
+  int nb;
+  int job[5], row[5], panel[5];
+};
+constexpr int kMaxColsUnits = 32;
+struct FragCols {
+  ColsJob job[2];
+  const cplx* B;
+  const int* bl;
+  const int* part;
+  const int4* frag;
+  const cplx* pack;  // panels of the row blocks, npanel per K
+  int npanel;
+  int perm[3];
+  int v, vp, nfrag, nunit, steps, nsplit;  // full steps of four k in all, and per split
+  ColsUnit unit[kMaxColsUnits];
+};
+
+template <int IB, int NS>
+__device__ __forceinline__ void cols_unit(const FragCols& d, const ColsUnit& u, int f, int split) {
+  constexpr int D = 3;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
+  const int v = d.v;
+  const int64_t vb = (int64_t)v * v * d.vp;
+  const int4 fr = d.frag[f];
+  const bool ok = l16 < fr.z;
+  int e = fr.x, b = fr.y + (ok ? l16 : 0);
+  while (b >= v) {
+    b -= v;
+    ++e;
+  }
+  const int I = d.bl[4 * e], J = d.bl[4 * e + 1], n = d.bl[4 * e + 3];
+  const int K = __builtin_amdgcn_readfirstlane(d.bl[4 * e + 2]);  // the same for all columns of a fragment
+  // B: one resource per stream from the lowest of the lanes' blocks on (the
+  // table keeps a fragment's blocks within 2^31 bytes of each other)
+  __amdgpu_buffer_rsrc_t rb[NS];
+  int bo[NS];
+#pragma unroll
+  for (int w = 0; w < NS; ++w) {
+    const int slot = d.part[6 * n + d.perm[w]];
+    int lo = slot;
+#pragma unroll
+    for (int x = 1; x < 16; x <<= 1) lo = min(lo, __shfl_xor(lo, x));
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    rb[w] = __builtin_amdgcn_make_buffer_rsrc((void*)(d.B + lo * vb), 0, -1, kRsrcWord3);
+    bo[w] = (int)(((uint32_t)(slot - lo) * (uint32_t)vb + (uint32_t)(b + kl * d.vp)) * (uint32_t)sizeof(cplx));
+  }
+  __amdgpu_buffer_rsrc_t ra[IB];
+  int ao[IB];
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const int64_t len = (int64_t)((v * v + 3) / 4) * 64;
+    ra[i] = rsrc(d.pack + ((int64_t)K * d.npanel + u.panel[i]) * len, len);
+    ao[i] = lane * (int)sizeof(cplx);
+  }
+  const int sbk = 4 * d.vp * (int)sizeof(cplx);
+  Acc<IB, 1> acc;
+  acc.clear();
+  d2v a[D][IB], x[D][NS];
+  auto load = [&](int r, int q) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i) a[r][i] = frag_load(ra[i], ao[i], q * 64 * (int)sizeof(cplx));
+#pragma unroll
+    for (int w = 0; w < NS; ++w) x[r][w] = frag_load(rb[w], bo[w], q * sbk);
+  };
+  auto step = [&](const d2v* ar, const d2v* xr) {
+    d2v z = xr[0];
+    if constexpr (NS == 3) {
+      const d2v t{xr[1][0] + xr[2][0], xr[1][1] + xr[2][1]};
+      z = d2v{__builtin_fma(2.0, xr[0][0], -t[0]), __builtin_fma(2.0, xr[0][1], -t[1])};
+    }
+    acc.step(ar, &z);
+  };
+  const int q0 = split * d.steps / d.nsplit, q1 = (split + 1) * d.steps / d.nsplit;
+  if (q0 < q1) {
+#pragma unroll
+    for (int r = 0; r < D; ++r) load(r, min(q0 + r, q1 - 1));
+    for (int q = q0; q < q1; q += D) {
+#pragma unroll
+      for (int r = 0; r < D; ++r) {
+        if (q + r >= q1) break;
+        step(a[r], x[r]);
+        __builtin_amdgcn_sched_barrier(0);  // the refill follows the products of its slot
+        load(r, min(q + r + D, q1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  const int rest = (v * v) & 3;
+  if (rest && split + 1 == d.nsplit) {  // the last k: A is zero at the missing ones, B reads a valid k
+    const int back = min(kl, rest - 1) - kl;
+    d2v at[IB], xt[NS];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) at[i] = frag_load(ra[i], ao[i], d.steps * 64 * (int)sizeof(cplx));
+#pragma unroll
+    for (int w = 0; w < NS; ++w) xt[w] = frag_load(rb[w], bo[w] + back * d.vp * (int)sizeof(cplx), d.steps * sbk);
+    step(at, xt);
+  }
+  if (!ok) return;
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const ColsJob& g = d.job[u.job[i]];
+    cplx* C = g.C + g.cC[0] * I + g.cC[1] * J + b * g.sCb;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = u.row[i] + 4 * r + kl;
+      if (m >= g.M) continue;
+      const d2v z = acc.value(i, 0, r);
+      cplx* c = C + m * g.sCm;
+      unsafeAtomicAdd(&c->re, z[0]);
+      unsafeAtomicAdd(&c->im, z[1]);
+    }
+  }
+}
+
+// X2 (three streams) and Y2 with R8 (one).  Bound by the matrix cores (Y2: MFMA
+// busy 0.88 of the SIMD cycles) and, for X2, by the three orderings of each
+// block that pass through the L2.  o=15, v=57, alone: X2 5.9 -> 5.6 ms, Y2 and R8
+// 7.6 -> 5.4; o=10, v=38: 0.73 -> 0.45 and 0.85 -> 0.45, since columns of all
+// entries of a K are numbered through and rows come in blocks of 16.  A read
+// straight from the integrals (64-byte pieces of rows 52 KB apart) instead of
+// packed panels made that 9.6 and 7.8 ms.
+// One wave per 16 columns, group of row blocks and split of k, four to a
+// workgroup as they come (splits outermost, so that the waves that run
+// together read the same stretch of k of blocks they share).
+template <int NS>
+__global__ __launch_bounds__(256, 2) void frag_cols_kernel(FragCols d) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t w = (int64_t)xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * 4 + wave;
+  const int split = (int)(w / ((int64_t)d.nfrag * d.nunit));
+  if (split >= d.nsplit) return;
+  const int f = (int)(w / d.nunit % d.nfrag);
+  const ColsUnit& u = d.unit[w % d.nunit];
+  switch (u.nb) {
+    case 1:
+      cols_unit<1, NS>(d, u, f, split);
+      break;
+    case 2:
+      cols_unit<2, NS>(d, u, f, split);
+      break;
+    case 3:
+      cols_unit<3, NS>(d, u, f, split);
+      break;
+    case 4:
+      cols_unit<4, NS>(d, u, f, split);
+      break;
+    default:
+      if constexpr (NS == 1) cols_unit<5, NS>(d, u, f, split);
+  }
+}
+
 }  // namespace
+
+int64_t frag_cols_pack(const int* rows, int njob, int o, int v) {
+  int64_t nrb = 0;
+  for (int j = 0; j < njob; ++j) nrb += (rows[j] + 15) / 16;
+  return o * nrb * (((int64_t)v * v + 3) / 4) * 64;
+}
+
+void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int nstream, int v, int vp,
+               const int* part, const int* bl, const int* frags, int nfrag, int o, cplx* pack, hipStream_t s) {
+  if (nfrag <= 0 || njob <= 0) return;
+  RTCC3_CHECK(njob <= 2 && (nstream == 1 || nstream == 3) && v >= 1 && vp >= v, "frag: bad column product");
+  RTCC3_CHECK((int64_t)v * v * vp < (1LL << 27), "frag: product too large");
+  FragCols d;
+  d.B = B;
+  d.bl = bl;
+  d.part = part;
+  d.frag = reinterpret_cast<const int4*>(frags);
+  for (int w = 0; w < 3; ++w) d.perm[w] = w < nstream ? perm[w] : 0;
+  d.v = v;
+  d.vp = vp;
+  d.nfrag = nfrag;
+  d.steps = v * v / 4;
+  struct RowBlock {
+    int job, row;
+  };
+  std::vector<RowBlock> rb;
+  for (int j = 0; j < njob; ++j) {
+    RTCC3_CHECK(jobs[j].M >= 1, "frag: bad column operand");
+    d.job[j] = jobs[j];
+    for (int m = 0; m < jobs[j].M; m += 16) rb.push_back({j, m});
+  }
+  ColsPack pk;
+  for (int j = 0; j < 2; ++j) {
+    pk.job[j] = jobs[std::min(j, njob - 1)];
+    pk.nrb[j] = j < njob ? (jobs[j].M + 15) / 16 : 0;
+  }
+  pk.njob = njob;
+  pk.n = o;
+  pk.steps = (v * v + 3) / 4;
+  pk.v2 = (int64_t)v * v;
+  pk.dst = pack;
+  RTCC3_CHECK((int64_t)pk.steps * 64 < (1LL << 27), "frag: product too large");
+  const int64_t packed = (int64_t)o * (int64_t)rb.size() * pk.steps * 64;
+  hipLaunchKernelGGL(cols_pack_kernel, dim3((unsigned)std::min<int64_t>((packed + 255) / 256, 65536)), dim3(256), 0, s,
+                     pk);
+  RTCC3_HIP(hipGetLastError());
+  d.pack = pack;
+  d.npanel = (int)rb.size();
+  // Row blocks in groups as large as the registers allow (the sums of a B
+  // fragment and, with three streams, its combination serve all of a group's
+  // rows), of about the same size.
+  const int most = nstream == 1 ? 5 : 4;
+  const int ng = ((int)rb.size() + most - 1) / most;
+  auto launch = [&]() {
+    // splits of k for at least four rounds of the chip's 2048 waves, of 32 steps or more
+    const int64_t waves = (int64_t)nfrag * d.nunit;
+    d.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>((4 * 2048 + waves - 1) / waves, d.steps / 32));
+    const int64_t nw = waves * d.nsplit;
+    RTCC3_CHECK(nw < (1LL << 31), "frag: product too large");
+    const dim3 grid((unsigned)((nw + 3) / 4));
+    if (nstream == 1)
+      hipLaunchKernelGGL(frag_cols_kernel<1>, grid, dim3(256), 0, s, d);
+    else
+      hipLaunchKernelGGL(frag_cols_kernel<3>, grid, dim3(256), 0, s, d);
+    RTCC3_HIP(hipGetLastError());
+    d.nunit = 0;
+  };
+  d.nunit = 0;
+  for (int g = 0; g < ng; ++g) {
+    const int r0 = (int)(rb.size() * g / ng), r1 = (int)(rb.size() * (g + 1) / ng);
+    ColsUnit& u = d.unit[d.nunit++];
+    u.nb = r1 - r0;
+    for (int q = 0; q < 5; ++q) {
+      u.job[q] = rb[std::min(r0 + q, r1 - 1)].job;
+      u.row[q] = rb[std::min(r0 + q, r1 - 1)].row;
+      u.panel[q] = std::min(r0 + q, r1 - 1);
+    }
+    if (d.nunit == kMaxColsUnits) launch();
+  }
+  if (d.nunit > 0) launch();
+}
 
 void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
                  hipStream_t s) {

@@ -364,6 +364,50 @@ void prod_frag_gather(Engine& e, const std::vector<FragJob>& jobs, const int64_t
   frag_gather(ja.data(), (int)ja.size(), B, v, vp, bl, nblk, group, s);
 }
 
+// Column products (ColsJob) after the same check, with their derivatives in
+// tangent mode.
+void prod_frag_cols(Engine& e, const std::vector<ColsJob>& jobs, const int64_t* lenA, const int64_t* lenC,
+                    const cplx* B, int64_t lenB, const int* perm, int nstream, int o, int v, int vp, const Window& w,
+                    const ColTable& ct, hipStream_t s) {
+  const int64_t vb = (int64_t)v * v * vp, v2 = (int64_t)v * v;
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    const ColsJob& g = jobs[j];
+    const int64_t eA = (int64_t)(g.M - 1) * g.sAm + v2 - 1;
+    const int64_t eC = (int64_t)(g.M - 1) * g.sCm + (int64_t)(v - 1) * g.sCb;
+    for (size_t p = 0; p < ct.bl.size(); p += 4) {
+      const int* q = &ct.bl[p];
+      const int64_t oA = g.cAK * q[2], oC = g.cC[0] * q[0] + g.cC[1] * q[1];
+      RTCC3_CHECK(oA >= 0 && oA + eA < lenA[j], "triples: A operand out of bounds");
+      RTCC3_CHECK(oC >= 0 && oC + eC < lenC[j], "triples: C operand out of bounds");
+      for (int x = 0; x < nstream; ++x) {
+        const int64_t slot = w.part[6 * q[3] + perm[x]];
+        RTCC3_CHECK(slot >= 0 && (slot + 1) * vb <= lenB, "triples: B operand out of bounds");
+      }
+    }
+  }
+  const int nf = (int)ct.frag.size() / 4;
+  std::vector<int> rows;
+  for (const ColsJob& g : jobs) rows.push_back(g.M);
+  cplx* pack = e.scratch(frag_cols_pack(rows.data(), (int)rows.size(), o, v), s);
+  frag_cols(jobs.data(), (int)jobs.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+  if (!e.tangent()) return;
+  const cplx* bt = e.twin(B);
+  std::vector<ColsJob> jb, ja;
+  for (const ColsJob& g : jobs) {
+    const cplx* at = e.twin(g.A);
+    if (!bt && !at) continue;
+    ColsJob h = g;
+    h.C = e.twin_out(g.C);
+    if (bt) jb.push_back(h);
+    if (at) {
+      h.A = at;
+      ja.push_back(h);
+    }
+  }
+  frag_cols(jb.data(), (int)jb.size(), bt, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+  frag_cols(ja.data(), (int)ja.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+}
+
 // The innermost index of a window block padded to a multiple of 8.
 int pad8(int v) { return (v + 7) / 8 * 8; }
 
@@ -417,7 +461,7 @@ void Triples::free_windows() {
   for (auto* ws : {&rhs_windows_, &den_windows_}) {
     for (auto& w : *ws) {
       for (int* p : {w.d_bl, w.d_part, w.d_owned, w.d_canon, w.d_slabs, w.d_orb, w.d_orb_owned, w.d_bk_t3,
-                     w.d_bk_l3, w.d_bk_own, w.d_gat_t3, w.d_gat_l3, w.rt_t3.d, w.rt_l3.d})
+                     w.d_bk_l3, w.d_bk_own, w.d_gat_t3, w.d_gat_l3, w.rt_t3.d, w.rt_l3.d, w.cols_t3.d_bl, w.cols_t3.d_frag, w.cols_l3.d_bl, w.cols_l3.d_frag})
         if (p) (void)hipFree(p);
       for (Groups* gr : {&w.gJ, &w.gK})
         for (int* p : {gr->d_key, gr->d_start, gr->d_bl})
@@ -659,6 +703,67 @@ void Triples::upload(Window& w) {
   w.gat_l3 = sorted(cb, 1, 2, 0);
   put(&w.d_gat_t3, w.gat_t3);
   put(&w.d_gat_l3, w.gat_l3);
+  // The products with an operand of K alone: groups of whole permutation orbits
+  // follow each other, within a group the entries of a K are numbered through.
+  // X2 reads three orderings of each triple: with one orbit a group the waves
+  // that run together on an XCD share them (o=15, v=57: groups of 6, 30 and 120
+  // blocks take 5.6, 6.7 and 7.6 ms).  The products over lambda3 read one, and
+  // larger groups leave fewer fragments part empty (5.8, 5.4 and 5.4 ms).
+  auto columns = [&](size_t orbit_group, ColTable& out) {
+    std::map<std::array<int, 3>, std::vector<std::array<int, 4>>> by;
+    for (size_t e = 0; e < cb.size(); e += 4) {
+      std::array<int, 3> key{cb[e], cb[e + 1], cb[e + 2]};
+      std::sort(key.begin(), key.end(), std::greater<int>());
+      by[key].push_back({cb[e], cb[e + 1], cb[e + 2], cb[e + 3]});
+    }
+    std::vector<std::array<int, 4>> all, group;
+    auto flush = [&]() {
+      std::sort(group.begin(), group.end(), [](const std::array<int, 4>& a, const std::array<int, 4>& b) {
+        return std::make_tuple(a[2], a[0], a[1]) < std::make_tuple(b[2], b[0], b[1]);
+      });
+      all.insert(all.end(), group.begin(), group.end());
+      group.clear();
+    };
+    for (auto& kv : by) {
+      group.insert(group.end(), kv.second.begin(), kv.second.end());
+      if (group.size() >= orbit_group) flush();
+    }
+    flush();
+    out.bl.clear();
+    out.frag.clear();
+    for (auto& q : all) out.bl.insert(out.bl.end(), q.begin(), q.end());
+    const int v = d_.v;
+    const int64_t vb = (int64_t)v * v * pad8(v);
+    // entries e and f in one fragment: the same K, every pair of their blocks near enough
+    auto near = [&](size_t e, size_t f) {
+      if (e == f) return true;
+      if (all[e][2] != all[f][2]) return false;
+      for (int p = 0; p < 6; ++p)
+        if (((int64_t)std::abs(w.part[6 * all[e][3] + p] - w.part[6 * all[f][3] + p]) + 1) * vb * 16 >= ((int64_t)1 << 30))
+          return false;
+      return true;
+    };
+    size_t e = 0;
+    int b = 0;
+    while (e < all.size()) {
+      const int e0 = (int)e, b0 = b;
+      int n = 0;
+      while (n < 16 && e < all.size() && near(e0, e)) {
+        const int take = std::min(16 - n, v - b);
+        n += take;
+        b += take;
+        if (b == v) {
+          b = 0;
+          ++e;
+        }
+      }
+      out.frag.insert(out.frag.end(), {e0, b0, n, 0});
+    }
+    put(&out.d_bl, out.bl);
+    put(&out.d_frag, out.frag);
+  };
+  columns(1, w.cols_t3);
+  columns(120, w.cols_l3);
   if (!w.owned.empty()) {
     w.bk_own = sorted(w.owned, 2, 0, 1);
     put(&w.d_bk_own, w.bk_own);
@@ -819,6 +924,11 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
   const int* bl = w.d_bl;
   const int* blh = w.bl.data();
   const int pr = prec_;
+  if (pr != RTCC3_PREC_FP64) {  // the panels of the FP64 products, for a later switch to FP64
+    const int rows[2] = {v, o};
+    (void)e.scratch(frag_cols_pack(rows, 2, o, v), s);
+    (void)e.scratch(frag_cols_pack(rows, 2, o, v), s2);
+  }
   // Terms 9 and 10 of Y1.  In FP64 they come from Z_i (below), which saves the
   // S product and its segment (4.7 ms a right-hand side at o=15, v=57).  The
   // reduced precisions keep S, which the split precisions form from bf16 slices:
@@ -1004,8 +1114,13 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.comb_w[2] = -1.0;
       g.comb_stride = vb;
     };
-    {  // X2: sum_ce Z1[b][(c,e)] (ac|ke)~ into X2p[I][J][a][b], with (c,e) contiguous:
-       //   Z1[b][c][e] = (2 T_JIK - T_KIJ - T_JKI)[b][c][e]
+    // X2: sum_ce Z1[b][(c,e)] (ac|ke)~ into X2p[I][J][a][b].  In FP64 (the bf16 splits run it in FP64 too) with b
+    // contiguous: T_JIK[b][c][e] = T_IKJ[c][e][b], T_KIJ[b][c][e] = T_IJK[c][e][b], T_JKI[b][c][e] = T_KIJ[c][e][b].
+    if (pr != RTCC3_PREC_FP32) {
+      const int perm[3] = {2, 0, 4};
+      prod_frag_cols(e, {{gX2a, v3, v2, v, X2p, {(int64_t)o * v2, v2}, v, 1}}, &lOVVV, &oovv, T, winlen, perm, 3, o, v, vp,
+                     w, w.cols_t3, s);
+    } else {  // with (c,e) contiguous
       GemmDesc g = base(v, v, (int)v2, cn, obl, pr);
       g.atomic = 1;
       g.K0 = v;  // k = (c,e)
@@ -1071,8 +1186,16 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
         x2b(gX2b, cbK, ccK, w.gK);
       }
     }
-    {  // Y2: sum_de (da|eK)~ lambda[d][b][e] into Y2p[I][J][a][b]; lambda_IJK[d][b][e] =
-       // lambda_JIK[b][d][e], read with (d,e) contiguous
+    // Y2: sum_de (da|eK)~ lambda[d][b][e] into Y2p[I][J][a][b].  In FP64 with b contiguous, lambda_IJK[d][b][e] =
+    // lambda_IKJ[d][e][b], together with the sum of terms 7, 8 and 12 (below), which reads
+    // sum_bc lambda_IKJ[b][c][d] t2[j][K][(b,c)] into R8[I][J][d][j] from the same block.
+    if (pr == RTCC3_PREC_FP64) {
+      const int perm[1] = {2};
+      const int64_t lA[2] = {lOVVV, t2len}, lC[2] = {oovv, lR};
+      prod_frag_cols(e, {{gY2a, v3, v2, v, Y2p, {(int64_t)o * v2, v2}, v, 1},
+                         {t2, v2, (int64_t)o * v2, o, R8, {(int64_t)o * v * o, (int64_t)v * o}, 1, o}},
+                     lA, lC, L, winlen, perm, 1, o, v, vp, w, w.cols_l3, s2);
+    } else {  // lambda_IJK[d][b][e] = lambda_JIK[b][d][e], read with (d,e) contiguous
       GemmDesc g = base(v, v, (int)v2, cn, cbl, pr);
       g.atomic = 1;
       g.K0 = v;  // k = (d,e)
@@ -1226,7 +1349,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
                    {c6, l2len, lR, l2len, ov}},
                   s);
     }
-    {  // terms 7, 8, 12 and the last density term: Q[d][j] = sum_bc lambda[(b,c)][d] t2[j][J][(b,c)] into
+    if (via_s) {  // terms 7, 8, 12 and the last density term: Q[d][j] = sum_bc lambda[(b,c)][d] t2[j][J][(b,c)] into
        //    R8[I][K]; with lambda[b][c][d] = lambda_KIJ[d][b][c] and the labels renamed ((K,I,J) -> (I,J,K)):
        //    sum_bc lambda_n[d][(b,c)] t2[j][K][(b,c)] into R8[J][I].
        // The four terms take the same sum (over the block (l,m,k) = (I,J,K) of term 12 and (j,k,l) = (I,J,K) of
@@ -1234,9 +1357,8 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       const int64_t ovo = (int64_t)o * v * o, vo = (int64_t)v * o, ov2 = (int64_t)o * v2;
       std::vector<SegSpec> specs = {{cseg(t2, {0, 0, v2, 0}, 1, ov2, R8, {vo, ovo, 0, 0}, o, 1, 1.0), t2len, lR, 0, 0}};
       // terms 9, 10 from S: Y1[x][a] -= sum_(c,d) lambda_n[a][(c,d)] S[n][(c,d)][x]
-      if (via_s)
-        specs.push_back({cseg(S, {0, 0, 0, v2 * o}, o, 1, Y1, {0, 0, 0, 0}, 1, v, -1.0), (int64_t)max_nw_ * v2 * o, ov,
-                         0, 0});
+      specs.push_back({cseg(S, {0, 0, 0, v2 * o}, o, 1, Y1, {0, 0, 0, 0}, 1, v, -1.0), (int64_t)max_nw_ * v2 * o, ov,
+                       0, 0});
       seg_product(L, specs, s2);
     }
     if (pr != RTCC3_PREC_FP64) {  // Zi, summed over the blocks of each J

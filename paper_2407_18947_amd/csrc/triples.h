@@ -33,6 +33,15 @@ struct RowTiles {
   int* d = nullptr;
 };
 
+// The contraction blocks by groups of whole permutation orbits and, within a
+// group, by (K, I, J), with their column fragments (4 ints each, see
+// frag_kernels.h).
+struct ColTable {
+  std::vector<int> bl, frag;
+  int* d_bl = nullptr;
+  int* d_frag = nullptr;
+};
+
 // A window: a set of ordered occupied triples that is closed under permutation,
 // so every block's P_ijk^abc partners are in it.  The contraction set (all
 // blocks, or the owned ones) is a union of whole permutation orbits as well.
@@ -55,6 +64,7 @@ struct Window {
   // the contraction blocks by (I, K, J) and by (J, K, I), for the gathered
   // products over t3 and over lambda3
   std::vector<int> gat_t3, gat_l3;
+  ColTable cols_t3, cols_l3;  // for the column products over t3 and over lambda3
   int* d_bl = nullptr;
   int* d_part = nullptr;
   int* d_owned = nullptr;
