@@ -59,4 +59,32 @@ void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, in
                const int* part, const int* bl, const int* frags, int nfrag, int o, cplx* pack, hipStream_t s);
 int64_t frag_cols_pack(const int* rows, int njob, int o, int v);
 
+// Products of one block each, X[b][k] read as rows k < v^2 of v columns b (the
+// block at slot part[6 n + perm] of entry n), with the n columns of several
+// groups,
+//   C_g[b][x] += alpha_g * sum_k X[k][b] B_g[x][k],   x < n,
+// B_g at B + (I, J or K, by key)*sKey + x*sB + k, C_g at C + cC.(I,J,K) + b*sCm +
+// x*sCx (atomic adds).  A trace takes the column x = (I, J or K, by col) of a
+// group once more, times its own alpha, into C + (I, J or K, by row)*sC + b.
+struct BlockCols {
+  const cplx* B;
+  int key;
+  int64_t sKey, sB;
+  cplx* C;
+  int64_t cC[3], sCm, sCx;
+  double alpha;
+};
+struct BlockTrace {
+  int group, col, row;
+  cplx* C;
+  int64_t sC;
+  double alpha;
+};
+constexpr int kMaxBlockCols = 4;
+// pack: space for frag_block_pack() elements, used on s only until the product
+// is done; o: the extent of I, J and K.
+void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
+                int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s);
+int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v);
+
 }  // namespace rtcc3

@@ -575,7 +575,254 @@ __global__ __launch_bounds__(256, 2) void frag_cols_kernel(FragCols d) {
   }
 }
 
+// Column operands of frag_block in the order the waves read them: the panel of
+// an operand and key holds, step of four k by step, the columns' four elements,
+// zero beyond the last k.
+struct BlockPack {
+  struct {
+    const cplx* B;
+    int64_t sKey, sB;
+  } src[kMaxBlockCols];
+  int64_t v2;
+  int nsrc, n, o, steps;
+  cplx* dst;
+};
+__global__ __launch_bounds__(256) void block_pack_kernel(BlockPack d) {
+  const int64_t total = (int64_t)d.nsrc * d.o * d.steps * d.n * 4;
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+    const int x = (int)((t >> 2) % d.n);
+    const int64_t r = (t >> 2) / d.n;
+    const int panel = (int)(r / d.steps);
+    const int64_t k = 4 * (r % d.steps) + (t & 3);
+    const auto& g = d.src[panel / d.o];
+    d.dst[t] = k < d.v2 ? g.B[g.sKey * (panel % d.o) + x * g.sB + k] : cplx{0, 0};
+  }
+}
+
+struct FragBlock {
+  BlockCols g[kMaxBlockCols];
+  int panel[kMaxBlockCols];  // a group's first panel
+  BlockTrace tr[kMaxBlockCols];
+  int ng, n, ntr;
+  const cplx* X;
+  const cplx* pack;
+  const int* bl;
+  const int* part;
+  int perm, v, vp, nblk, nfrag, nrg, steps, nsplit;
+  int row0[8], nb[8];  // groups of row blocks: first row and number
+};
+
+template <int IB>
+__device__ __forceinline__ void block_unit(const FragBlock& d, int e, int f, int row0, int split) {
+  constexpr int D = 3;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
+  const int v = d.v;
+  const int64_t vb = (int64_t)v * v * d.vp;
+  const int ijk[3] = {d.bl[4 * e], d.bl[4 * e + 1], d.bl[4 * e + 2]};
+  const int slot = __builtin_amdgcn_readfirstlane(d.part[6 * d.bl[4 * e + 3] + d.perm]);
+  auto pick = [&](int w) { return w == 0 ? ijk[0] : w == 1 ? ijk[1] : ijk[2]; };
+  // the lane's column: its group and its place there; one resource from the
+  // lowest of the lanes' panels on
+  const int c = 16 * f + l16;
+  const bool ok = c < d.ng * d.n;
+  const int gi = ok ? c / d.n : 0, x = ok ? c % d.n : 0;
+  const BlockCols& g = d.g[gi];
+  const int panel = d.panel[gi] + pick(g.key);
+  int lo = panel;
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) lo = min(lo, __shfl_xor(lo, m));
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  const int plen = (v * v + 3) / 4 * 4 * d.n;
+  const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(d.pack + (int64_t)lo * plen), 0, -1, kRsrcWord3);
+  const int bo = (int)(((uint32_t)(panel - lo) * (uint32_t)plen + (uint32_t)(4 * x + kl)) * (uint32_t)sizeof(cplx));
+  const auto ra = rsrc(d.X + slot * vb, vb);
+  int ao[IB];
+#pragma unroll
+  for (int i = 0; i < IB; ++i) ao[i] = (min(row0 + 16 * i + l16, v - 1) + kl * d.vp) * (int)sizeof(cplx);
+  const int sak = 4 * d.vp * (int)sizeof(cplx), sbk = 4 * d.n * (int)sizeof(cplx);
+  Acc<IB, 1> acc;
+  acc.clear();
+  d2v a[D][IB], b[D];
+  auto load = [&](int r, int q) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i) a[r][i] = frag_load(ra, ao[i], q * sak);
+    b[r] = frag_load(rb, bo, q * sbk);
+  };
+  const int q0 = split * d.steps / d.nsplit, q1 = (split + 1) * d.steps / d.nsplit;
+  if (q0 < q1) {
+#pragma unroll
+    for (int r = 0; r < D; ++r) load(r, min(q0 + r, q1 - 1));
+    for (int q = q0; q < q1; q += D) {
+#pragma unroll
+      for (int r = 0; r < D; ++r) {
+        if (q + r >= q1) break;
+        acc.step(a[r], &b[r]);
+        __builtin_amdgcn_sched_barrier(0);  // the refill follows the products of its slot
+        load(r, min(q + r + D, q1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  const int rest = (v * v) & 3;
+  if (rest && split + 1 == d.nsplit) {  // the last k: B is zero at the missing ones, A reads a valid k
+    const int back = min(kl, rest - 1) - kl;
+    d2v at[IB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) at[i] = frag_load(ra, ao[i] + back * d.vp * (int)sizeof(cplx), d.steps * sak);
+    const d2v bt = frag_load(rb, bo, d.steps * sbk);
+    acc.step(at, &bt);
+  }
+  if (!ok) return;
+  auto add = [&](cplx* C, int64_t sCm, double alpha) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = row0 + 16 * i + 4 * r + kl;
+        if (m >= v) continue;
+        const d2v z = acc.value(i, 0, r);
+        cplx* q = C + m * sCm;
+        unsafeAtomicAdd(&q->re, alpha * z[0]);
+        unsafeAtomicAdd(&q->im, alpha * z[1]);
+      }
+  };
+  add(g.C + g.cC[0] * ijk[0] + g.cC[1] * ijk[1] + g.cC[2] * ijk[2] + x * g.sCx, g.sCm, g.alpha);
+  for (int t = 0; t < d.ntr; ++t) {
+    const BlockTrace& u = d.tr[t];
+    if (u.group == gi && x == pick(u.col)) add(u.C + u.sC * pick(u.row), 1, u.alpha);
+  }
+}
+
+// Terms 1, 2, 5 and 6 of Y1 with X1 and terms 3 and 4 as traces of them.  Bound
+// by the matrix cores.  o=15, v=57, alone: 5.95 -> 4.54 ms; o=10, v=38: 0.76 ->
+// 0.45; o=16, v=66: 26.4 (16-wide columns of each segment, X1 and terms 3 and 4
+// in a sweep of their own) -> 8.2.  The columns of all groups are numbered
+// through (4 o of them, so that little of the 16-wide fragments is padding) and
+// packed: read where they lie, as 16 pieces of 64 bytes v^2 apart each step, they
+// made that 6.56, 0.78 and 14.2 ms.
+// One wave per block, 16 columns, group of row blocks and split of k; the
+// waves of a block follow each other, so that they share its rows in the L1.
+__global__ __launch_bounds__(256, 2) void frag_block_kernel(FragBlock d) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t w = (int64_t)xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * 4 + wave;
+  const int per = d.nfrag * d.nrg;
+  const int64_t t = w / per;
+  const int r = (int)(w % per), f = r % d.nfrag, rg = r / d.nfrag;
+  const int e = (int)(t / d.nsplit), split = (int)(t % d.nsplit);
+  if (e >= d.nblk) return;
+  switch (d.nb[rg]) {
+    case 1:
+      block_unit<1>(d, e, f, d.row0[rg], split);
+      break;
+    case 2:
+      block_unit<2>(d, e, f, d.row0[rg], split);
+      break;
+    case 3:
+      block_unit<3>(d, e, f, d.row0[rg], split);
+      break;
+    case 4:
+      block_unit<4>(d, e, f, d.row0[rg], split);
+      break;
+    default:
+      block_unit<5>(d, e, f, d.row0[rg], split);
+  }
+}
+
 }  // namespace
+
+namespace {
+
+// First panel of each group's operand, groups with the same one sharing it;
+// returns the number of panels.
+int block_panels(const BlockCols* g, int ng, int o, int* panel) {
+  int np = 0;
+  for (int q = 0; q < ng; ++q) {
+    panel[q] = -1;
+    for (int p = 0; p < q && panel[q] < 0; ++p)
+      if (g[p].B == g[q].B && g[p].sKey == g[q].sKey && g[p].sB == g[q].sB) panel[q] = panel[p];
+    if (panel[q] >= 0) continue;
+    panel[q] = np;
+    np += o;
+  }
+  return np;
+}
+
+}  // namespace
+
+int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v) {
+  int panel[kMaxBlockCols];
+  RTCC3_CHECK(ng <= kMaxBlockCols, "frag: too many column groups");
+  return (int64_t)block_panels(groups, ng, o, panel) * (((int64_t)v * v + 3) / 4 * 4 * n);
+}
+
+void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
+                int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s) {
+  if (nblk <= 0 || ng <= 0) return;
+  RTCC3_CHECK(ng <= kMaxBlockCols && ntr <= kMaxBlockCols && n >= 1 && v >= 1 && vp >= v &&
+                  (int64_t)v * v * vp < (1LL << 27) && ((int64_t)v * v + 3) * n < (1LL << 27),
+              "frag: bad block product");
+  FragBlock d;
+  const int64_t plen = ((int64_t)v * v + 3) / 4 * 4 * n;
+  if (ng > 1 && (block_panels(groups, ng, o, d.panel) + 1) * plen * (int64_t)sizeof(cplx) > (1LL << 32)) {
+    // a fragment's panels have to lie within 2^32 bytes: with one group it has one
+    for (int q = 0; q < ng; ++q) {
+      std::vector<BlockTrace> own;
+      for (int t = 0; t < ntr; ++t)
+        if (tr[t].group == q) {
+          own.push_back(tr[t]);
+          own.back().group = 0;
+        }
+      frag_block(groups + q, 1, n, own.data(), (int)own.size(), X, perm, o, v, vp, part, bl, nblk, pack, s);
+    }
+    return;
+  }
+  block_panels(groups, ng, o, d.panel);
+  d.ng = ng;
+  d.n = n;
+  d.ntr = ntr;
+  for (int t = 0; t < ntr; ++t) d.tr[t] = tr[t];
+  BlockPack pk;
+  pk.v2 = (int64_t)v * v;
+  pk.n = n;
+  pk.o = o;
+  pk.steps = (v * v + 3) / 4;
+  pk.nsrc = 0;
+  pk.dst = pack;
+  for (int q = 0; q < ng; ++q) {
+    d.g[q] = groups[q];
+    if (d.panel[q] == pk.nsrc * o) pk.src[pk.nsrc++] = {groups[q].B, groups[q].sKey, groups[q].sB};
+  }
+  const int64_t packed = (int64_t)pk.nsrc * o * plen;
+  hipLaunchKernelGGL(block_pack_kernel, dim3((unsigned)std::min<int64_t>((packed + 255) / 256, 65536)), dim3(256), 0, s,
+                     pk);
+  RTCC3_HIP(hipGetLastError());
+  d.X = X;
+  d.pack = pack;
+  d.bl = bl;
+  d.part = part;
+  d.perm = perm;
+  d.v = v;
+  d.vp = vp;
+  d.nblk = nblk;
+  d.nfrag = (ng * n + 15) / 16;
+  d.steps = v * v / 4;
+  const int nrb = (v + 15) / 16, nrg = (nrb + 4) / 5;
+  for (int g0 = 0; g0 < nrg; g0 += 8) {
+    d.nrg = std::min(8, nrg - g0);
+    for (int g = 0; g < d.nrg; ++g) {
+      const int r0 = nrb * (g0 + g) / nrg, r1 = nrb * (g0 + g + 1) / nrg;
+      d.row0[g] = 16 * r0;
+      d.nb[g] = r1 - r0;
+    }
+    // splits of k for at least four rounds of the chip's 2048 waves, of 32 steps or more
+    const int64_t waves = (int64_t)nblk * d.nfrag * d.nrg;
+    d.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>((4 * 2048 + waves - 1) / waves, d.steps / 32));
+    const int64_t nw = waves * d.nsplit;
+    RTCC3_CHECK(nw < (1LL << 31), "frag: product too large");
+    hipLaunchKernelGGL(frag_block_kernel, dim3((unsigned)((nw + 3) / 4)), dim3(256), 0, s, d);
+    RTCC3_HIP(hipGetLastError());
+  }
+}
 
 int64_t frag_cols_pack(const int* rows, int njob, int o, int v) {
   int64_t nrb = 0;

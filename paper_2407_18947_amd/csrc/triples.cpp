@@ -408,6 +408,56 @@ void prod_frag_cols(Engine& e, const std::vector<ColsJob>& jobs, const int64_t* 
   frag_cols(ja.data(), (int)ja.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
 }
 
+// Block products (BlockCols, BlockTrace) after the same check, with their
+// derivatives in tangent mode.
+void prod_frag_block(Engine& e, const std::vector<BlockCols>& groups, const std::vector<BlockTrace>& traces, int o,
+                     const int64_t* lenB, const int64_t* lenC, const int64_t* lenT, const cplx* X, int64_t lenX,
+                     int perm, int v, int vp, const Window& w, const std::vector<int>& bl_host, const int* bl,
+                     hipStream_t s) {
+  const int64_t vb = (int64_t)v * v * vp, v2 = (int64_t)v * v;
+  const int nblk = (int)bl_host.size() / 4;
+  for (int p = 0; p < nblk; ++p) {
+    const int* q = &bl_host[4 * p];
+    const int64_t slot = w.part[6 * q[3] + perm];
+    RTCC3_CHECK(slot >= 0 && (slot + 1) * vb <= lenX, "triples: A operand out of bounds");
+    for (size_t x = 0; x < groups.size(); ++x) {
+      const BlockCols& g = groups[x];
+      const int64_t oC = g.cC[0] * q[0] + g.cC[1] * q[1] + g.cC[2] * q[2];
+      RTCC3_CHECK(g.sKey * (o - 1) + (o - 1) * g.sB + v2 <= lenB[x], "triples: B segment out of bounds");
+      RTCC3_CHECK(oC >= 0 && oC + (v - 1) * g.sCm + (o - 1) * g.sCx < lenC[x], "triples: C segment out of bounds");
+    }
+    for (size_t t = 0; t < traces.size(); ++t)
+      RTCC3_CHECK(traces[t].sC * q[traces[t].row] + v <= lenT[t], "triples: C segment out of bounds");
+  }
+  auto run = [&](const std::vector<BlockCols>& g, const std::vector<BlockTrace>& t, const cplx* x) {
+    if (g.empty()) return;
+    cplx* pack = e.scratch(frag_block_pack(g.data(), (int)g.size(), o, o, v), s);
+    frag_block(g.data(), (int)g.size(), o, t.data(), (int)t.size(), x, perm, o, v, vp, w.d_part, bl, nblk, pack, s);
+  };
+  run(groups, traces, X);
+  if (!e.tangent()) return;
+  // d(X B) = dX B + X dB
+  const cplx* xt = e.twin(X);
+  for (int side = 0; side < 2; ++side) {
+    std::vector<BlockCols> g;
+    std::vector<BlockTrace> t;
+    for (size_t x = 0; x < groups.size(); ++x) {
+      const cplx* bt = e.twin(groups[x].B);
+      if (side == 0 ? !xt : !bt) continue;
+      for (BlockTrace u : traces)
+        if (u.group == (int)x) {
+          u.group = (int)g.size();
+          u.C = e.twin_out(u.C);
+          t.push_back(u);
+        }
+      g.push_back(groups[x]);
+      g.back().C = e.twin_out(g.back().C);
+      if (side == 1) g.back().B = bt;
+    }
+    run(g, t, side == 0 ? xt : X);
+  }
+}
+
 // The innermost index of a window block padded to a multiple of 8.
 int pad8(int v) { return (v + 7) / 8 * 8; }
 
@@ -840,7 +890,7 @@ void Triples::blocks(Engine& e, const CCSDResult& r) {
   t = make("tb_X2c", {o, o, o, v});  // (ki|mc) - 2(mi|kc) at [k][m][i][c] (+ the f~ term below)
   e.einsum("Pki,Pmc->kmic", ONE, B('o', 'o'), B('o', 'v'), t);
   e.einsum("Pmi,Pkc->kmic", R(-2), B('o', 'o'), B('o', 'v'), t);
-  if (o <= 15) {
+  if (o <= 15 || prec_ == RTCC3_PREC_FP64) {
     // The f~ term of X2, sum_c (t[a,b,c] - t[c,b,a]) f~_kc into X2p[I][J], goes through
     // the same gathered product: its second part relabelled (t_IJK[c][b][a] = t_KJI[a][b][c],
     // then I <-> K), both read the block itself, so
@@ -926,7 +976,8 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
   const int pr = prec_;
   if (pr != RTCC3_PREC_FP64) {  // the panels of the FP64 products, for a later switch to FP64
     const int rows[2] = {v, o};
-    (void)e.scratch(frag_cols_pack(rows, 2, o, v), s);
+    const int64_t block = 3 * (int64_t)o * o * (v2 + 3);
+    (void)e.scratch(std::max(frag_cols_pack(rows, 2, o, v), block), s);
     (void)e.scratch(frag_cols_pack(rows, 2, o, v), s2);
   }
   // Terms 9 and 10 of Y1.  In FP64 they come from Z_i (below), which saves the
@@ -1087,11 +1138,12 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     // X1, the f~ term of X2 and Z34 (terms 3 and 4 of Y1): with o <= 15 they ride
     // along with products that read the block anyway (tail columns of the Y1
     // product below; the f~ term inside tb_X2c); else one sweep per block
-    const bool tails = o <= 15;
+    // (in FP64 with any o)
+    const bool tails = o <= 15 || pr == RTCC3_PREC_FP64;
     // the 16-wide gathered products in FP64 (the split precisions too)
     const bool frag16 = pr == RTCC3_PREC_FP64 || (pr != RTCC3_PREC_FP32 && o <= 16);
+    RTCC3_CHECK(o <= 15 || !e.tangent(), "triples: derivatives need o <= 15");
     if (!tails) {
-      RTCC3_CHECK(!e.tangent(), "triples: derivatives need o <= 15");
       launch_small_t3(T, cbl, cn, Lov, F, l2, X1, X2p, Z34, o, v, vp, 3, s);
     }
     // the t3 side's products are bound by the matrix cores like the lambda3
@@ -1329,25 +1381,39 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
        // Term 5 sums t[(b,c)][d] = t_KIJ[d][(b,c)] over the blocks; with the labels renamed
        // ((K,I,J) -> (I,J,K)) it reads the block itself, into R15[K][I] with G5[J].
       const int64_t ovo = (int64_t)o * v * o, vo = (int64_t)v * o, ov2 = (int64_t)o * v2;
-      GemmDesc::ColSeg c1 = cseg(gG1, {ov2, 0, 0, 0}, 1, v2, R15, {0, ovo, vo, 0}, o, 1, 1.0);   // term 1: (xc|Id)
-      GemmDesc::ColSeg c5 = cseg(gG5, {0, ov2, 0, 0}, 1, v2, R15, {vo, 0, ovo, 0}, o, 1, -1.0);  // term 5: L_Ibxc
-      GemmDesc::ColSeg c2 = cseg(l2, {v2, 0, 0, 0}, 1, ov2, R2t, {0, ovo, vo, 0}, o, 1, 1.0);    // term 2: l2[x][I]
-      GemmDesc::ColSeg c6 = cseg(l2, {0, 0, v2, 0}, 1, ov2, R6, {ovo, vo, 0, 0}, o, 1, 1.0);     // term 6: l2[x][K]
-      if (tails) {
-        // X1[I][a] += sum_bc t[a][b][c] L_JbKc, and -sum_bc t[c][b][a] L_JbKc relabelled
-        // (t_IJK[c][b][a] = t_KJI[a][b][c], then I <-> K) into X1[K] with L_JbIc;
-        // Z34[I][a] += sum_bc t[a][b][c] l2[J][K][b][c], and -sum_bc t[b][a][c] l2[J][K][b][c]
-        // relabelled (t_IJK[b][a][c] = t_JIK[a][b][c], then I <-> J) into Z34[J] with l2[I][K].
-        // L_JbKc = (tb_G5)[J][K][b][c].
-        tail(c1, gG5, {0, ov2, v2, 0}, X1, {v, 0, 0, 0}, 1.0);
-        tail(c5, gG5, {v2, ov2, 0, 0}, X1, {0, 0, v, 0}, -1.0);
-        tail(c2, l2, {0, ov2, v2, 0}, Z34, {v, 0, 0, 0}, 1.0);
-        tail(c6, l2, {ov2, 0, v2, 0}, Z34, {0, v, 0, 0}, -1.0);
-      }
-      seg_product(T,
+      // Of the same sums, per block as well:
+      // X1[I][a] += sum_bc t[a][b][c] L_JbKc, and -sum_bc t[c][b][a] L_JbKc relabelled
+      // (t_IJK[c][b][a] = t_KJI[a][b][c], then I <-> K) into X1[K] with L_JbIc;
+      // Z34[I][a] += sum_bc t[a][b][c] l2[J][K][b][c], and -sum_bc t[b][a][c] l2[J][K][b][c]
+      // relabelled (t_IJK[b][a][c] = t_JIK[a][b][c], then I <-> J) into Z34[J] with l2[I][K].
+      // L_JbKc = (tb_G5)[J][K][b][c].  In FP64 they are the columns x = K and x = I of
+      // term 5 and x = J and x = I of term 6; else columns of their own.
+      if (pr == RTCC3_PREC_FP64) {  // t_IJK[b][(c,d)] = t_JKI[c][d][b]
+        const std::vector<BlockCols> groups = {
+            {gG1, 0, ov2, v2, R15, {0, ovo, vo}, o, 1, 1.0},    // term 1: (xc|Id)
+            {gG5, 1, ov2, v2, R15, {vo, 0, ovo}, o, 1, -1.0},   // term 5: L_Ibxc
+            {l2, 0, v2, ov2, R2t, {0, ovo, vo}, o, 1, 1.0},     // term 2: l2[x][I]
+            {l2, 2, v2, ov2, R6, {ovo, vo, 0}, o, 1, 1.0}};     // term 6: l2[x][K]
+        const std::vector<BlockTrace> traces = {
+            {1, 2, 0, X1, v, 1.0}, {1, 0, 2, X1, v, -1.0}, {3, 1, 0, Z34, v, 1.0}, {3, 0, 1, Z34, v, -1.0}};
+        const int64_t lB[4] = {lOOVV, lOOVV, l2len, l2len}, lC[4] = {lR, lR, lR, lR}, lT[4] = {ov, ov, ov, ov};
+        prod_frag_block(e, groups, traces, o, lB, lC, lT, T, winlen, 5, v, vp, w, pairwin ? w.owned : w.bl, cbl, s);
+      } else {
+        GemmDesc::ColSeg c1 = cseg(gG1, {ov2, 0, 0, 0}, 1, v2, R15, {0, ovo, vo, 0}, o, 1, 1.0);   // term 1: (xc|Id)
+        GemmDesc::ColSeg c5 = cseg(gG5, {0, ov2, 0, 0}, 1, v2, R15, {vo, 0, ovo, 0}, o, 1, -1.0);  // term 5: L_Ibxc
+        GemmDesc::ColSeg c2 = cseg(l2, {v2, 0, 0, 0}, 1, ov2, R2t, {0, ovo, vo, 0}, o, 1, 1.0);    // term 2: l2[x][I]
+        GemmDesc::ColSeg c6 = cseg(l2, {0, 0, v2, 0}, 1, ov2, R6, {ovo, vo, 0, 0}, o, 1, 1.0);     // term 6: l2[x][K]
+        if (tails) {
+          tail(c1, gG5, {0, ov2, v2, 0}, X1, {v, 0, 0, 0}, 1.0);
+          tail(c5, gG5, {v2, ov2, 0, 0}, X1, {0, 0, v, 0}, -1.0);
+          tail(c2, l2, {0, ov2, v2, 0}, Z34, {v, 0, 0, 0}, 1.0);
+          tail(c6, l2, {ov2, 0, v2, 0}, Z34, {0, v, 0, 0}, -1.0);
+        }
+        seg_product(T,
                   {{c1, lOOVV, lR, lOOVV, ov}, {c5, lOOVV, lR, lOOVV, ov}, {c2, l2len, lR, l2len, ov},
                    {c6, l2len, lR, l2len, ov}},
                   s);
+      }
     }
     if (via_s) {  // terms 7, 8, 12 and the last density term: Q[d][j] = sum_bc lambda[(b,c)][d] t2[j][J][(b,c)] into
        //    R8[I][K]; with lambda[b][c][d] = lambda_KIJ[d][b][c] and the labels renamed ((K,I,J) -> (I,J,K)):
