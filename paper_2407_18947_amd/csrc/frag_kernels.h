@@ -87,4 +87,12 @@ void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, in
                 int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s);
 int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v);
 
+// A plain FP64 product (no segments, gathered K or combined operands) with its
+// k split over ksplit workgroups (atomic adds if more than one);
+// frag_gemm_fits: whether the kernel takes it (32-bit operand spans),
+// frag_gemm_split: the split to use where none was measured.
+bool frag_gemm_fits(const GemmDesc& g);
+int frag_gemm_split(const GemmDesc& g);
+void frag_gemm(const GemmDesc& g, int ksplit, hipStream_t s);
+
 }  // namespace rtcc3

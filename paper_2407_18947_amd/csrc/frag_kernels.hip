@@ -16,6 +16,7 @@
 #include "frag_kernels.h"
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 namespace rtcc3 {
@@ -728,6 +729,213 @@ __global__ __launch_bounds__(256, 2) void frag_block_kernel(FragBlock d) {
   }
 }
 
+struct FragGemm {
+  const cplx* A;
+  const cplx* B;
+  cplx* C;
+  int M, N, M0, N0;
+  int64_t sAm1, sAm0, sBn1, sBn0, sCm1, sCm0, sCn1, sCn0, sAb, sBb, sCb;
+  const int* bl;
+  int64_t cA[4], cB[4], cC[4];
+  int64_t nA, nB;              // elements from an entry's first to past its last
+  int K0, steps;               // inner extent of k; steps of four in all (one level: full ones)
+  int sak1, sak0, sbk1, sbk0;  // bytes per k
+  int mt, nt, wm, wn, gm, gn;  // wave tiles; a workgroup's tiles; workgroups along M and N
+  int mfast;                   // consecutive workgroups walk along M
+  int ksplit;
+  int mode;                    // 0: C += , 1: C = , 2: atomic C +=
+  double are, aim;
+};
+
+// C[m][n] (+)= alpha sum_k A[m][k] B[k][n] of one entry, tile of 16 IB x 16 JB
+// and split of k.  KW = 1: a workgroup's four waves take neighbouring tiles;
+// else its KW waves split the k of one tile and add up through the LDS.
+// Steps are of four k; two are loaded at a time, so that an operand stored
+// k-fast is read in whole lines.  k of one level (TAIL < 0): the last K % 4 go
+// first, in a step that reads zeros past the last.  k of two levels, inner runs
+// of K0: such a step ends each run (TAIL = 1), or K0 % 4 is zero (TAIL = 0).
+//
+// The plain products of the einsum engine.  Bound by the matrix cores where the
+// contraction is long (o=4, v=96, the two ladders over 9216 virtual pairs with
+// 300 rows: 51 and 75 TFLOP/s, k-fast against n-fast columns), by C where it is
+// short (3249 x 3249 x 216: 338 MB of C, 0.33 ms at 55 TFLOP/s), by latency and
+// launch below some 10^8 terms.  A right-hand side's 110 products, kernel time:
+// o=15, v=57 8.2 -> 6.1 ms, o=4, v=96 16.5 -> 15.1, o=5, v=18 2.0 -> 0.69 (an
+// 18 us LDS-tiled product with its split added by atomics becomes one of 6 us:
+// a workgroup's waves split k down to a few steps each).  Steps in pairs with k
+// next to each other (8u + 2 (l/16) + 0, 1) made k-fast operands read half lines
+// twice as often: 6.6 ms at o=15.
+template <int IB, int JB, int KW, int TAIL>
+__global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) void frag_gemm_kernel(FragGemm d) {
+  constexpr int R = IB * JB > 1 ? 4 : 6;  // steps in flight
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int g = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+  const int per = d.gm * d.gn;
+  const int t = g % per;
+  g /= per;
+  const int ks = g % d.ksplit, e = g / d.ksplit;
+  int ti = d.mfast ? t % d.gm : t / d.gn, tj = d.mfast ? t / d.gm : t % d.gn;
+  if constexpr (KW == 1) {
+    ti = ti * d.wm + wave % d.wm;
+    tj = tj * d.wn + wave / d.wm;
+    if (ti >= d.mt || tj >= d.nt) return;
+  }
+  const cplx* pA = d.A;
+  const cplx* pB = d.B;
+  cplx* pC = d.C;
+  if (d.bl) {
+    const int* q = d.bl + 4 * (int64_t)e;
+    const int q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+    pA += d.cA[0] * q0 + d.cA[1] * q1 + d.cA[2] * q2 + d.cA[3] * q3;
+    pB += d.cB[0] * q0 + d.cB[1] * q1 + d.cB[2] * q2 + d.cB[3] * q3;
+    pC += d.cC[0] * q0 + d.cC[1] * q1 + d.cC[2] * q2 + d.cC[3] * q3;
+  } else {
+    pA += d.sAb * e;
+    pB += d.sBb * e;
+    pC += d.sCb * e;
+  }
+  auto off = [](int x, int X0, int X, int64_t s1, int64_t s0) {
+    if (X0 == X) return x * s0;
+    const int h = x / X0;
+    return h * s1 + (x - h * X0) * s0;
+  };
+  const auto ra = rsrc(pA, d.nA), rb = rsrc(pB, d.nB);
+  constexpr int kOut = 0x7ffffff0;  // beyond every operand (spans below 2^31 bytes)
+  // row and column offsets, and those of the lane's first k
+  constexpr bool TWO = TAIL >= 0;
+  int ao[IB], bo[JB], al[IB], bl[JB];
+  const int rest = d.K0 & 3;
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    ao[i] = (int)off(min(16 * (ti * IB + i) + l16, d.M - 1), d.M0, d.M, d.sAm1, d.sAm0) * (int)sizeof(cplx) + kl * d.sak0;
+    al[i] = kl < rest ? ao[i] : kOut;
+  }
+#pragma unroll
+  for (int j = 0; j < JB; ++j) {
+    bo[j] = (int)off(min(16 * (tj * JB + j) + l16, d.N - 1), d.N0, d.N, d.sBn1, d.sBn0) * (int)sizeof(cplx) + kl * d.sbk0;
+    bl[j] = kl < rest ? bo[j] : kOut;
+  }
+  // the wave's steps
+  const int nsp = d.ksplit * KW, sp = KW == 1 ? ks : ks * KW + wave;
+  const int t0 = (int)((int64_t)d.steps * sp / nsp), t1 = (int)((int64_t)d.steps * (sp + 1) / nsp);
+  Acc<IB, JB> acc;
+  acc.clear();
+  d2v a[R][IB], b[R][JB];
+  [[maybe_unused]] d2v at[IB], bt[JB];
+  [[maybe_unused]] const bool tail = !TWO && rest > 0 && sp + 1 == nsp;
+  if constexpr (!TWO) {
+    if (tail) {
+#pragma unroll
+      for (int i = 0; i < IB; ++i) at[i] = frag_load(ra, al[i], d.steps * 4 * d.sak0);
+#pragma unroll
+      for (int j = 0; j < JB; ++j) bt[j] = frag_load(rb, bl[j], d.steps * 4 * d.sbk0);
+    }
+  }
+  [[maybe_unused]] const int run = (d.K0 + 3) >> 2;  // steps of an inner run
+  [[maybe_unused]] int k1 = 0, q = 0;
+  if constexpr (TWO) {
+    k1 = t0 / run;
+    q = t0 - k1 * run;
+  }
+  auto load = [&](int r, int t) {
+    if constexpr (TWO) {
+      const int sa = k1 * d.sak1 + 4 * q * d.sak0, sb = k1 * d.sbk1 + 4 * q * d.sbk0;
+      const bool last = q + 1 == run;
+#pragma unroll
+      for (int i = 0; i < IB; ++i) a[r][i] = frag_load(ra, TAIL && last ? al[i] : ao[i], sa);
+#pragma unroll
+      for (int j = 0; j < JB; ++j) b[r][j] = frag_load(rb, TAIL && last ? bl[j] : bo[j], sb);
+      if (t + 1 < t1) {
+        q = last ? 0 : q + 1;
+        k1 = last ? k1 + 1 : k1;
+      }
+    } else {
+      const int x = 4 * min(t, t1 - 1);
+#pragma unroll
+      for (int i = 0; i < IB; ++i) a[r][i] = frag_load(ra, ao[i], x * d.sak0);
+#pragma unroll
+      for (int j = 0; j < JB; ++j) b[r][j] = frag_load(rb, bo[j], x * d.sbk0);
+    }
+  };
+  if (t0 < t1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) load(r, t0 + r);
+  }
+  if constexpr (!TWO) {
+    if (tail) acc.step(at, bt);
+  }
+  if (t0 < t1) {
+    for (int t = t0; t < t1; t += R) {
+#pragma unroll
+      for (int r = 0; r < R; r += 2) {
+        if (t + r >= t1) break;
+        acc.step(a[r], b[r]);
+        if (t + r + 1 >= t1) break;
+        acc.step(a[r + 1], b[r + 1]);
+        __builtin_amdgcn_sched_barrier(0);  // the refill follows the products of its slots
+        load(r, t + r + R);
+        load(r + 1, t + r + 1 + R);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  auto put = [&](int m, int n, d2v z) {
+    cplx* c = pC + off(m, d.M0, d.M, d.sCm1, d.sCm0) + off(n, d.N0, d.N, d.sCn1, d.sCn0);
+    const double re = d.are * z[0] - d.aim * z[1], im = d.are * z[1] + d.aim * z[0];
+    if (d.mode == 2) {
+      unsafeAtomicAdd(&c->re, re);
+      unsafeAtomicAdd(&c->im, im);
+    } else if (d.mode == 1) {
+      *c = cplx{re, im};
+    } else {
+      *c = cplx{c->re + re, c->im + im};
+    }
+  };
+  if constexpr (KW == 1) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+          const int m = 16 * (ti * IB + i) + 4 * r + kl, n = 16 * (tj * JB + j) + l16;
+          if (m < d.M && n < d.N) put(m, n, acc.value(i, j, r));
+        }
+  } else {
+    __shared__ d2v red[KW * IB * JB * 256];
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+      for (int j = 0; j < JB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[((wave * IB * JB + i * JB + j) * 4 + r) * 64 + lane] = acc.value(i, j, r);
+    __syncthreads();
+    for (int x = threadIdx.x; x < IB * JB * 256; x += KW * 64) {
+      d2v z = red[x];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) z += red[w * IB * JB * 256 + x];
+      const int l = x & 63, r = (x >> 6) & 3, ij = x >> 8;
+      const int m = 16 * (ti * IB + ij / JB) + 4 * r + (l >> 4), n = 16 * (tj * JB + ij % JB) + (l & 15);
+      if (m < d.M && n < d.N) put(m, n, z);
+    }
+  }
+}
+
+template <int IB, int JB, int KW>
+void launch_frag_gemm(FragGemm& d, int batch, bool two, hipStream_t s) {
+  const int64_t wg = (int64_t)d.gm * d.gn * d.ksplit * batch;
+  RTCC3_CHECK(wg < (1LL << 31), "frag: product too large");
+  const dim3 grid((unsigned)wg), block((KW == 1 ? 4 : KW) * 64);
+  if (!two)
+    hipLaunchKernelGGL((frag_gemm_kernel<IB, JB, KW, -1>), grid, block, 0, s, d);
+  else if (d.K0 & 3)
+    hipLaunchKernelGGL((frag_gemm_kernel<IB, JB, KW, 1>), grid, block, 0, s, d);
+  else
+    hipLaunchKernelGGL((frag_gemm_kernel<IB, JB, KW, 0>), grid, block, 0, s, d);
+  RTCC3_HIP(hipGetLastError());
+}
+
 }  // namespace
 
 namespace {
@@ -822,6 +1030,163 @@ void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, in
     hipLaunchKernelGGL(frag_block_kernel, dim3((unsigned)((nw + 3) / 4)), dim3(256), 0, s, d);
     RTCC3_HIP(hipGetLastError());
   }
+}
+
+namespace {
+
+// The largest offset of a two-level index plus one.
+int64_t reach(int64_t X, int64_t X0, int64_t s1, int64_t s0) { return (X / X0 - 1) * s1 + (X0 - 1) * s0; }
+
+// A wave's tile, the waves that split the k of one (1: none), two levels of k.
+struct FragTile {
+  int ib, jb, kw;
+  bool two;
+};
+
+// The product with n as the index along which C is contiguous, if any, and its
+// k levels in the order the kernel takes; false: not one for the kernel.
+bool frag_gemm_plan(const GemmDesc& g, FragGemm& d, FragTile& tile) {
+  if (g.gk_start || g.ncs || g.nseg || g.comb_n || g.M % g.M0 || g.N % g.N0 || g.K % g.K0) return false;
+  struct Level {
+    int64_t n, a, b;
+  } in{g.K0, g.sAk0, g.sBk0}, out{g.K / g.K0, g.sAk1, g.sBk1};
+  if (in.n == 1) std::swap(in, out);
+  if (out.n == 1) out.a = out.b = 0;
+  if (in.n == 1) in.a = in.b = 0;
+  if (out.n > 1 && out.a == in.n * in.a && out.b == in.n * in.b) {
+    in.n *= out.n;
+    out = Level{1, 0, 0};
+  }
+  // fewer padded steps with the other level inside
+  if (out.n > 1 && in.n * ((out.n + 3) / 4) < out.n * ((in.n + 3) / 4)) std::swap(in, out);
+  const bool two = tile.two = out.n > 1;
+  d.K0 = (int)in.n;
+  d.steps = two ? (int)(out.n * ((in.n + 3) / 4)) : (int)(in.n / 4);
+  const int64_t spanA = reach(g.M, g.M0, g.M0 == g.M ? 0 : g.sAm1, g.M0 == 1 ? 0 : g.sAm0) + (out.n - 1) * out.a + (in.n - 1) * in.a + 1;
+  const int64_t spanB = reach(g.N, g.N0, g.N0 == g.N ? 0 : g.sBn1, g.N0 == 1 ? 0 : g.sBn0) + (out.n - 1) * out.b + (in.n - 1) * in.b + 1;
+  // offsets are formed in 32 bits, for k up to eight past the last
+  if (spanA + 8 * in.a >= (1LL << 27) || spanB + 8 * in.b >= (1LL << 27)) return false;
+  if (in.a < 0 || in.b < 0 || out.a < 0 || out.b < 0 || spanA < 1 || spanB < 1) return false;
+  d.sak1 = (int)(out.a * sizeof(cplx));
+  d.sak0 = (int)(in.a * sizeof(cplx));
+  d.sbk1 = (int)(out.b * sizeof(cplx));
+  d.sbk0 = (int)(in.b * sizeof(cplx));
+  d.A = g.A;
+  d.B = g.B;
+  d.C = g.C;
+  d.M = g.M;
+  d.N = g.N;
+  d.M0 = g.M0;
+  d.N0 = g.N0;
+  d.sAm1 = g.sAm1, d.sAm0 = g.sAm0, d.sAb = g.sAb;
+  d.sBn1 = g.sBn1, d.sBn0 = g.sBn0, d.sBb = g.sBb;
+  d.sCm1 = g.sCm1, d.sCm0 = g.sCm0, d.sCn1 = g.sCn1, d.sCn0 = g.sCn0, d.sCb = g.sCb;
+  d.bl = g.bl;
+  std::copy(g.cA, g.cA + 4, d.cA);
+  std::copy(g.cB, g.cB + 4, d.cB);
+  std::copy(g.cC, g.cC + 4, d.cC);
+  d.nA = spanA;
+  d.nB = spanB;
+  d.are = g.alpha.re;
+  d.aim = g.alpha.im;
+  if (g.sCm0 == 1 && g.sCn0 != 1 && g.M0 > 1) {  // C^T = B^T A^T
+    std::swap(d.A, d.B);
+    std::swap(d.M, d.N);
+    std::swap(d.M0, d.N0);
+    std::swap(d.sAm1, d.sBn1);
+    std::swap(d.sAm0, d.sBn0);
+    std::swap(d.sAb, d.sBb);
+    std::swap(d.sCm1, d.sCn1);
+    std::swap(d.sCm0, d.sCn0);
+    std::swap(d.cA, d.cB);
+    std::swap(d.nA, d.nB);
+    std::swap(d.sak1, d.sbk1);
+    std::swap(d.sak0, d.sbk0);
+  }
+  // rows whose outer level is contiguous in A: numbered the other way round, so
+  // that a fragment reads whole lines (of C, the columns are)
+  if (d.M0 > 1 && d.M0 < d.M && d.sAm1 == 1 && d.sAm0 != 1 && d.sak0 != (int)sizeof(cplx)) {
+    d.M0 = d.M / d.M0;
+    std::swap(d.sAm1, d.sAm0);
+    std::swap(d.sCm1, d.sCm0);
+  }
+  // Tiles of four 16 x 16 blocks a wave in the shape with the least padding
+  // where they fill the chip's 2048 such waves, then (a long enough k) as
+  // workgroups of four waves that split it; else one block and as many waves
+  // for its k as that takes.
+  auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  const int64_t mb = up(d.M, 16), nb = up(d.N, 16);
+  const int64_t p22 = up(mb, 2) * up(nb, 2), p14 = mb * up(nb, 4), p41 = up(mb, 4) * nb;
+  const int64_t wide = std::min(p22, std::min(p14, p41));
+  if (wide * g.batch >= 2048 || (wide * g.batch >= 64 && wide * g.batch * d.steps >= 16384)) {
+    tile.kw = wide * g.batch >= 2048 ? 1 : 4;
+    tile.ib = wide == p22 ? 2 : wide == p14 ? 1 : 4;
+    tile.jb = 4 / tile.ib;
+  } else {
+    const int64_t w = mb * nb * g.batch;
+    tile.kw = w * 4 >= 2048 || d.steps < 16 ? 4 : w * 8 >= 2048 || d.steps < 32 ? 8 : 16;
+    tile.ib = tile.jb = 1;
+  }
+  d.mt = (int)up(mb, tile.ib);
+  d.nt = (int)up(nb, tile.jb);
+  d.wm = tile.kw > 1 || d.mt == 1 ? 1 : d.nt == 1 ? 4 : 2;
+  d.wn = tile.kw > 1 ? 1 : 4 / d.wm;
+  d.gm = (int)up(d.mt, d.wm);
+  d.gn = (int)up(d.nt, d.wn);
+  d.mfast = d.gm <= d.gn;
+  return true;
+}
+
+}  // namespace
+
+bool frag_gemm_fits(const GemmDesc& g) {
+  FragGemm d;
+  FragTile t;
+  return frag_gemm_plan(g, d, t);
+}
+
+// The split of k with the least time by a simple account: rounds of workgroups
+// on the chip, each its steps at the matrix cores' rate and 2 us to begin and
+// end, and the atomic adds of a split product at 1 TB/s.
+int frag_gemm_split(const GemmDesc& g) {
+  FragGemm d;
+  FragTile t;
+  if (!frag_gemm_plan(g, d, t) || g.store) return 1;
+  const int blocks = t.ib * t.jb, waves = t.kw == 1 ? 4 : t.kw;
+  const int per_cu = blocks > 1 ? 2 : std::max(1, 20 / waves);
+  const double step = blocks * 192 / 2400.0 * std::max(1.0, per_cu * waves / 4.0);  // us, a wave's
+  const double wgs = (double)d.gm * d.gn * g.batch;
+  int best = 1;
+  double tbest = 0;
+  for (int ks = 1; ks <= 16 && d.steps >= 8 * ks * t.kw / (t.kw == 1 ? 1 : 2); ++ks) {
+    const double x = std::ceil(wgs * ks / (256.0 * per_cu)) * (std::ceil((double)d.steps / (ks * t.kw)) * step + 2.0) +
+                     (ks > 1 ? (double)d.M * d.N * g.batch * ks * sizeof(cplx) / 1e6 : 0.0);
+    if (ks == 1 || x < 0.9 * tbest) {
+      best = ks;
+      tbest = x;
+    }
+  }
+  return best;
+}
+
+void frag_gemm(const GemmDesc& g, int ksplit, hipStream_t s) {
+  FragGemm d;
+  FragTile t;
+  RTCC3_CHECK(frag_gemm_plan(g, d, t), "frag: bad product");
+  d.ksplit = ksplit;
+  d.mode = g.atomic || ksplit > 1 ? 2 : g.store ? 1 : 0;
+  if (t.ib == 2)
+    t.kw == 1 ? launch_frag_gemm<2, 2, 1>(d, g.batch, t.two, s) : launch_frag_gemm<2, 2, 4>(d, g.batch, t.two, s);
+  else if (t.jb == 4)
+    t.kw == 1 ? launch_frag_gemm<1, 4, 1>(d, g.batch, t.two, s) : launch_frag_gemm<1, 4, 4>(d, g.batch, t.two, s);
+  else if (t.ib == 4)
+    t.kw == 1 ? launch_frag_gemm<4, 1, 1>(d, g.batch, t.two, s) : launch_frag_gemm<4, 1, 4>(d, g.batch, t.two, s);
+  else if (t.kw == 4)
+    launch_frag_gemm<1, 1, 4>(d, g.batch, t.two, s);
+  else if (t.kw == 8)
+    launch_frag_gemm<1, 1, 8>(d, g.batch, t.two, s);
+  else
+    launch_frag_gemm<1, 1, 16>(d, g.batch, t.two, s);
 }
 
 int64_t frag_cols_pack(const int* rows, int njob, int o, int v) {

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "common.h"
+#include "frag_kernels.h"
 
 namespace rtcc3 {
 
@@ -1522,7 +1523,10 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
   // FP32, which is at least as accurate.
   const bool split = d.prec == RTCC3_PREC_BF16X3 || d.prec == RTCC3_PREC_BF16X2;
   const int prec = split && ((d.nseg == 0 && !d.force_prec) || d.comb_n || d.gk_start || d.ncs) ? RTCC3_PREC_FP32 : d.prec;
+  const bool frag = prec == RTCC3_PREC_FP64 && frag_gemm_fits(d);
+  if (frag) ksplit = frag_gemm_split(d);
   auto launch = [&](int ks) {
+    if (frag) return frag_gemm(d, ks, s);
     const int kchunk = (int)((((int64_t)d.K + ks - 1) / ks + BKMAX - 1) / BKMAX * BKMAX);
     RTCC3_CHECK(tiles * ks < (1LL << 31), "gemm: too many tiles");
     RTCC3_CHECK(!d.gk_start || kchunk / d.K0 + 2 <= GK_MAXSEG, "gemm: gathered K range too long for one workgroup");
