@@ -30,7 +30,7 @@ CCSDResult ccsd_evaluate(Engine& e, const Dims& d, const cplx* y, const View& h,
 namespace {
 View fresh_view(Engine& e, const char* name, std::vector<int64_t> shape) {
   View t = e.tensor(name, shape);
-  e.zero(t);
+  e.zero_later(t);
   e.set_requires_grad(t.buf, false);
   return t;
 }
@@ -105,6 +105,7 @@ CCSDResult ccsd_forward(Engine& e, const Dims& d, const cplx* y, const View& h, 
   r.X = X;
   r.Y = Y;
   if (want_grad) e.tape_end();  // paused: the residual continues this tape
+  e.settle();
   return r;
 }
 
@@ -175,6 +176,7 @@ void ccsd_residual(Engine& e, const Dims& d, CCSDResult& r) {
   r.R1 = R1;
   r.R2 = R2;
   if (want_grad) e.tape_end();
+  e.settle();
 }
 
 void ccsd_backward(Engine& e, const Dims& d, const cplx* y, const View& ones_o, CCSDResult& r) {
@@ -196,6 +198,7 @@ void ccsd_backward(Engine& e, const Dims& d, const cplx* y, const View& ones_o, 
   e.axpy(ONE, ones_o, Engine::diag(blk(e.grad(ht), 'o', 'o'), 0, 1));
   e.axpy(ONE, Engine::permute(Lov, {0, 2, 1, 3}), e.grad(t2));
   e.backward();
+  e.settle();
   r.G1 = e.grad(t1);
   r.G2 = e.grad(t2);
   r.Dt = e.grad(ht);

@@ -83,6 +83,12 @@ struct GemmDesc {
   Seg seg[4];
   // store = 1: C = alpha*AB without reading C (no split-K, not atomic).
   int store;
+  // fresh = 1: as if C's buffer, fresh_n elements at fresh_p, were zero: gemm()
+  // stores where it can (every element of the buffer is one of the product's)
+  // and clears the buffer first where it adds.
+  int fresh;
+  cplx* fresh_p;
+  int64_t fresh_n;
   // A bf16-split precision runs unsegmented products in FP32 unless
   // force_prec is set (self-tests of the split kernel).
   int force_prec;
@@ -177,10 +183,19 @@ struct AxpyDesc {
   cplx* Y;
   int64_t sy[8];
   cplx alpha;
+  int store;  // Y = alpha X without reading Y
 };
 void axpy_strided(const AxpyDesc& d, hipStream_t s);
 
 void fill(cplx* p, int64_t n, cplx val, hipStream_t s);
+// Several buffers zeroed by one launch (per kMaxZero of them).
+struct ZeroList {
+  static constexpr int kMaxZero = 32;
+  cplx* p[kMaxZero];
+  int64_t n[kMaxZero];
+  int count;
+};
+void zero_many(const ZeroList& z, hipStream_t s);
 void fill_int(int* p, int64_t n, int val, hipStream_t s);
 // Propagation state on the device, so that one RK4 step is the same work every
 // time (a captured graph replays it): pst[0] = step within the current chunk,

@@ -63,7 +63,95 @@ cplx* Engine::twin_out(const cplx* p) {
   return t + off;
 }
 
+bool* Engine::due(const cplx* p, const Range** r) {
+  if (ndue_ == 0) return nullptr;
+  int64_t off = 0;
+  *r = find(p, &off);
+  if (!*r) return nullptr;
+  Buf& b = bufs_[(*r)->buf];
+  bool* f = (*r)->kind == 0 ? &b.p_due : &b.g_due;
+  return *f ? f : nullptr;
+}
+
+void Engine::touch(const cplx* p) {
+  const Range* r = nullptr;
+  bool* f = due(p, &r);
+  if (!f) return;
+  *f = false;
+  --ndue_;
+  const Buf& b = bufs_[r->buf];
+  fill(r->kind == 0 ? b.p : b.g, b.n, cplx{0, 0}, stream);
+}
+
+bool Engine::claim(const View& v) {
+  const Range* r = nullptr;
+  bool* f = due(v.p, &r);
+  if (!f) return false;
+  // every element once: the strides are those of a dense tensor in some order
+  bool all = v.numel() == r->n;
+  std::vector<std::pair<int64_t, int64_t>> d;
+  for (int k = 0; k < v.nd; ++k)
+    if (v.sh[k] != 1) d.push_back({v.st[k], v.sh[k]});
+  std::sort(d.begin(), d.end());
+  int64_t s = 1;
+  for (auto& x : d) {
+    all = all && x.first == s;
+    s *= x.second;
+  }
+  if (!all) {
+    touch(v.p);
+    return false;
+  }
+  *f = false;
+  --ndue_;
+  return true;
+}
+
+void Engine::zero_later(const View& v) {
+  int64_t off = 0;
+  const Range* r = find(v.p, &off);
+  if (!r || off != 0 || v.numel() != r->n) return zero(v);
+  Buf& b = bufs_[r->buf];
+  bool& f = r->kind == 0 ? b.p_due : b.g_due;
+  if (!f) ++ndue_;
+  f = true;
+  bool& nz = r->kind == 0 ? b.tp_nz : b.tg_nz;
+  if (nz) fill(r->kind == 0 ? b.tp : b.tg, b.n, cplx{0, 0}, stream);
+  nz = false;
+}
+
+void Engine::settle() {
+  if (ndue_ == 0) return;
+  ZeroList z;
+  z.count = 0;
+  auto add = [&](cplx* p, int64_t n, bool& f) {
+    if (!f) return;
+    f = false;
+    z.p[z.count] = p;
+    z.n[z.count++] = n;
+    if (z.count < ZeroList::kMaxZero) return;
+    zero_many(z, stream);
+    z.count = 0;
+  };
+  for (auto& b : bufs_) {
+    add(b.p, b.n, b.p_due);
+    add(b.g, b.n, b.g_due);
+  }
+  if (z.count > 0) zero_many(z, stream);
+  ndue_ = 0;
+}
+
 void Engine::copy(cplx* dst, const cplx* src, int64_t n) {
+  touch(src);
+  const Range* rd = nullptr;
+  if (bool* f = due(dst, &rd)) {
+    if (n == rd->n) {
+      *f = false;
+      --ndue_;
+    } else {
+      touch(dst);
+    }
+  }
   rtcc3::copy(dst, src, n, stream);
   if (!tangent_) return;
   const cplx* st = twin(src);
@@ -111,6 +199,8 @@ void Engine::release(const std::string& name) {
   if (b.g) ranges_.erase(b.g);
   for (cplx* q : {b.p, b.g, b.tp, b.tg})
     if (q) RTCC3_HIP(hipFree(q));
+  ndue_ -= (int)b.p_due + (int)b.g_due;
+  b.p_due = b.g_due = false;
   b.p = b.g = b.tp = b.tg = nullptr;
   b.tp_nz = b.tg_nz = false;
   b.n = 0;
@@ -163,6 +253,7 @@ void Engine::zero(const View& v) {
     s *= v.sh[k];
   }
   RTCC3_CHECK(contiguous, "engine: zero() needs a contiguous view");
+  (void)claim(v);  // cleared here if that is due
   fill(v.p, v.numel(), cplx{0, 0}, stream);
   if (!twins_) return;
   int64_t off = 0;
@@ -177,6 +268,10 @@ void Engine::zero(const View& v) {
 
 void Engine::zero_buffer(int buf) {
   Buf& b = bufs_[buf];
+  if (b.p_due) {
+    b.p_due = false;
+    --ndue_;
+  }
   fill(b.p, b.n, cplx{0, 0}, stream);
   if (b.tp_nz) fill(b.tp, b.n, cplx{0, 0}, stream);
   b.tp_nz = false;
@@ -263,10 +358,12 @@ void Engine::tape_begin() {
   recording_ = true;
 }
 
+// The gradients' clearing waits for their first use, as in zero_later().
 void Engine::zero_grads() {
   for (auto& b : bufs_)
     if (b.rg && b.g) {
-      fill(b.g, b.n, cplx{0, 0}, stream);
+      if (!b.g_due) ++ndue_;
+      b.g_due = true;
       if (b.tg_nz) fill(b.tg, b.n, cplx{0, 0}, stream);
       b.tg_nz = false;
     }
@@ -302,6 +399,8 @@ void Engine::axpy_exec(cplx alpha, const View& X, const View& Y) {
   d.X = X.p;
   d.Y = Y.p;
   d.alpha = alpha;
+  touch(X.p);
+  d.store = claim(Y);
   axpy_strided(d, stream);
 }
 
@@ -427,6 +526,8 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
   add(sc, C0);
   for (auto& kv : ext)
     if (kv.second == 0) return;  // empty contraction or output
+  touch(A0.p);
+  touch(B0.p);
   std::string gb, gm, gn, gk;
   for (char c : sc) {
     const bool ina = sa.find(c) != std::string::npos, inb = sb.find(c) != std::string::npos;
@@ -510,7 +611,6 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       }());
       std::vector<int> perm;
       for (char c : gb + gm + gk) perm.push_back((int)oa.idx.find(c));
-      fill(t.p, t.numel(), cplx{0, 0}, stream);
       View src = permute(A, perm);
       AxpyDesc d;
       d.nd = t.nd;
@@ -522,6 +622,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       d.X = src.p;
       d.Y = t.p;
       d.alpha = cplx{1, 0};
+      d.store = 1;
       axpy_strided(d, stream);
       A = t;
       oa.idx = gb + gm + gk;
@@ -535,7 +636,6 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       }());
       std::vector<int> perm;
       for (char c : gb + gk + gn) perm.push_back((int)ob.idx.find(c));
-      fill(t.p, t.numel(), cplx{0, 0}, stream);
       View src = permute(B, perm);
       AxpyDesc d;
       d.nd = t.nd;
@@ -547,6 +647,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       d.X = src.p;
       d.Y = t.p;
       d.alpha = cplx{1, 0};
+      d.store = 1;
       axpy_strided(d, stream);
       B = t;
       ob.idx = gb + gk + gn;
@@ -559,7 +660,6 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     std::vector<int64_t> s;
     for (char c : gb + gm + gn) s.push_back(ext.at(c));
     C = raw(take(extent(gb + gm + gn, ext)), s);
-    fill(C.p, C.numel(), cplx{0, 0}, stream);
     oc.idx = gb + gm + gn;
   }
   // final split points (all operands now compatible)
@@ -615,6 +715,16 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
   RTCC3_CHECK(reach(g.M, g.M0, g.sCm1, g.sCm0) + reach(g.N, g.N0, g.sCn1, g.sCn0) +
                       (int64_t)(g.batch - 1) * g.sCb <= extent_of(C),
               "einsum: C access out of range in " + spec);
+  const bool fresh = claim(C0);
+  if (copyC) {
+    g.fresh = 1;
+    g.fresh_p = C.p;
+    g.fresh_n = C.numel();
+  } else if (fresh) {
+    g.fresh = 1;
+    g.fresh_p = C0.p;
+    g.fresh_n = C0.numel();
+  }
   gemm(g, stream);
   if (copyC) {
     // scatter the temp result into the real output
@@ -631,6 +741,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     d.X = src.p;
     d.Y = Cfinal.p;
     d.alpha = cplx{1, 0};
+    d.store = fresh;
     axpy_strided(d, stream);
   }
 }

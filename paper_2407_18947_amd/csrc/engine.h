@@ -50,6 +50,13 @@ class Engine {
   View tensor_of(int buf, std::vector<int64_t> shape);
   void zero(const View& v);
   void zero_buffer(int buf);
+  // zero() whose clearing waits for the first use: an operation that writes
+  // all of the buffer (or gradient) stores instead of adding, any other one
+  // clears it first.  settle() clears what has had no use, before anything but
+  // this engine's operations reads it: each function that calls zero_later()
+  // ends with it.
+  void zero_later(const View& v);
+  void settle();
   cplx* data(int buf) { return bufs_[buf].p; }
   int64_t size(int buf) { return bufs_[buf].n; }
 
@@ -115,6 +122,7 @@ class Engine {
     cplx* tp = nullptr;  // twin of p
     cplx* tg = nullptr;  // twin of g
     bool tp_nz = false, tg_nz = false;  // twin written since it was last cleared
+    bool p_due = false, g_due = false;  // to be cleared (zero_later)
   };
   // address range of a buffer (kind 0) or gradient (kind 1)
   struct Range {
@@ -126,6 +134,10 @@ class Engine {
   bool twins_ = false, tangent_ = false;
   const Range* find(const cplx* p, int64_t* off) const;
   cplx* alloc_twin(int64_t n);
+  int ndue_ = 0;  // buffers and gradients to be cleared
+  bool* due(const cplx* p, const Range** r);
+  void touch(const cplx* p);   // clears the buffer of p if that is due
+  bool claim(const View& v);   // the same, or, if v is all of it, leaves it to the caller: true
   void einsum_dual(const std::string& spec, cplx alpha, const View& A, const View& B, const View& C);
   void axpy_exec(cplx alpha, const View& X, const View& Y);
   struct Op {

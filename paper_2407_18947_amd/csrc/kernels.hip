@@ -1067,22 +1067,34 @@ __global__ __launch_bounds__(NT, CMB == 2 ? 2 : 3) void zgemm_kb_f64_kernel(Gemm
       }
 }
 
+// Y = alpha X (+ Y) over up to 8 index runs; INT the type indexes are formed in.
+template <typename INT>
 __global__ void axpy_kernel(AxpyDesc d, int64_t total) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
-    int64_t r = e, ox = 0, oy = 0;
-    for (int k = d.nd - 1; k >= 0; --k) {
-      const int64_t q = r % d.shape[k];
-      r /= d.shape[k];
+    INT r = (INT)e;
+    int64_t ox = 0, oy = 0;
+    for (int k = d.nd - 1; k > 0; --k) {
+      const INT h = r / (INT)d.shape[k], q = r - h * (INT)d.shape[k];
+      r = h;
       ox += q * d.sx[k];
       oy += q * d.sy[k];
     }
+    ox += r * d.sx[0];
+    oy += r * d.sy[0];
     const cplx x = d.X[ox];
-    cplx y = d.Y[oy];
+    cplx y = d.store ? cplx{0, 0} : d.Y[oy];
     y.re += d.alpha.re * x.re - d.alpha.im * x.im;
     y.im += d.alpha.re * x.im + d.alpha.im * x.re;
     d.Y[oy] = y;
   }
+}
+
+__global__ void zero_many_kernel(ZeroList z) {
+  cplx* p = z.p[blockIdx.y];
+  const int64_t n = z.n[blockIdx.y];
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+    p[e] = cplx{0, 0};
 }
 
 __global__ void fill_kernel(cplx* p, int64_t n, cplx v) {
@@ -1368,7 +1380,7 @@ uint64_t desc_key(const GemmDesc& d) {
   for (int64_t x : {(int64_t)d.M, (int64_t)d.N, (int64_t)d.K, (int64_t)d.batch, (int64_t)d.M0, (int64_t)d.N0,
                     (int64_t)d.K0, d.sAm1, d.sAm0, d.sAk1, d.sAk0, d.sAb, d.sBk1, d.sBk0, d.sBn1, d.sBn0, d.sBb,
                     d.sCm1, d.sCm0, d.sCn1, d.sCn0, d.sCb, (int64_t)d.atomic, (int64_t)d.prec, (int64_t)d.store,
-                    (int64_t)d.nseg, (int64_t)d.ncs, (int64_t)d.comb_n, (int64_t)d.comb_on,
+                    (int64_t)d.fresh, (int64_t)d.nseg, (int64_t)d.ncs, (int64_t)d.comb_n, (int64_t)d.comb_on,
                     (int64_t)(d.gk_start != nullptr), (int64_t)(d.bl != nullptr), (int64_t)d.force_prec})
     k.add(x);
   for (int i = 0; i < d.ncs; ++i) {
@@ -1525,7 +1537,16 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
   const int prec = split && ((d.nseg == 0 && !d.force_prec) || d.comb_n || d.gk_start || d.ncs) ? RTCC3_PREC_FP32 : d.prec;
   const bool frag = prec == RTCC3_PREC_FP64 && frag_gemm_fits(d);
   if (frag) ksplit = frag_gemm_split(d);
-  auto launch = [&](int ks) {
+  auto launch = [&](int ks, bool trial = false) {
+    // In FP32 the trials add in any case: which split is the fastest by itself
+    // decides, since the split is also how far the sums are formed in FP32.
+    d.store = d_in.store;
+    if (d.fresh && (frag || !trial)) {
+      if (ks == 1 && !d.atomic)
+        d.store = 1;
+      else
+        fill(d.fresh_p, d.fresh_n, cplx{0, 0}, s);
+    }
     if (frag) return frag_gemm(d, ks, s);
     const int kchunk = (int)((((int64_t)d.K + ks - 1) / ks + BKMAX - 1) / BKMAX * BKMAX);
     RTCC3_CHECK(tiles * ks < (1LL << 31), "gemm: too many tiles");
@@ -1566,14 +1587,14 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
       const int64_t kmax = std::max<int64_t>(kmin, d.K / 64);
       for (int64_t ks = kmin; ks <= kmax && ks <= 64; ks *= 2)
         if (ks != ksplit) cand.push_back((int)ks);
-      launch(ksplit);  // warm the caches
+      launch(ksplit, true);  // warm the caches
       float best_ms = 1e30f, heur_ms = 0.f;
       int best = ksplit;
       for (int ks : cand) {
         float ms = 1e30f;
         for (int rep = 0; rep < 2; ++rep) {
           RTCC3_HIP(hipEventRecord(tu->e0, s));
-          launch(ks);
+          launch(ks, true);
           RTCC3_HIP(hipEventRecord(tu->e1, s));
           RTCC3_HIP(hipEventSynchronize(tu->e1));
           float t = 0.f;
@@ -1598,11 +1619,44 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
   launch(ksplit);
 }
 
-void axpy_strided(const AxpyDesc& d, hipStream_t s) {
+void axpy_strided(const AxpyDesc& d_in, hipStream_t s) {
+  // index runs that are contiguous in both operands count as one
+  AxpyDesc d = d_in;
+  d.nd = 0;
   int64_t total = 1;
-  for (int k = 0; k < d.nd; ++k) total *= d.shape[k];
+  for (int k = 0; k < d_in.nd; ++k) {
+    total *= d_in.shape[k];
+    if (d_in.shape[k] == 1) continue;
+    if (d.nd > 0 && d.sx[d.nd - 1] == d_in.sx[k] * d_in.shape[k] && d.sy[d.nd - 1] == d_in.sy[k] * d_in.shape[k]) {
+      d.shape[d.nd - 1] *= d_in.shape[k];
+      d.sx[d.nd - 1] = d_in.sx[k];
+      d.sy[d.nd - 1] = d_in.sy[k];
+    } else {
+      d.shape[d.nd] = d_in.shape[k];
+      d.sx[d.nd] = d_in.sx[k];
+      d.sy[d.nd] = d_in.sy[k];
+      ++d.nd;
+    }
+  }
   if (total <= 0) return;
-  hipLaunchKernelGGL(axpy_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, d, total);
+  if (d.nd == 0) {
+    d.nd = 1;
+    d.shape[0] = 1;
+    d.sx[0] = d.sy[0] = 0;
+  }
+  if (total < (1LL << 32))
+    hipLaunchKernelGGL(axpy_kernel<uint32_t>, dim3(grid_for(total, 256)), dim3(256), 0, s, d, total);
+  else
+    hipLaunchKernelGGL(axpy_kernel<int64_t>, dim3(grid_for(total, 256)), dim3(256), 0, s, d, total);
+  RTCC3_HIP(hipGetLastError());
+}
+
+void zero_many(const ZeroList& z, hipStream_t s) {
+  int64_t most = 0;
+  for (int k = 0; k < z.count; ++k) most = std::max(most, z.n[k]);
+  if (most <= 0) return;
+  const dim3 grid(grid_for(most, 256), (unsigned)z.count);
+  hipLaunchKernelGGL(zero_many_kernel, grid, dim3(256), 0, s, z);
   RTCC3_HIP(hipGetLastError());
 }
 

@@ -181,7 +181,7 @@ void rhs_impl(rtcc3_ctx* c, FieldRef E, const cplx* y, cplx* dy, const TermsOut&
   if (want_density) {
     // D = D_ccsd + triples terms (T1-transformed frame); mu_x = sum_pq D_pq mu~^x_pq
     View D = e.tensor("Dtot", {n, n});
-    e.zero(D);
+    e.zero_later(D);
     e.axpy(ONE, r.Dt, D);
     if (with_triples) {
       e.axpy(ONE, to.Dij, Engine::slice(Engine::slice(D, 0, 0, o), 1, 0, o));
@@ -189,14 +189,15 @@ void rhs_impl(rtcc3_ctx* c, FieldRef E, const cplx* y, cplx* dy, const TermsOut&
       e.axpy(ONE, to.Dia, Engine::slice(Engine::slice(D, 0, 0, o), 1, o, n));
     }
     View muX = e.tensor("muX", {3, n, n});
-    e.zero(muX);
+    e.zero_later(muX);
     e.einsum("pr,xrs->xps", ONE, r.X, c->mu, muX);
     View mut = e.tensor("mut", {3, n, n});
-    e.zero(mut);
+    e.zero_later(mut);
     e.einsum("xps,sq->xpq", ONE, muX, r.Y, mut);
     View m3 = e.tensor("mu3", {3});
-    e.zero(m3);
+    e.zero_later(m3);
     e.einsum("pq,xpq->x", ONE, D, mut, m3);
+    e.settle();
     if (t.mu) copy(t.mu, m3.p, 3, c->stream);
     if (t.mu_dot) {
       const cplx* m3t = e.twin(m3.p);

@@ -865,7 +865,7 @@ void Triples::blocks(Engine& e, const CCSDResult& r) {
   };
   auto make = [&](const char* name, std::vector<int64_t> shape) {
     View t = e.tensor(name, shape);
-    e.zero(t);
+    e.zero_later(t);
     return t;
   };
   View t;
@@ -1545,10 +1545,13 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   std::vector<std::vector<int64_t>> shapes = {{o, v},       {o, o, v, v}, {o, v},       {o, o, v, v},
                                               {o, v},       {o, o, v, o}, {o, o, v, o}, {o, o, v, o},
                                               {o, o, v, o}, {o, v, v, v}};
-  for (size_t i = 0; i < shapes.size(); ++i) e.zero(e.tensor(names[i], shapes[i]));
+  for (size_t i = 0; i < shapes.size(); ++i) e.zero_later(e.tensor(names[i], shapes[i]));
   if (want_density) {
-    e.zero(e.tensor("td_Dij", {o, o}));
-    e.zero(e.tensor("td_Dab", {v, v}));
+    e.zero_later(e.tensor("td_Dij", {o, o}));
+    e.zero_later(e.tensor("td_Dab", {v, v}));
+  }
+  e.settle();
+  if (want_density) {
     // one pass over the pair windows: right-hand side for the owned blocks, density terms
     for (auto& w : den_windows_) window_pass(e, w, y, true);
   } else {
@@ -1592,12 +1595,12 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   out.Y1 = Y1;
   // P_ij^ab symmetrisation of X2 and Y2
   View X2 = e.tensor("tr_X2", {o, o, v, v});
-  e.zero(X2);
+  e.zero_later(X2);
   View X2p = e.tensor("tr_X2p", {o, o, v, v});
   e.axpy(ONE, X2p, X2);
   e.axpy(ONE, Engine::permute(X2p, {1, 0, 3, 2}), X2);
   View Y2 = e.tensor("tr_Y2", {o, o, v, v});
-  e.zero(Y2);
+  e.zero_later(Y2);
   View Y2p = e.tensor("tr_Y2p", {o, o, v, v});
   e.axpy(ONE, Y2p, Y2);
   e.axpy(ONE, Engine::permute(Y2p, {1, 0, 3, 2}), Y2);
@@ -1608,7 +1611,7 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
     View Dij = e.tensor("td_Dij", {o, o}), Dab = e.tensor("td_Dab", {v, v});
     View Z34 = e.tensor("tr_Z34", {o, v});
     View Dia = e.tensor("td_Dia", {o, v});
-    e.zero(Dia);
+    e.zero_later(Dia);
     e.axpy(ONE, Z34, Dia);
     View t2 = Engine::raw(const_cast<cplx*>(y) + ov, {o, o, v, v});
     e.einsum("kjbx,kjab->xa", R(-1), e.tensor("tr_R8", {o, o, v, o}), t2, Dia);
@@ -1616,6 +1619,7 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
     out.Dab = Dab;
     out.Dia = Dia;
   }
+  e.settle();
   if (timing_on_) RTCC3_HIP(hipEventRecord(rev_[nrev_++], s));
   return out;
 }
