@@ -576,6 +576,38 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     return bx.size() >= by.size() ? 1 : 2;
   };
 
+  // A sum over three runs of indices (FP64): one of them becomes a batch whose
+  // entries add to the same output, rather than one operand copied into
+  // another order.  (ibde,daeb->ia with 1.4 GB of daeb, o=4, v=96: copy and
+  // product 3.2 ms, as a batch over d 0.3.)
+  bool summed = false;
+  if (prec == RTCC3_PREC_FP64 && gb.empty()) {
+    int sm, sn;
+    std::vector<int> u = breaks(oa, gk, ext);
+    for (int b : breaks(ob, gk, ext))
+      if (std::find(u.begin(), u.end(), b) == u.end()) u.push_back(b);
+    if (u.size() == 2 && split_of(oa, oc, gm, sm) == 0 && split_of(ob, oc, gn, sn) == 0) {
+      std::sort(u.begin(), u.end());
+      const int cut[4] = {0, u[0], u[1], (int)gk.size()};
+      int best = 0;
+      int64_t far = -1;
+      for (int x = 0; x < 3; ++x) {  // the run that is least contiguous in either operand
+        int64_t a, b, t0, t1;
+        const std::string g = gk.substr(cut[x], cut[x + 1] - cut[x]);
+        level_strides(oa, g, 0, ext, t0, t1, a);
+        level_strides(ob, g, 0, ext, t0, t1, b);
+        if (std::min(a, b) > far) {
+          far = std::min(a, b);
+          best = x;
+        }
+      }
+      gb = gk.substr(cut[best], cut[best + 1] - cut[best]);
+      gk.erase(cut[best], cut[best + 1] - cut[best]);
+      summed = true;
+      (void)scratch(need);  // what the copy takes, for a later switch of the precision
+    }
+  }
+
   bool copyA = false, copyB = false, copyC = false;
   // batch group must be a single run in every operand
   if (!breaks(oa, gb, ext).empty()) copyA = true;
@@ -691,6 +723,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
   g.C = C.p;
   g.alpha = alpha;
   g.prec = prec;
+  g.atomic = summed;
   if (g.K == 0) return;
   // host-side guard: the GEMM must not reach beyond the extent of its views
   auto reach = [](int64_t X, int64_t X0, int64_t s1, int64_t s0) -> int64_t {
