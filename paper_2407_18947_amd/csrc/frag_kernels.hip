@@ -445,7 +445,7 @@ struct FragCols {
 
 template <int IB, int NS>
 __device__ __forceinline__ void cols_unit(const FragCols& d, const ColsUnit& u, int f, int split) {
-  constexpr int D = 3;
+  constexpr int D = NS == 3 && IB <= 4 ? 4 : 3;
   const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
   const int v = d.v;
   const int64_t vb = (int64_t)v * v * d.vp;
@@ -542,8 +542,8 @@ __device__ __forceinline__ void cols_unit(const FragCols& d, const ColsUnit& u, 
 
 // X2 (three streams) and Y2 with R8 (one).  Bound by the matrix cores (Y2: MFMA
 // busy 0.88 of the SIMD cycles) and, for X2, by the three orderings of each
-// block that pass through the L2.  o=15, v=57, alone: X2 5.9 -> 5.6 ms, Y2 and R8
-// 7.6 -> 5.4; o=10, v=38: 0.73 -> 0.45 and 0.85 -> 0.45, since columns of all
+// block that pass through the L2.  o=15, v=57, alone: X2 5.9 -> 5.3 ms, Y2 and R8
+// 7.6 -> 5.2; o=10, v=38: 0.73 -> 0.43 and 0.85 -> 0.45, since columns of all
 // entries of a K are numbered through and rows come in blocks of 16.  A read
 // straight from the integrals (64-byte pieces of rows 52 KB apart) instead of
 // packed panels made that 9.6 and 7.8 ms.
@@ -572,7 +572,7 @@ __global__ __launch_bounds__(256, 2) void frag_cols_kernel(FragCols d) {
       cols_unit<4, NS>(d, u, f, split);
       break;
     default:
-      if constexpr (NS == 1) cols_unit<5, NS>(d, u, f, split);
+      cols_unit<5, NS>(d, u, f, split);
   }
 }
 
@@ -1238,13 +1238,18 @@ void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, in
   d.npanel = (int)rb.size();
   // Row blocks in groups as large as the registers allow (the sums of a B
   // fragment and, with three streams, its combination serve all of a group's
-  // rows), of about the same size.
-  const int most = nstream == 1 ? 5 : 4;
+  // rows), of about the same size.  Five blocks in one group where four would
+  // make two: X2 at o=16, v=66 26.2 -> 11.8 ms.
+  const int most = 5;
   const int ng = ((int)rb.size() + most - 1) / most;
   auto launch = [&]() {
-    // splits of k for at least four rounds of the chip's 2048 waves, of 32 steps or more
+    // Splits of k for at least four rounds of the chip's 2048 waves, of 32 steps
+    // or more; and of 256 to 511 steps, at whose ends the waves that share blocks
+    // meet again (X2 at o=16, v=66 12.4 -> 11.0 ms, o=15, v=57 5.46 -> 5.28; of 33
+    // steps at o=10, v=38 0.43 -> 0.53).
     const int64_t waves = (int64_t)nfrag * d.nunit;
-    d.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>((4 * 2048 + waves - 1) / waves, d.steps / 32));
+    d.nsplit = (int)std::max<int64_t>(1, std::max<int64_t>(std::min<int64_t>((4 * 2048 + waves - 1) / waves, d.steps / 32),
+                                                           d.steps / 256));
     const int64_t nw = waves * d.nsplit;
     RTCC3_CHECK(nw < (1LL << 31), "frag: product too large");
     const dim3 grid((unsigned)((nw + 3) / 4));
