@@ -444,8 +444,10 @@ void launch_gram(const cplx* A, const cplx* B, const int* slabs, int nslab, int 
                  hipStream_t s) {
   if (nslab <= 0 || K <= 0) return;
   RTCC3_CHECK(o >= 1 && o <= 16, "gram: at most 16 rows");
-  // about 2048 workgroups over the slabs, K ranges in whole LDS stages
-  const int64_t per = std::max<int64_t>(1, (2048 + nslab - 1) / nslab);
+  // About 2048 workgroups over the slabs, K ranges in whole LDS stages, of 16 or
+  // more: each adds to the same o^2 elements, some 45 ns a workgroup (o=5, v=18:
+  // 1525 workgroups of two stages took 69 us, MEASURED).
+  const int64_t per = std::max<int64_t>(1, std::min<int64_t>((2048 + nslab - 1) / nslab, K / (16 * GR_KC)));
   const int64_t kchunk = ((K + per - 1) / per + GR_KC - 1) / GR_KC * GR_KC;
   const unsigned nx = (unsigned)((K + kchunk - 1) / kchunk);
   RTCC3_CHECK(nslab < 65536, "gram: too many slabs");
