@@ -729,11 +729,26 @@ __global__ __launch_bounds__(256, 2) void frag_block_kernel(FragBlock d) {
   }
 }
 
+// x / d for 0 <= x < 2^31 by a multiplication: with 2^(s-1) < d <= 2^s, m =
+// floor(2^(31+s) / d) + 1 is at most 2^32 - 1 and too large by less than 2^-s of
+// 2^31 (an integer division takes some 35 instructions, which is what a small
+// product waits for).
+struct Divisor {
+  uint32_t d = 1, m = 0x80000001u, s = 0;
+  Divisor() = default;
+  explicit Divisor(int64_t x) : d((uint32_t)x) {
+    while ((1ll << s) < x) ++s;
+    m = (uint32_t)((1ull << (31 + s)) / d + 1);
+  }
+  __device__ __forceinline__ int quot(int x) const { return (int)(__umulhi(2u * (uint32_t)x, m) >> s); }
+};
+
 struct FragGemm {
   const cplx* A;
   const cplx* B;
   cplx* C;
   int M, N, M0, N0;
+  Divisor per, fast, split, dM0, dN0, drun;  // workgroups of an entry and split, those of its fast index, ksplit, M0, N0, run
   int64_t sAm1, sAm0, sBn1, sBn0, sCm1, sCm0, sCn1, sCn0, sAb, sBb, sCb;
   const int* bl;
   int64_t cA[4], cB[4], cC[4];
@@ -764,18 +779,19 @@ struct FragGemm {
 // 18 us LDS-tiled product with its split added by atomics becomes one of 6 us:
 // a workgroup's waves split k down to a few steps each).  Steps in pairs with k
 // next to each other (8u + 2 (l/16) + 0, 1) made k-fast operands read half lines
-// twice as often: 6.6 ms at o=15.
+// twice as often: 6.6 ms at o=15.  Where a workgroup has one block, its thread's
+// element of C is loaded before the product and indexes are divided by
+// multiplications: o=5, v=18 0.67 -> 0.56 ms.
 template <int IB, int JB, int KW, int TAIL>
 __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) void frag_gemm_kernel(FragGemm d) {
-  constexpr int R = IB * JB > 1 ? 4 : 6;  // steps in flight
+  constexpr int R = IB * JB > 1 || KW > 4 ? 4 : 6;  // steps in flight
   const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  int g = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
-  const int per = d.gm * d.gn;
-  const int t = g % per;
-  g /= per;
-  const int ks = g % d.ksplit, e = g / d.ksplit;
-  int ti = d.mfast ? t % d.gm : t / d.gn, tj = d.mfast ? t / d.gm : t % d.gn;
+  const int g = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+  const int ge = d.per.quot(g), t = g - ge * (int)d.per.d;
+  const int e = d.split.quot(ge), ks = ge - e * (int)d.split.d;
+  const int slow = d.fast.quot(t), fast = t - slow * (int)d.fast.d;
+  int ti = d.mfast ? fast : slow, tj = d.mfast ? slow : fast;
   if constexpr (KW == 1) {
     ti = ti * d.wm + wave % d.wm;
     tj = tj * d.wn + wave / d.wm;
@@ -795,12 +811,26 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
     pB += d.sBb * e;
     pC += d.sCb * e;
   }
-  auto off = [](int x, int X0, int X, int64_t s1, int64_t s0) {
-    if (X0 == X) return x * s0;
-    const int h = x / X0;
-    return h * s1 + (x - h * X0) * s0;
+  auto off = [](int x, int X, const Divisor& X0, int64_t s1, int64_t s0) {
+    if ((int)X0.d == X) return x * s0;
+    const int h = X0.quot(x);
+    return h * s1 + (x - h * (int)X0.d) * s0;
   };
   const auto ra = rsrc(pA, d.nA), rb = rsrc(pB, d.nB);
+  auto at_c = [&](int m, int n) {
+    return pC + off(m, d.M, d.dM0, d.sCm1, d.sCm0) + off(n, d.N, d.dN0, d.sCn1, d.sCn0);
+  };
+  // one block a workgroup: the thread's element of C, on its way as long as the
+  // product is formed
+  [[maybe_unused]] cplx* c1 = nullptr;
+  [[maybe_unused]] d2v old = {0, 0};
+  if constexpr (IB * JB == 1) {
+    const int x = threadIdx.x, m = 16 * ti + 4 * (x >> 6) + kl, n = 16 * tj + l16;
+    if (x < 256 && m < d.M && n < d.N) {
+      c1 = at_c(m, n);
+      if (d.mode == 0) old = *reinterpret_cast<const d2v*>(c1);
+    }
+  }
   constexpr int kOut = 0x7ffffff0;  // beyond every operand (spans below 2^31 bytes)
   // row and column offsets, and those of the lane's first k
   constexpr bool TWO = TAIL >= 0;
@@ -808,12 +838,12 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
   const int rest = d.K0 & 3;
 #pragma unroll
   for (int i = 0; i < IB; ++i) {
-    ao[i] = (int)off(min(16 * (ti * IB + i) + l16, d.M - 1), d.M0, d.M, d.sAm1, d.sAm0) * (int)sizeof(cplx) + kl * d.sak0;
+    ao[i] = (int)off(min(16 * (ti * IB + i) + l16, d.M - 1), d.M, d.dM0, d.sAm1, d.sAm0) * (int)sizeof(cplx) + kl * d.sak0;
     al[i] = kl < rest ? ao[i] : kOut;
   }
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
-    bo[j] = (int)off(min(16 * (tj * JB + j) + l16, d.N - 1), d.N0, d.N, d.sBn1, d.sBn0) * (int)sizeof(cplx) + kl * d.sbk0;
+    bo[j] = (int)off(min(16 * (tj * JB + j) + l16, d.N - 1), d.N, d.dN0, d.sBn1, d.sBn0) * (int)sizeof(cplx) + kl * d.sbk0;
     bl[j] = kl < rest ? bo[j] : kOut;
   }
   // the wave's steps
@@ -835,7 +865,7 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
   [[maybe_unused]] const int run = (d.K0 + 3) >> 2;  // steps of an inner run
   [[maybe_unused]] int k1 = 0, q = 0;
   if constexpr (TWO) {
-    k1 = t0 / run;
+    k1 = d.drun.quot(t0);
     q = t0 - k1 * run;
   }
   auto load = [&](int r, int t) {
@@ -881,7 +911,7 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
     }
   }
   auto put = [&](int m, int n, d2v z) {
-    cplx* c = pC + off(m, d.M0, d.M, d.sCm1, d.sCm0) + off(n, d.N0, d.N, d.sCn1, d.sCn0);
+    cplx* c = at_c(m, n);
     const double re = d.are * z[0] - d.aim * z[1], im = d.are * z[1] + d.aim * z[0];
     if (d.mode == 2) {
       unsafeAtomicAdd(&c->re, re);
@@ -911,6 +941,20 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[((wave * IB * JB + i * JB + j) * 4 + r) * 64 + lane] = acc.value(i, j, r);
     __syncthreads();
+    if constexpr (IB * JB == 1) {
+      if (!c1) return;
+      d2v z = red[threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) z += red[w * 256 + threadIdx.x];
+      const double re = d.are * z[0] - d.aim * z[1], im = d.are * z[1] + d.aim * z[0];
+      if (d.mode == 2) {
+        unsafeAtomicAdd(&c1->re, re);
+        unsafeAtomicAdd(&c1->im, im);
+      } else {
+        *c1 = cplx{old[0] + re, old[1] + im};
+      }
+      return;
+    }
     for (int x = threadIdx.x; x < IB * JB * 256; x += KW * 64) {
       d2v z = red[x];
 #pragma unroll
@@ -1134,6 +1178,11 @@ bool frag_gemm_plan(const GemmDesc& g, FragGemm& d, FragTile& tile) {
   d.gm = (int)up(d.mt, d.wm);
   d.gn = (int)up(d.nt, d.wn);
   d.mfast = d.gm <= d.gn;
+  d.per = Divisor((int64_t)d.gm * d.gn);
+  d.fast = Divisor(d.mfast ? d.gm : d.gn);
+  d.dM0 = Divisor(d.M0);
+  d.dN0 = Divisor(d.N0);
+  d.drun = Divisor((d.K0 + 3) / 4);
   return true;
 }
 
@@ -1174,6 +1223,7 @@ void frag_gemm(const GemmDesc& g, int ksplit, hipStream_t s) {
   FragTile t;
   RTCC3_CHECK(frag_gemm_plan(g, d, t), "frag: bad product");
   d.ksplit = ksplit;
+  d.split = Divisor(ksplit);
   d.mode = g.atomic || ksplit > 1 ? 2 : g.store ? 1 : 0;
   if (t.ib == 2)
     t.kw == 1 ? launch_frag_gemm<2, 2, 1>(d, g.batch, t.two, s) : launch_frag_gemm<2, 2, 4>(d, g.batch, t.two, s);
