@@ -51,6 +51,8 @@ CCSDResult ccsd_forward(Engine& e, const Dims& d, const cplx* y, const View& h, 
   View t2 = e.tensor("t2", {o, o, v, v});
   e.copy(t1.p, y, ov);
   e.copy(t2.p, y + ov, oovv);
+  Engine::Queue queued(e);
+  e.start_queue();
   e.set_requires_grad(t1.buf, want_grad);
   e.set_requires_grad(t2.buf, want_grad);
   if (want_grad) e.tape_begin();
@@ -111,6 +113,8 @@ CCSDResult ccsd_forward(Engine& e, const Dims& d, const cplx* y, const View& h, 
 
 void ccsd_residual(Engine& e, const Dims& d, CCSDResult& r) {
   const int64_t o = d.o, v = d.v, n = d.n;
+  Engine::Queue queued(e);
+  e.start_queue();
   const bool want_grad = e.requires_grad(e.tensor("t1", {o, v}).buf);
   if (want_grad) e.tape_resume();
   auto fresh = [&](const char* name, std::vector<int64_t> shape) { return fresh_view(e, name, shape); };
@@ -192,6 +196,8 @@ void ccsd_backward(Engine& e, const Dims& d, const cplx* y, const View& ones_o, 
   e.zero_grads();
   View gR1 = e.grad(r.R1), gR2 = e.grad(r.R2);
   e.copy(gR1.p, y + ov + oovv, ov);
+  Engine::Queue queued(e);
+  e.start_queue();
   View l2 = Engine::raw(const_cast<cplx*>(y) + 2 * ov + oovv, {o, o, v, v});
   e.axpy(R(0.5), l2, gR2);
   e.axpy(ONE, ones_o, Engine::diag(blk(e.grad(r.F), 'o', 'o'), 0, 1));

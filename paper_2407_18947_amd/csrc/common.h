@@ -164,6 +164,7 @@ Tuner* tuner_new();
 int tuner_records(const Tuner* t, TuneRecord* out, int cap);
 void tuner_delete(Tuner* t);
 void tuner_set_tuning(Tuner* t, bool on);
+bool tuning_now();  // whether gemm() times its products on this thread
 void tuner_clear(Tuner* t);
 // products tuned, and how many of them run with a split other than the heuristic's
 void tuner_counts(const Tuner* t, int& sites, int& changed);
@@ -186,6 +187,11 @@ struct AxpyDesc {
   int store;  // Y = alpha X without reading Y
 };
 void axpy_strided(const AxpyDesc& d, hipStream_t s);
+// axpys that do not depend on each other, small ones in launches of up to twelve
+void axpy_group(const AxpyDesc* d, int n, hipStream_t s);
+// Products that do not depend on each other: small FP64 ones whose k is not to
+// be split share launches, the others run one by one as by gemm().
+void gemm_group(const GemmDesc* g, int n, hipStream_t s);
 
 void fill(cplx* p, int64_t n, cplx val, hipStream_t s);
 // Several buffers zeroed by one launch (per kMaxZero of them).

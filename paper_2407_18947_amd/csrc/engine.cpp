@@ -63,6 +63,85 @@ cplx* Engine::twin_out(const cplx* p) {
   return t + off;
 }
 
+void Engine::start_queue() {
+  queue_.clear();
+  // tuning times its products one by one; twins are cleared as they go
+  queueing_ = !tuning_now() && !tangent_;
+}
+
+Engine::Reach Engine::reach_of(const View& v) {
+  int64_t m = 0;
+  for (int k = 0; k < v.nd; ++k) m += (v.sh[k] - 1) * v.st[k];
+  return Reach{v.p, v.p + m + 1};
+}
+
+Engine::Queued& Engine::enqueue(int kind, Reach r0, Reach r1, Reach w) {
+  auto meet = [](const Reach& a, const Reach& b) { return a.lo < b.hi && b.lo < a.hi; };
+  int level = 0;
+  for (const Queued& q : queue_)
+    if (q.level >= level && (meet(q.wr, r0) || meet(q.wr, r1) || meet(q.wr, w) || meet(q.rd[0], w) || meet(q.rd[1], w)))
+      level = q.level + 1;
+  queue_.emplace_back();
+  Queued& q = queue_.back();
+  q.kind = kind;
+  q.level = level;
+  q.rd[0] = r0;
+  q.rd[1] = r1;
+  q.wr = w;
+  return q;
+}
+
+void Engine::run_gemm(const GemmDesc& g, const View& A, const View& B, const View& C) {
+  if (!queueing_) return gemm(g, stream);
+  Reach w = reach_of(C);
+  if (g.fresh) w = Reach{g.fresh_p, g.fresh_p + g.fresh_n};
+  enqueue(0, reach_of(A), reach_of(B), w).g = g;
+}
+
+void Engine::run_axpy(const AxpyDesc& d, const View& X, const View& Y) {
+  if (!queueing_) return axpy_strided(d, stream);
+  enqueue(1, reach_of(X), reach_of(X), reach_of(Y)).a = d;
+}
+
+void Engine::run_clear(cplx* p, int64_t n) {
+  if (!queueing_) return fill(p, n, cplx{0, 0}, stream);
+  const Reach none{nullptr, nullptr};
+  Queued& q = enqueue(2, none, none, Reach{p, p + n});
+  q.p = p;
+  q.n = n;
+}
+
+void Engine::flush() {
+  if (queue_.empty()) return;
+  int last = 0;
+  for (const Queued& q : queue_) last = std::max(last, q.level);
+  std::vector<GemmDesc> g;
+  std::vector<AxpyDesc> a;
+  for (int l = 0; l <= last; ++l) {
+    g.clear();
+    a.clear();
+    ZeroList z;
+    z.count = 0;
+    for (const Queued& q : queue_) {
+      if (q.level != l) continue;
+      if (q.kind == 0) g.push_back(q.g);
+      if (q.kind == 1) a.push_back(q.a);
+      if (q.kind == 2) {
+        z.p[z.count] = q.p;
+        z.n[z.count++] = q.n;
+        if (z.count == ZeroList::kMaxZero) {
+          zero_many(z, stream);
+          z.count = 0;
+        }
+      }
+    }
+    if (z.count > 0) zero_many(z, stream);
+    axpy_group(a.data(), (int)a.size(), stream);
+    gemm_group(g.data(), (int)g.size(), stream);
+  }
+  queue_.clear();
+}
+
 bool* Engine::due(const cplx* p, const Range** r) {
   if (ndue_ == 0) return nullptr;
   int64_t off = 0;
@@ -80,7 +159,7 @@ void Engine::touch(const cplx* p) {
   *f = false;
   --ndue_;
   const Buf& b = bufs_[r->buf];
-  fill(r->kind == 0 ? b.p : b.g, b.n, cplx{0, 0}, stream);
+  run_clear(r->kind == 0 ? b.p : b.g, b.n);
 }
 
 bool Engine::claim(const View& v) {
@@ -121,6 +200,8 @@ void Engine::zero_later(const View& v) {
 }
 
 void Engine::settle() {
+  flush();
+  queueing_ = false;
   if (ndue_ == 0) return;
   ZeroList z;
   z.count = 0;
@@ -142,6 +223,7 @@ void Engine::settle() {
 }
 
 void Engine::copy(cplx* dst, const cplx* src, int64_t n) {
+  flush();
   touch(src);
   const Range* rd = nullptr;
   if (bool* f = due(dst, &rd)) {
@@ -152,6 +234,7 @@ void Engine::copy(cplx* dst, const cplx* src, int64_t n) {
       touch(dst);
     }
   }
+  flush();
   rtcc3::copy(dst, src, n, stream);
   if (!tangent_) return;
   const cplx* st = twin(src);
@@ -193,6 +276,7 @@ int Engine::buffer(const std::string& name, int64_t n) {
 void Engine::release(const std::string& name) {
   auto it = names_.find(name);
   if (it == names_.end()) return;
+  flush();
   RTCC3_HIP(hipStreamSynchronize(stream));
   Buf& b = bufs_[it->second];
   if (b.p) ranges_.erase(b.p);
@@ -254,6 +338,7 @@ void Engine::zero(const View& v) {
   }
   RTCC3_CHECK(contiguous, "engine: zero() needs a contiguous view");
   (void)claim(v);  // cleared here if that is due
+  flush();
   fill(v.p, v.numel(), cplx{0, 0}, stream);
   if (!twins_) return;
   int64_t off = 0;
@@ -272,6 +357,7 @@ void Engine::zero_buffer(int buf) {
     b.p_due = false;
     --ndue_;
   }
+  flush();
   fill(b.p, b.n, cplx{0, 0}, stream);
   if (b.tp_nz) fill(b.tp, b.n, cplx{0, 0}, stream);
   b.tp_nz = false;
@@ -322,6 +408,7 @@ cplx* Engine::scratch(int64_t n, hipStream_t on) {
     sc = &scratch_.back();
   }
   if (n > sc->n) {
+    flush();  // queued work may use the old one
     if (sealed_) throw Error(-4, "engine: scratch grown after the context was set up");
     // work on any stream may still read the old scratch
     RTCC3_HIP(hipDeviceSynchronize());
@@ -401,7 +488,7 @@ void Engine::axpy_exec(cplx alpha, const View& X, const View& Y) {
   d.alpha = alpha;
   touch(X.p);
   d.store = claim(Y);
-  axpy_strided(d, stream);
+  run_axpy(d, X, Y);
 }
 
 void Engine::einsum_dual(const std::string& spec, cplx alpha, const View& A, const View& B, const View& C) {
@@ -655,7 +742,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       d.Y = t.p;
       d.alpha = cplx{1, 0};
       d.store = 1;
-      axpy_strided(d, stream);
+      run_axpy(d, src, t);
       A = t;
       oa.idx = gb + gm + gk;
       changed = true;
@@ -680,7 +767,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       d.Y = t.p;
       d.alpha = cplx{1, 0};
       d.store = 1;
-      axpy_strided(d, stream);
+      run_axpy(d, src, t);
       B = t;
       ob.idx = gb + gk + gn;
       changed = true;
@@ -758,7 +845,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     g.fresh_p = C0.p;
     g.fresh_n = C0.numel();
   }
-  gemm(g, stream);
+  run_gemm(g, A, B, C);
   if (copyC) {
     // scatter the temp result into the real output
     std::vector<int> perm;
@@ -775,7 +862,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     d.Y = Cfinal.p;
     d.alpha = cplx{1, 0};
     d.store = fresh;
-    axpy_strided(d, stream);
+    run_axpy(d, src, Cfinal);
   }
 }
 

@@ -57,6 +57,23 @@ class Engine {
   // ends with it.
   void zero_later(const View& v);
   void settle();
+  // From here to settle() the operations (einsum, axpy and the clearing before
+  // them) are queued, and run by settle() in levels: an operation goes to the
+  // first level after those it depends on (memory it reads or writes that they
+  // write, memory it writes that they read), and the small operations of a
+  // level share launches.  Nothing else may use the engine's buffers meanwhile.
+  // What is queued when the returned object goes (an exception) is dropped.
+  struct Queue {
+    Engine& e;
+    explicit Queue(Engine& x) : e(x) {}
+    Queue(const Queue&) = delete;
+    Queue& operator=(const Queue&) = delete;
+    ~Queue() {
+      e.queue_.clear();
+      e.queueing_ = false;
+    }
+  };
+  void start_queue();
   cplx* data(int buf) { return bufs_[buf].p; }
   int64_t size(int buf) { return bufs_[buf].n; }
 
@@ -135,6 +152,26 @@ class Engine {
   const Range* find(const cplx* p, int64_t* off) const;
   cplx* alloc_twin(int64_t n);
   int ndue_ = 0;  // buffers and gradients to be cleared
+  struct Reach {  // elements [lo, hi) that an operation may touch
+    const cplx *lo, *hi;
+  };
+  struct Queued {
+    int kind;  // 0 product, 1 axpy, 2 clearing
+    int level;
+    GemmDesc g;
+    AxpyDesc a;
+    cplx* p;
+    int64_t n;
+    Reach rd[2], wr;
+  };
+  bool queueing_ = false;
+  std::vector<Queued> queue_;
+  static Reach reach_of(const View& v);
+  Queued& enqueue(int kind, Reach r0, Reach r1, Reach w);
+  void run_gemm(const GemmDesc& g, const View& A, const View& B, const View& C);
+  void run_axpy(const AxpyDesc& d, const View& X, const View& Y);
+  void run_clear(cplx* p, int64_t n);
+  void flush();
   bool* due(const cplx* p, const Range** r);
   void touch(const cplx* p);   // clears the buffer of p if that is due
   bool claim(const View& v);   // the same, or, if v is all of it, leaves it to the caller: true

@@ -94,5 +94,9 @@ int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v);
 bool frag_gemm_fits(const GemmDesc& g);
 int frag_gemm_split(const GemmDesc& g);
 void frag_gemm(const GemmDesc& g, int ksplit, hipStream_t s);
+// Products of one 16 x 16 block a workgroup (frag_gemm_small), k not split over
+// workgroups, that do not depend on each other, in launches of up to eight.
+bool frag_gemm_small(const GemmDesc& g);
+void frag_gemm_group(const GemmDesc* g, int n, hipStream_t s);
 
 }  // namespace rtcc3

@@ -783,11 +783,10 @@ struct FragGemm {
 // element of C is loaded before the product and indexes are divided by
 // multiplications: o=5, v=18 0.67 -> 0.56 ms.
 template <int IB, int JB, int KW, int TAIL>
-__global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) void frag_gemm_kernel(FragGemm d) {
+__device__ __forceinline__ void frag_gemm_tile(const FragGemm& d, const int g, d2v* red) {
   constexpr int R = IB * JB > 1 || KW > 4 ? 4 : 6;  // steps in flight
   const int lane = threadIdx.x & 63, l16 = lane & 15, kl = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int g = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
   const int ge = d.per.quot(g), t = g - ge * (int)d.per.d;
   const int e = d.split.quot(ge), ks = ge - e * (int)d.split.d;
   const int slow = d.fast.quot(t), fast = t - slow * (int)d.fast.d;
@@ -933,7 +932,6 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
           if (m < d.M && n < d.N) put(m, n, acc.value(i, j, r));
         }
   } else {
-    __shared__ d2v red[KW * IB * JB * 256];
 #pragma unroll
     for (int i = 0; i < IB; ++i)
 #pragma unroll
@@ -964,6 +962,37 @@ __global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) voi
       if (m < d.M && n < d.N) put(m, n, z);
     }
   }
+}
+
+template <int IB, int JB, int KW, int TAIL>
+__global__ __launch_bounds__((KW == 1 ? 4 : KW) * 64, (IB * JB > 1 ? 2 : 4)) void frag_gemm_kernel(FragGemm d) {
+  __shared__ d2v red[KW == 1 ? 1 : KW * IB * JB * 256];
+  frag_gemm_tile<IB, JB, KW, TAIL>(d, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), red);
+}
+
+// Several small products that do not depend on each other in one launch, one
+// block of 16 x 16 a workgroup and its k split over eight waves.  A launch of a
+// small product is 4 to 8 us of latency whatever its size.
+constexpr int kGroup = 8;
+struct FragGroup {
+  FragGemm g[kGroup];
+  int end[kGroup];   // workgroups up to and with product i
+  int tail[kGroup];  // TAIL of its tile
+  int n;
+};
+static_assert(sizeof(FragGroup) <= 4096, "kernel arguments");
+__global__ __launch_bounds__(512, 4) void frag_group_kernel(FragGroup d) {
+  __shared__ d2v red[8 * 256];
+  int i = 0;
+  while (i + 1 < d.n && (int)blockIdx.x >= d.end[i]) ++i;
+  const FragGemm& g = d.g[i];
+  const int x = (int)blockIdx.x - (i > 0 ? d.end[i - 1] : 0);
+  if (d.tail[i] < 0)
+    frag_gemm_tile<1, 1, 8, -1>(g, x, red);
+  else if (d.tail[i] > 0)
+    frag_gemm_tile<1, 1, 8, 1>(g, x, red);
+  else
+    frag_gemm_tile<1, 1, 8, 0>(g, x, red);
 }
 
 template <int IB, int JB, int KW>
@@ -1237,6 +1266,34 @@ void frag_gemm(const GemmDesc& g, int ksplit, hipStream_t s) {
     launch_frag_gemm<1, 1, 8>(d, g.batch, t.two, s);
   else
     launch_frag_gemm<1, 1, 16>(d, g.batch, t.two, s);
+}
+
+bool frag_gemm_small(const GemmDesc& g) {
+  FragGemm d;
+  FragTile t;
+  // (with the eight waves that a group gives to each)
+  return frag_gemm_plan(g, d, t) && t.ib * t.jb == 1 && d.steps <= 512 && (int64_t)d.gm * d.gn * g.batch < (1 << 20);
+}
+
+void frag_gemm_group(const GemmDesc* g, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += kGroup) {
+    FragGroup d;
+    d.n = std::min(kGroup, n - i0);
+    int wg = 0;
+    for (int i = 0; i < d.n; ++i) {
+      FragTile t;
+      const GemmDesc& q = g[i0 + i];
+      RTCC3_CHECK(frag_gemm_plan(q, d.g[i], t) && t.ib * t.jb == 1, "frag: not a small product");
+      d.g[i].ksplit = 1;
+      d.g[i].split = Divisor(1);
+      d.g[i].mode = q.atomic ? 2 : q.store ? 1 : 0;
+      d.tail[i] = !t.two ? -1 : (d.g[i].K0 & 3) != 0;
+      wg += d.g[i].gm * d.g[i].gn * q.batch;
+      d.end[i] = wg;
+    }
+    hipLaunchKernelGGL(frag_group_kernel, dim3((unsigned)wg), dim3(512), 0, s, d);
+    RTCC3_HIP(hipGetLastError());
+  }
 }
 
 int64_t frag_cols_pack(const int* rows, int njob, int o, int v) {

@@ -1069,9 +1069,8 @@ __global__ __launch_bounds__(NT, CMB == 2 ? 2 : 3) void zgemm_kb_f64_kernel(Gemm
 
 // Y = alpha X (+ Y) over up to 8 index runs; INT the type indexes are formed in.
 template <typename INT>
-__global__ void axpy_kernel(AxpyDesc d, int64_t total) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
+__device__ __forceinline__ void axpy_range(const AxpyDesc& d, int64_t first, int64_t step, int64_t total) {
+  for (int64_t e = first; e < total; e += step) {
     INT r = (INT)e;
     int64_t ox = 0, oy = 0;
     for (int k = d.nd - 1; k > 0; --k) {
@@ -1088,6 +1087,25 @@ __global__ void axpy_kernel(AxpyDesc d, int64_t total) {
     y.im += d.alpha.re * x.im + d.alpha.im * x.re;
     d.Y[oy] = y;
   }
+}
+template <typename INT>
+__global__ void axpy_kernel(AxpyDesc d, int64_t total) {
+  axpy_range<INT>(d, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x, total);
+}
+constexpr int kAxpyGroup = 12;
+struct AxpyGroup {
+  AxpyDesc d[kAxpyGroup];
+  uint32_t total[kAxpyGroup];
+  int end[kAxpyGroup];  // workgroups up to and with axpy i
+  int n;
+};
+static_assert(sizeof(AxpyGroup) <= 4096, "kernel arguments");
+__global__ void axpy_group_kernel(AxpyGroup d) {
+  int i = 0;
+  while (i + 1 < d.n && (int)blockIdx.x >= d.end[i]) ++i;
+  const int b0 = i > 0 ? d.end[i - 1] : 0;
+  axpy_range<uint32_t>(d.d[i], (int64_t)((int)blockIdx.x - b0) * blockDim.x + threadIdx.x,
+                       (int64_t)(d.end[i] - b0) * blockDim.x, d.total[i]);
 }
 
 __global__ void zero_many_kernel(ZeroList z) {
@@ -1408,6 +1426,7 @@ void tuner_delete(Tuner* t) {
   delete t;
 }
 void tuner_set_tuning(Tuner* t, bool on) { t->tuning = on; }
+bool tuning_now() { return g_tuner && g_tuner->tuning; }
 void tuner_clear(Tuner* t) {
   t->best.clear();
   t->heur.clear();
@@ -1619,9 +1638,11 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
   launch(ksplit);
 }
 
-void axpy_strided(const AxpyDesc& d_in, hipStream_t s) {
-  // index runs that are contiguous in both operands count as one
-  AxpyDesc d = d_in;
+namespace {
+// Index runs that are contiguous in both operands counted as one; returns the
+// number of elements.
+int64_t axpy_runs(const AxpyDesc& d_in, AxpyDesc& d) {
+  d = d_in;
   d.nd = 0;
   int64_t total = 1;
   for (int k = 0; k < d_in.nd; ++k) {
@@ -1638,17 +1659,79 @@ void axpy_strided(const AxpyDesc& d_in, hipStream_t s) {
       ++d.nd;
     }
   }
-  if (total <= 0) return;
   if (d.nd == 0) {
     d.nd = 1;
     d.shape[0] = 1;
     d.sx[0] = d.sy[0] = 0;
   }
+  return total;
+}
+}  // namespace
+
+void axpy_strided(const AxpyDesc& d_in, hipStream_t s) {
+  AxpyDesc d;
+  const int64_t total = axpy_runs(d_in, d);
+  if (total <= 0) return;
   if (total < (1LL << 32))
     hipLaunchKernelGGL(axpy_kernel<uint32_t>, dim3(grid_for(total, 256)), dim3(256), 0, s, d, total);
   else
     hipLaunchKernelGGL(axpy_kernel<int64_t>, dim3(grid_for(total, 256)), dim3(256), 0, s, d, total);
   RTCC3_HIP(hipGetLastError());
+}
+
+void axpy_group(const AxpyDesc* a, int n, hipStream_t s) {
+  AxpyGroup g;
+  g.n = 0;
+  auto launch = [&]() {
+    if (g.n == 0) return;
+    hipLaunchKernelGGL(axpy_group_kernel, dim3((unsigned)g.end[g.n - 1]), dim3(256), 0, s, g);
+    RTCC3_HIP(hipGetLastError());
+    g.n = 0;
+  };
+  for (int i = 0; i < n; ++i) {
+    AxpyDesc d;
+    const int64_t total = axpy_runs(a[i], d);
+    if (total <= 0) continue;
+    if (n == 1 || total > (1 << 20)) {
+      axpy_strided(a[i], s);
+      continue;
+    }
+    g.d[g.n] = d;
+    g.total[g.n] = (uint32_t)total;
+    g.end[g.n] = (g.n > 0 ? g.end[g.n - 1] : 0) + (int)grid_for(total, 256);
+    if (++g.n == kAxpyGroup) launch();
+  }
+  launch();
+}
+
+void gemm_group(const GemmDesc* g, int n, hipStream_t s) {
+  std::vector<GemmDesc> small;
+  for (int i = 0; i < n; ++i) {
+    const GemmDesc& d = g[i];
+    bool in = n > 1 && d.prec == RTCC3_PREC_FP64 && d.M > 0 && d.N > 0 && d.K > 0 && d.batch > 0 && frag_gemm_small(d);
+    if (in) {
+      // the split that gemm() would take (it forms the key of the product as it runs it)
+      GemmDesc x = d.M <= 16 && d.N > 16 ? transposed(d) : d;
+      int ks = frag_gemm_split(x);
+      if (g_tuner) {
+        auto it = g_tuner->best.find(desc_key(x));
+        if (it != g_tuner->best.end()) ks = it->second;
+      }
+      in = ks == 1 && !(d.fresh && d.atomic);
+    }
+    if (!in) {
+      gemm(d, s);
+      continue;
+    }
+    small.push_back(d);
+    if (d.fresh) small.back().store = 1;
+  }
+  // one by itself in the kernel of its own shape (5.3 us against 6.2)
+  if (small.size() == 1) {
+    gemm(small[0], s);
+  } else if (!small.empty()) {
+    frag_gemm_group(small.data(), (int)small.size(), s);
+  }
 }
 
 void zero_many(const ZeroList& z, hipStream_t s) {

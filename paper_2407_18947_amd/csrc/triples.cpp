@@ -1558,6 +1558,8 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
     if (nrev_ + 2 > (int)rev_.size()) fold_timing();
     RTCC3_HIP(hipEventRecord(rev_[nrev_++], s));
   }
+  Engine::Queue queued(e);
+  e.start_queue();
   blocks(e, r);
   beside_ = beside ? &beside : nullptr;
   side_done_ = nullptr;
@@ -1589,6 +1591,7 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   // stream's own scratch): they need not wait for the work beside
   if (ready) RTCC3_HIP(hipStreamWaitEvent(s, ready, 0));
   // ---- final contractions of the Y1 intermediates
+  e.start_queue();
   View Y1 = e.tensor("tr_Y1", {o, v});
   View l2 = Engine::raw(const_cast<cplx*>(y) + 2 * ov + oovv, {o, o, v, v});
   View Lov = e.tensor("Lov", {o, v, o, v});
