@@ -1,5 +1,7 @@
 #include "engine.h"
 
+#include "frag_kernels.h"
+
 #include <algorithm>
 #include <cstring>
 
@@ -75,16 +77,24 @@ Engine::Reach Engine::reach_of(const View& v) {
   return Reach{v.p, v.p + m + 1};
 }
 
-Engine::Queued& Engine::enqueue(int kind, Reach r0, Reach r1, Reach w) {
-  auto meet = [](const Reach& a, const Reach& b) { return a.lo < b.hi && b.lo < a.hi; };
+namespace {
+template <class R>
+bool meet(const R& a, const R& b) {
+  return a.lo < b.hi && b.lo < a.hi;
+}
+}  // namespace
+
+Engine::Queued& Engine::enqueue(int kind, bool adds, Reach r0, Reach r1, Reach w) {
   int level = 0;
   for (const Queued& q : queue_)
-    if (q.level >= level && (meet(q.wr, r0) || meet(q.wr, r1) || meet(q.wr, w) || meet(q.rd[0], w) || meet(q.rd[1], w)))
+    if (q.level >= level && (meet(q.wr, r0) || meet(q.wr, r1) || (meet(q.wr, w) && !(adds && q.adds)) ||
+                             meet(q.rd[0], w) || meet(q.rd[1], w)))
       level = q.level + 1;
   queue_.emplace_back();
   Queued& q = queue_.back();
   q.kind = kind;
   q.level = level;
+  q.adds = adds;
   q.rd[0] = r0;
   q.rd[1] = r1;
   q.wr = w;
@@ -95,18 +105,19 @@ void Engine::run_gemm(const GemmDesc& g, const View& A, const View& B, const Vie
   if (!queueing_) return gemm(g, stream);
   Reach w = reach_of(C);
   if (g.fresh) w = Reach{g.fresh_p, g.fresh_p + g.fresh_n};
-  enqueue(0, reach_of(A), reach_of(B), w).g = g;
+  const bool adds = !g.fresh && g.prec == RTCC3_PREC_FP64 && frag_gemm_small(g);
+  enqueue(0, adds, reach_of(A), reach_of(B), w).g = g;
 }
 
 void Engine::run_axpy(const AxpyDesc& d, const View& X, const View& Y) {
   if (!queueing_) return axpy_strided(d, stream);
-  enqueue(1, reach_of(X), reach_of(X), reach_of(Y)).a = d;
+  enqueue(1, false, reach_of(X), reach_of(X), reach_of(Y)).a = d;
 }
 
 void Engine::run_clear(cplx* p, int64_t n) {
   if (!queueing_) return fill(p, n, cplx{0, 0}, stream);
   const Reach none{nullptr, nullptr};
-  Queued& q = enqueue(2, none, none, Reach{p, p + n});
+  Queued& q = enqueue(2, false, none, none, Reach{p, p + n});
   q.p = p;
   q.n = n;
 }
@@ -124,7 +135,11 @@ void Engine::flush() {
     z.count = 0;
     for (const Queued& q : queue_) {
       if (q.level != l) continue;
-      if (q.kind == 0) g.push_back(q.g);
+      if (q.kind == 0) {
+        g.push_back(q.g);
+        for (const Queued& x : queue_)
+          if (&x != &q && x.level == l && x.adds && q.adds && meet(x.wr, q.wr)) g.back().atomic = 1;
+      }
       if (q.kind == 1) a.push_back(q.a);
       if (q.kind == 2) {
         z.p[z.count] = q.p;

@@ -61,7 +61,8 @@ class Engine {
   // them) are queued, and run by settle() in levels: an operation goes to the
   // first level after those it depends on (memory it reads or writes that they
   // write, memory it writes that they read), and the small operations of a
-  // level share launches.  Nothing else may use the engine's buffers meanwhile.
+  // level share launches.  Small FP64 products that add to the same output may
+  // share a level and add atomically.  Nothing else may use the engine's buffers meanwhile.
   // What is queued when the returned object goes (an exception) is dropped.
   struct Queue {
     Engine& e;
@@ -158,6 +159,7 @@ class Engine {
   struct Queued {
     int kind;  // 0 product, 1 axpy, 2 clearing
     int level;
+    bool adds;  // a small product that adds to its output
     GemmDesc g;
     AxpyDesc a;
     cplx* p;
@@ -167,7 +169,7 @@ class Engine {
   bool queueing_ = false;
   std::vector<Queued> queue_;
   static Reach reach_of(const View& v);
-  Queued& enqueue(int kind, Reach r0, Reach r1, Reach w);
+  Queued& enqueue(int kind, bool adds, Reach r0, Reach r1, Reach w);
   void run_gemm(const GemmDesc& g, const View& A, const View& B, const View& C);
   void run_axpy(const AxpyDesc& d, const View& X, const View& Y);
   void run_clear(cplx* p, int64_t n);

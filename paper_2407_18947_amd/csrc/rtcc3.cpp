@@ -164,6 +164,8 @@ void rhs_impl(rtcc3_ctx* c, FieldRef E, const cplx* y, cplx* dy, const TermsOut&
     e.zero(Engine::raw(dy, {c->ylen}));
     View dt1 = sub(dy, 0, {o, v}), dt2 = sub(dy, ov, {o, o, v, v});
     View dl1 = sub(dy, ov + oovv, {o, v}), dl2 = sub(dy, 2 * ov + oovv, {o, o, v, v});
+    Engine::Queue queued(e);
+    e.start_queue();
     e.axpy(C(0, -1), r.R1, dt1);
     e.axpy(C(0, -1), r.R2, dt2);
     e.axpy(C(0, 1), r.G1, dl1);
@@ -176,6 +178,7 @@ void rhs_impl(rtcc3_ctx* c, FieldRef E, const cplx* y, cplx* dy, const TermsOut&
       e.axpy(C(0, 1), to.Y1, dl1);
       e.axpy(C(0, 1), to.Y2, dl2);
     }
+    e.settle();
   }
 
   if (want_density) {
