@@ -1,6 +1,6 @@
-// Generic kernels: batched complex GEMM on the matrix cores (FP64 MFMA with
-// the complex product as three real products, FP32 MFMA with four), strided
-// axpy/permute, fill.
+// Generic kernels: batched complex GEMM on the matrix cores (FP32 MFMA with the
+// complex product as four real products, bf16 slices; FP64 with three for what
+// frag_kernels.hip does not take), strided axpy/permute, fill.
 #include <algorithm>
 #include <type_traits>
 #include <unordered_map>
@@ -851,222 +851,6 @@ __global__ __launch_bounds__(NT) void zgemm_split_kernel(GemmDesc d, int ksplit,
         put<ATOMIC>(d, C, ro[i][r], co[j], (double)crr[i][j][r] - (double)cii[i][j][r], (double)cim[i][j][r]);
 }
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-constexpr int kOOB = 0x7ffffff0;  // beyond every resource (host-checked spans stay below 2^31 bytes)
-constexpr int kRsrcWord3 = 0x00020000;
-
-// The element at byte offset voff of resource r if ok, else zero (read beyond
-// the resource).  The empty asm keeps the offset select a select: the compiler
-// would otherwise branch around a load per element.
-__device__ __forceinline__ cplx buf_load_cplx(__amdgpu_buffer_rsrc_t r, bool ok, int voff) {
-  int o = ok ? voff : kOOB;
-  asm volatile("" : "+v"(o));
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
-  cplx x;
-  __builtin_memcpy(&x, &v, sizeof(x));
-  return x;
-}
-
-// ---------------------------------------------------------------------------
-// FP64 product with both operands read k-fast (A[m][k] and B[k][n] contiguous in
-// k), plain or with B one permuted block (CMB = 4) or a combination of three
-// permuted blocks (CMB = 2): buffer resources over the batch entry's operands,
-// 32-bit offsets, elements outside the product read as zero beyond the
-// resource, the three-product planes formed at the LDS store.  A thread loads the four A rows and the
-// BN/16 B columns of one k per step; a 64-wide tile has four waves of 32 x 32,
-// a 16-wide one four waves of 16 x 16 stacked along M.
-// ---------------------------------------------------------------------------
-// Three workgroups per CU (168 registers a wave); two for the combined operand,
-// whose three loaded blocks per element need more.
-template <bool ATOMIC, int BN, int CMB>
-__global__ __launch_bounds__(NT, CMB == 2 ? 2 : 3) void zgemm_kb_f64_kernel(GemmDesc d, int ksplit, int kchunk) {
-  constexpr int BK = 16, NB = BN / 16;  // B columns per thread
-  constexpr int WM = BN == 64 ? 32 : 16, WN = BN == 64 ? 32 : 16, IB = WM / 16, JB = WN / 16;
-  constexpr int NX = CMB == 2 ? 3 : 1;  // blocks combined into B
-  __shared__ double sA[3][BK][BM + 1];
-  __shared__ double sB[3][BK][BN + 1];
-
-  const int tilesN = (d.N + BN - 1) / BN;
-  // The entries of a combined operand read blocks that the neighbouring
-  // entries (the other orderings of the same occupied triple) read too: those
-  // run on one XCD (at o=15, v=57 the X2 product's L2 misses drop from 50 to
-  // 17.5 GB per launch).
-  int bx = blockIdx.x;
-  int64_t b = (int64_t)blockIdx.y + (int64_t)blockIdx.z * gridDim.y;
-  if constexpr (CMB == 2) {
-    const int64_t nyz = (int64_t)gridDim.y * gridDim.z;
-    const int64_t lg = xcd_contiguous((int64_t)blockIdx.x + (int64_t)gridDim.x * b, (int64_t)gridDim.x * nyz);
-    bx = (int)(lg % gridDim.x);
-    b = lg / gridDim.x;
-  }
-  const int kz = bx % ksplit, tile = bx / ksplit;
-  const int tm = tile / tilesN, tn = tile % tilesN;
-  if (b >= d.batch) return;
-  const int kbeg = kz * kchunk, kend = min(d.K, kbeg + kchunk);
-  if (kbeg >= kend) return;
-
-  const cplx *pa, *pb[NX];
-  cplx* C;
-  double wc[NX];
-  if (d.bl) {
-    const int I = d.bl[4 * b], J = d.bl[4 * b + 1], K = d.bl[4 * b + 2], n = d.bl[4 * b + 3];
-    C = d.C + d.cC[0] * I + d.cC[1] * J + d.cC[2] * K + d.cC[3] * n;
-    pa = d.A + d.cA[0] * I + d.cA[1] * J + d.cA[2] * K + d.cA[3] * n;
-    if constexpr (CMB == 0) {
-      pb[0] = d.B + d.cB[0] * I + d.cB[1] * J + d.cB[2] * K + d.cB[3] * n;
-      wc[0] = 1.0;
-    } else {
-#pragma unroll
-      for (int x = 0; x < NX; ++x) {
-        pb[x] = d.B + (int64_t)d.part[6 * n + d.comb_perm[x]] * d.comb_stride;
-        wc[x] = CMB == 2 ? d.comb_w[x] : 1.0;
-      }
-    }
-  } else {
-    C = d.C + b * d.sCb;
-    pa = d.A + b * d.sAb;
-    pb[0] = d.B + b * d.sBb;
-    wc[0] = 1.0;
-  }
-  // operand spans in elements (host-checked below 2^27)
-  const int spanA = (int)((d.M / d.M0 - 1) * d.sAm1 + (d.M0 - 1) * d.sAm0 + (d.K / d.K0 - 1) * d.sAk1 +
-                          (d.K0 - 1) * d.sAk0 + 1);
-  const int spanB = (int)((d.K / d.K0 - 1) * d.sBk1 + (d.K0 - 1) * d.sBk0 + (d.N / d.N0 - 1) * d.sBn1 +
-                          (d.N0 - 1) * d.sBn0 + 1);
-  const __amdgpu_buffer_rsrc_t ra =
-      __builtin_amdgcn_make_buffer_rsrc((void*)pa, 0, spanA * (int)sizeof(cplx), kRsrcWord3);
-  __amdgpu_buffer_rsrc_t rb[NX];
-#pragma unroll
-  for (int x = 0; x < NX; ++x)
-    rb[x] = __builtin_amdgcn_make_buffer_rsrc((void*)pb[x], 0, spanB * (int)sizeof(cplx), kRsrcWord3);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = BN == 64 ? (wave >> 1) * WM : wave * WM, wn = BN == 64 ? (wave & 1) * WN : 0;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int kt = tid & 15, rt = tid >> 4;  // the thread's k, and its first row / column
-  int aoff[4], boff[NB];
-  bool aok[4], bok[NB];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int m = m0 + rt + 16 * r;
-    aok[r] = m < d.M;
-    aoff[r] = aok[r] ? (int)((m / d.M0) * d.sAm1 + (m % d.M0) * d.sAm0) : 0;
-  }
-#pragma unroll
-  for (int r = 0; r < NB; ++r) {
-    const int nn = n0 + rt + 16 * r;
-    bok[r] = nn < d.N;
-    boff[r] = bok[r] ? (int)((nn / d.N0) * d.sBn1 + (nn % d.N0) * d.sBn0) : 0;
-  }
-  const float invK0 = 1.0f / (float)d.K0;
-
-  cplx av[4], bv[NB][NX];
-  auto load = [&](int k0) {
-    const int k = k0 + kt;
-    int q, r;
-    split_k(k, d.K0, invK0, q, r);
-    const bool kok = k < kend;
-    const int koa = (int)(q * d.sAk1 + r * d.sAk0), kob = (int)(q * d.sBk1 + r * d.sBk0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) av[t] = buf_load_cplx(ra, kok & aok[t], (aoff[t] + koa) * (int)sizeof(cplx));
-#pragma unroll
-    for (int t = 0; t < NB; ++t)
-#pragma unroll
-      for (int x = 0; x < NX; ++x)
-        bv[t][x] = buf_load_cplx(rb[x], kok & bok[t], (boff[t] + kob) * (int)sizeof(cplx));
-  };
-  auto stash = [&]() {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int m = rt + 16 * t;
-      const double re = av[t].re, im = av[t].im;
-      sA[0][kt][m] = re;
-      sA[1][kt][m] = im;
-      sA[2][kt][m] = re + im;
-    }
-#pragma unroll
-    for (int t = 0; t < NB; ++t) {
-      double re = bv[t][0].re, im = bv[t][0].im;
-      if constexpr (NX > 1) {
-        re = wc[0] * re;
-        im = wc[0] * im;
-#pragma unroll
-        for (int x = 1; x < NX; ++x) {
-          re += wc[x] * bv[t][x].re;
-          im += wc[x] * bv[t][x].im;
-        }
-      }
-      const int nn = rt + 16 * t;
-      sB[0][kt][nn] = re;
-      sB[1][kt][nn] = im - re;
-      sB[2][kt][nn] = re + im;
-    }
-  };
-
-  d4 c1[IB][JB], c2[IB][JB], c3[IB][JB];
-#pragma unroll
-  for (int i = 0; i < IB; ++i)
-#pragma unroll
-    for (int j = 0; j < JB; ++j) c1[i][j] = c2[i][j] = c3[i][j] = d4{0, 0, 0, 0};
-
-  const int nsteps = (kend - kbeg + BK - 1) / BK;
-  load(kbeg);
-  stash();
-  __syncthreads();
-  for (int it = 0; it < nsteps; ++it) {
-    load(kbeg + (it + 1) * BK);  // in flight during the MFMAs (masked after the last step)
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      const int kr = kk + (lane >> 4), c16 = lane & 15;
-      double ar[IB], ai[IB], sa[IB], br[JB], db[JB], sb[JB];
-#pragma unroll
-      for (int i = 0; i < IB; ++i) {
-        ar[i] = sA[0][kr][wm + 16 * i + c16];
-        ai[i] = sA[1][kr][wm + 16 * i + c16];
-        sa[i] = sA[2][kr][wm + 16 * i + c16];
-      }
-#pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        br[j] = sB[0][kr][wn + 16 * j + c16];
-        db[j] = sB[1][kr][wn + 16 * j + c16];
-        sb[j] = sB[2][kr][wn + 16 * j + c16];
-      }
-#pragma unroll
-      for (int i = 0; i < IB; ++i)
-#pragma unroll
-        for (int j = 0; j < JB; ++j) c1[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[i], br[j], c1[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < IB; ++i)
-#pragma unroll
-        for (int j = 0; j < JB; ++j) c2[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i], db[j], c2[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < IB; ++i)
-#pragma unroll
-        for (int j = 0; j < JB; ++j) c3[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[i], sb[j], c3[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-    stash();
-    __syncthreads();
-  }
-
-  int64_t co[JB], ro[IB][4];
-#pragma unroll
-  for (int j = 0; j < JB; ++j) co[j] = c_off(n0 + wn + 16 * j + (lane & 15), d.N, d.N0, d.sCn1, d.sCn0);
-#pragma unroll
-  for (int i = 0; i < IB; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) ro[i][r] = c_off(m0 + wm + 16 * i + Frag<double>::row(lane, r), d.M, d.M0, d.sCm1, d.sCm0);
-#pragma unroll
-  for (int i = 0; i < IB; ++i)
-#pragma unroll
-    for (int j = 0; j < JB; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const double p1 = c1[i][j][r];
-        put<ATOMIC>(d, C, ro[i][r], co[j], p1 - c3[i][j][r], p1 + c2[i][j][r]);
-      }
-}
-
 // Y = alpha X (+ Y) over up to 8 index runs; INT the type indexes are formed in.
 template <typename INT>
 __device__ __forceinline__ void axpy_range(const AxpyDesc& d, int64_t first, int64_t step, int64_t total) {
@@ -1217,10 +1001,10 @@ void launch_one(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit, int kch
     hipLaunchKernelGGL((zgemm_split_kernel<ATOMIC, KFA, NFB, BN, SEG, 2>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
 }
 
-// Combined-operand products (A k-fast, B k-fast), FP64 or FP32.
-template <int MODE, bool ATOMIC, int BN>
+// Combined-operand products (A k-fast, B k-fast), FP32.
+template <bool ATOMIC, int BN>
 void launch_comb_gemm(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit, int kchunk) {
-  typedef typename std::conditional<MODE == RTCC3_PREC_FP64, double, float>::type T;
+  typedef float T;
   if (d.comb_n == 1)
     hipLaunchKernelGGL((zgemm_kernel<T, ATOMIC, true, false, BN, false, 4>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
   else if (d.comb_on == 0)
@@ -1255,59 +1039,26 @@ void launch_gather_gemm(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit,
   }
 }
 
-// Products the k-fast FP64 kernel takes: both operands contiguous in k, no
-// gathered K, column or K segments, and operand spans within its 32-bit offsets.
-bool kb_f64_fits(const GemmDesc& d, bool kfa, bool nfb) {
-  if (!kfa || nfb || d.gk_start || d.ncs || d.nseg) return false;
-  if (!(d.comb_n == 0 || d.comb_n == 1 || (d.comb_n == 3 && d.comb_on == 1))) return false;
-  if (d.M % d.M0 || d.N % d.N0 || d.K % d.K0) return false;
-  const int64_t spanA = (d.M / d.M0 - 1) * d.sAm1 + (d.M0 - 1) * d.sAm0 + (d.K / d.K0 - 1) * d.sAk1 + (d.K0 - 1) * d.sAk0;
-  const int64_t spanB = (d.K / d.K0 - 1) * d.sBk1 + (d.K0 - 1) * d.sBk0 + (d.N / d.N0 - 1) * d.sBn1 + (d.N0 - 1) * d.sBn0;
-  // k is read up to K + 15 before it is masked: keep those offsets below 2^27 elements as well
-  const int64_t over = 16 * (d.sAk1 + d.sAk0 + d.sBk1 + d.sBk0);
-  return spanA >= 0 && spanB >= 0 && spanA + over < (1LL << 27) && spanB + over < (1LL << 27);
-}
-
 template <int MODE, bool ATOMIC>
 void launch_layout(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit, int kchunk, bool kfa, bool nfb, int bn) {
-  if constexpr (MODE == RTCC3_PREC_FP64) {
-    if (kb_f64_fits(d, kfa, nfb)) {
-      const int cmb = d.comb_n == 0 ? 0 : d.comb_n == 1 ? 4 : 2;
-      if (bn == 16) {
-        if (cmb == 0)
-          hipLaunchKernelGGL((zgemm_kb_f64_kernel<ATOMIC, 16, 0>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
-        else if (cmb == 4)
-          hipLaunchKernelGGL((zgemm_kb_f64_kernel<ATOMIC, 16, 4>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
-        else
-          hipLaunchKernelGGL((zgemm_kb_f64_kernel<ATOMIC, 16, 2>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
-      } else {
-        if (cmb == 0)
-          hipLaunchKernelGGL((zgemm_kb_f64_kernel<ATOMIC, 64, 0>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
-        else if (cmb == 4)
-          hipLaunchKernelGGL((zgemm_kb_f64_kernel<ATOMIC, 64, 4>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
-        else
-          hipLaunchKernelGGL((zgemm_kb_f64_kernel<ATOMIC, 64, 2>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
-      }
-      return;
-    }
-  }
   if (d.ncs > 0) {
-    if constexpr (ATOMIC && (MODE == RTCC3_PREC_FP64 || MODE == RTCC3_PREC_FP32)) {
-      typedef typename std::conditional<MODE == RTCC3_PREC_FP64, double, float>::type T;
-      hipLaunchKernelGGL((zgemm_kernel<T, true, true, false, 64, false, 5>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
+    if constexpr (ATOMIC && MODE == RTCC3_PREC_FP32) {
+      hipLaunchKernelGGL((zgemm_kernel<float, true, true, false, 64, false, 5>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
     } else {
-      RTCC3_CHECK(false, "gemm: column segments run in FP64 or FP32 with atomics");
+      RTCC3_CHECK(false, "gemm: column segments run in FP32 with atomics");
     }
     return;
   }
   if (d.gk_start) {
     if (MODE == RTCC3_PREC_FP64 || MODE == RTCC3_PREC_FP32) launch_gather_gemm<MODE, ATOMIC>(d, grid, s, ksplit, kchunk, kfa, nfb, bn);
   } else if (d.comb_n > 0) {
-    if (MODE == RTCC3_PREC_FP64 || MODE == RTCC3_PREC_FP32) {
+    if constexpr (MODE == RTCC3_PREC_FP32) {
       if (bn == 16)
-        launch_comb_gemm<MODE, ATOMIC, 16>(d, grid, s, ksplit, kchunk);
+        launch_comb_gemm<ATOMIC, 16>(d, grid, s, ksplit, kchunk);
       else
-        launch_comb_gemm<MODE, ATOMIC, 64>(d, grid, s, ksplit, kchunk);
+        launch_comb_gemm<ATOMIC, 64>(d, grid, s, ksplit, kchunk);
+    } else {
+      RTCC3_CHECK(false, "gemm: combined operands run in FP32");
     }
   } else if (d.nseg > 0)
     launch_one<MODE, ATOMIC, true, true, 64, true>(d, grid, s, ksplit, kchunk);
@@ -1452,15 +1203,13 @@ TunerScope::~TunerScope() { g_tuner = prev; }
 
 void gemm(const GemmDesc& d_in, hipStream_t s) {
   // A bf16-split run takes the split kernel for its segmented products only.
-  // Its other products run in FP32, except two forms whose FP64 kernels are
-  // faster than the FP32 ones on gfx950 (alone at o=15, v=57: the operand
-  // combined from three blocks 6.9 against 7.8 ms, the 16-wide gathered
-  // products 1.95 against 2.51 ms); those run in FP64, which is also more
+  // Its other products run in FP32, except the 16-wide gathered ones, whose FP64
+  // kernel was the faster one (1.95 against 2.51 ms at o=15, v=57) and is more
   // accurate.
   GemmDesc dsel = d_in;
   if ((dsel.prec == RTCC3_PREC_BF16X3 || dsel.prec == RTCC3_PREC_BF16X2) &&
       !((dsel.nseg > 0 || dsel.force_prec) && !dsel.comb_n && !dsel.gk_start && !dsel.ncs))
-    dsel.prec = (dsel.comb_n == 3 || (dsel.gk_start && dsel.N <= 16)) ? RTCC3_PREC_FP64 : RTCC3_PREC_FP32;
+    dsel.prec = dsel.gk_start && dsel.N <= 16 ? RTCC3_PREC_FP64 : RTCC3_PREC_FP32;
   const GemmDesc& d0 = dsel;
   if (d0.M <= 0 || d0.N <= 0 || d0.batch <= 0) return;
   if (d0.K <= 0) return;
@@ -1554,6 +1303,9 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
   // FP32, which is at least as accurate.
   const bool split = d.prec == RTCC3_PREC_BF16X3 || d.prec == RTCC3_PREC_BF16X2;
   const int prec = split && ((d.nseg == 0 && !d.force_prec) || d.comb_n || d.gk_start || d.ncs) ? RTCC3_PREC_FP32 : d.prec;
+  // Plain FP64 products go to the fragment kernel wherever its 32-bit offsets
+  // reach (o=15, v=57: 110 products of a right-hand side 8.2 ms through LDS tiles,
+  // 6.1 from fragments; o=5, v=18: 2.0 and 0.6).
   const bool frag = prec == RTCC3_PREC_FP64 && frag_gemm_fits(d);
   if (frag) ksplit = frag_gemm_split(d);
   auto launch = [&](int ks, bool trial = false) {

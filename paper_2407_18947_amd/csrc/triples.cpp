@@ -1135,10 +1135,10 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     cplx* Zi = P("tr_Zi", {o, v, v, v});
     const int64_t lR = (int64_t)o * o * v * o;
 
-    // X1, the f~ term of X2 and Z34 (terms 3 and 4 of Y1): with o <= 15 they ride
-    // along with products that read the block anyway (tail columns of the Y1
-    // product below; the f~ term inside tb_X2c); else one sweep per block
-    // (in FP64 with any o)
+    // X1, the f~ term of X2 and Z34 (terms 3 and 4 of Y1): in FP64, else with
+    // o <= 15, they ride along with products that read the block anyway (traces or
+    // tail columns of the Y1 product below; the f~ term inside tb_X2c); else one
+    // sweep per block
     const bool tails = o <= 15 || pr == RTCC3_PREC_FP64;
     // the 16-wide gathered products in FP64 (the split precisions too)
     const bool frag16 = pr == RTCC3_PREC_FP64 || (pr != RTCC3_PREC_FP32 && o <= 16);
