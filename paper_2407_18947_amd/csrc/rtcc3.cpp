@@ -136,7 +136,7 @@ void rhs_impl(rtcc3_ctx* c, FieldRef E, const cplx* y, cplx* dy, const TermsOut&
   if (with_triples) {
     // the reverse sweep needs only the CCSD forward part and residual: it runs
     // on the side stream after the residual, beside the triples work
-    to = c->tri->run(e, d, r, y, want_density, [&](hipEvent_t after) -> hipEvent_t {
+    to = c->tri->run(e, d, r, y, want_density, dy || t.terms, [&](hipEvent_t after) -> hipEvent_t {
       // With bf16 slices the builds are not bound by the matrix cores and the
       // sweep starts as soon as the residual is done, beside them; with FP64
       // or FP32 products it waits for the lambda3 build, so that the builds

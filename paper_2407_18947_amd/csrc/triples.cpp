@@ -883,6 +883,7 @@ void Triples::blocks(Engine& e, const CCSDResult& r) {
   t = make("tb_LD", {o, v, o, o});  // -(2(ia|jl) - (il|ja)) at [i][a][j][l]
   e.einsum("Pia,Pjl->iajl", R(-2), B('o', 'v'), B('o', 'o'), t);
   e.einsum("Pil,Pja->iajl", ONE, B('o', 'o'), B('o', 'v'), t);
+  if (!amps_) return;  // the rest serves X1, X2, Y1 and Y2 only
   t = make("tb_X2a", {o, v, v, v});  // (ac|ke) at [k][a][c][e]
   e.einsum("Pac,Pke->kace", ONE, B('v', 'v'), B('o', 'v'), t);
   t = make("tb_X2b", {o, o, o, v});  // (ki|mc) at [k][m][i][c]
@@ -1168,7 +1169,9 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     };
     // X2: sum_ce Z1[b][(c,e)] (ac|ke)~ into X2p[I][J][a][b].  In FP64 (the bf16 splits run it in FP64 too) with b
     // contiguous: T_JIK[b][c][e] = T_IKJ[c][e][b], T_KIJ[b][c][e] = T_IJK[c][e][b], T_JKI[b][c][e] = T_KIJ[c][e][b].
-    if (pr != RTCC3_PREC_FP32) {
+    if (!amps_) {
+      // not wanted
+    } else if (pr != RTCC3_PREC_FP32) {
       const int perm[3] = {2, 0, 4};
       prod_frag_cols(e, {{gX2a, v3, v2, v, X2p, {(int64_t)o * v2, v2}, v, 1}}, &lOVVV, &oovv, T, winlen, perm, 3, o, v, vp,
                      w, w.cols_t3, s);
@@ -1202,7 +1205,9 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     //      T_IJK G[K][I] stays.
     // In FP64 both read the block as T_KIJ[c][(a,b)], once for the two.  (The
     // bf16 splits run these in FP64 too, up to o = 16.)
-    if (frag16) {
+    if (!amps_) {
+      // not wanted
+    } else if (frag16) {
       const int64_t oov = (int64_t)o * o * v, ovl = (int64_t)o * v, ov2 = (int64_t)o * v2;
       const std::vector<FragJob> jobs = {{gX2c, {oov, ovl, 0}, v, ovl, o, X2p, {0, 0, v2}, ov2, 1.0},
                                          {gX2b, {0, oov, ovl}, v, ovl, o, X2p, {v2, 0, 0}, ov2, 1.0}};
@@ -1244,9 +1249,11 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     if (pr == RTCC3_PREC_FP64) {
       const int perm[1] = {2};
       const int64_t lA[2] = {lOVVV, t2len}, lC[2] = {oovv, lR};
-      prod_frag_cols(e, {{gY2a, v3, v2, v, Y2p, {(int64_t)o * v2, v2}, v, 1},
-                         {t2, v2, (int64_t)o * v2, o, R8, {(int64_t)o * v * o, (int64_t)v * o}, 1, o}},
-                     lA, lC, L, winlen, perm, 1, o, v, vp, w, w.cols_l3, s2);
+      std::vector<ColsJob> jobs = {{gY2a, v3, v2, v, Y2p, {(int64_t)o * v2, v2}, v, 1},
+                                   {t2, v2, (int64_t)o * v2, o, R8, {(int64_t)o * v * o, (int64_t)v * o}, 1, o}};
+      const int skip = amps_ ? 0 : 1;
+      jobs.erase(jobs.begin(), jobs.begin() + skip);
+      prod_frag_cols(e, jobs, lA + skip, lC + skip, L, winlen, perm, 1, o, v, vp, w, w.cols_l3, s2);
     } else {  // lambda_IJK[d][b][e] = lambda_JIK[b][d][e], read with (d,e) contiguous
       GemmDesc g = base(v, v, (int)v2, cn, cbl, pr);
       g.atomic = 1;
@@ -1280,7 +1287,9 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     const FragJob jZ{t2, {v2, 0, ov2l}, v, v2, v, Zi, {0, v3, 0}, v2, 1.0};
     // the first reads the block as lambda_KIJ[d][(a,b)]
     const FragJob jY{gY2b, {(int64_t)o * v, (int64_t)o * o * v, 0}, v, ov, o, Y2p, {0, 0, v2}, ov2l, -1.0};
-    if (pr == RTCC3_PREC_FP64) {
+    if (!amps_) {
+      // not wanted
+    } else if (pr == RTCC3_PREC_FP64) {
       const int64_t lA[2] = {t2len, lOOOV}, lC[2] = {lOVVV, oovv};
       prod_frag_gather(e, {jZ, jY}, lA, lC, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
     } else if (frag16) {
@@ -1389,15 +1398,22 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       // L_JbKc = (tb_G5)[J][K][b][c].  In FP64 they are the columns x = K and x = I of
       // term 5 and x = J and x = I of term 6; else columns of their own.
       if (pr == RTCC3_PREC_FP64) {  // t_IJK[b][(c,d)] = t_JKI[c][d][b]
-        const std::vector<BlockCols> groups = {
+        std::vector<BlockCols> groups = {
             {gG1, 0, ov2, v2, R15, {0, ovo, vo}, o, 1, 1.0},    // term 1: (xc|Id)
             {gG5, 1, ov2, v2, R15, {vo, 0, ovo}, o, 1, -1.0},   // term 5: L_Ibxc
             {l2, 0, v2, ov2, R2t, {0, ovo, vo}, o, 1, 1.0},     // term 2: l2[x][I]
             {l2, 2, v2, ov2, R6, {ovo, vo, 0}, o, 1, 1.0}};     // term 6: l2[x][K]
-        const std::vector<BlockTrace> traces = {
+        std::vector<BlockTrace> traces = {
             {1, 2, 0, X1, v, 1.0}, {1, 0, 2, X1, v, -1.0}, {3, 1, 0, Z34, v, 1.0}, {3, 0, 1, Z34, v, -1.0}};
         const int64_t lB[4] = {lOOVV, lOOVV, l2len, l2len}, lC[4] = {lR, lR, lR, lR}, lT[4] = {ov, ov, ov, ov};
-        prod_frag_block(e, groups, traces, o, lB, lC, lT, T, winlen, 5, v, vp, w, pairwin ? w.owned : w.bl, cbl, s);
+        int first = 0;
+        if (!amps_) {  // only Z34, from term 6
+          first = 3;
+          groups.erase(groups.begin(), groups.begin() + 3);
+          traces.erase(traces.begin(), traces.begin() + 2);
+          for (BlockTrace& t : traces) t.group = 0;
+        }
+        prod_frag_block(e, groups, traces, o, lB + first, lC + first, lT, T, winlen, 5, v, vp, w, pairwin ? w.owned : w.bl, cbl, s);
       } else {
         GemmDesc::ColSeg c1 = cseg(gG1, {ov2, 0, 0, 0}, 1, v2, R15, {0, ovo, vo, 0}, o, 1, 1.0);   // term 1: (xc|Id)
         GemmDesc::ColSeg c5 = cseg(gG5, {0, ov2, 0, 0}, 1, v2, R15, {vo, 0, ovo, 0}, o, 1, -1.0);  // term 5: L_Ibxc
@@ -1550,7 +1566,11 @@ void Triples::build_event(hipStream_t s) {
 }
 
 TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cplx* y, bool want_density,
-                        const Beside& beside, hipEvent_t ready) {
+                        bool want_amplitudes, const Beside& beside, hipEvent_t ready) {
+  // A dipole by itself needs t3, lambda3, the sum R8 of terms 7, 8 and 12 of Y1
+  // and terms 3 and 4 of it, not X2, Y2, Z_i and the other intermediates (o=10,
+  // v=38: 5.7 ms with them).
+  amps_ = want_amplitudes || !want_density || prec_ != RTCC3_PREC_FP64;
   const int64_t o = d.o, v = d.v;
   const int64_t ov = o * v, oovv = o * o * v * v;
   hipStream_t s = e.stream;
@@ -1600,35 +1620,41 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
   View g_voov = e.tensor("g_voov", {v, o, o, v});
   View g_vvvv = e.tensor("g_vvvv", {v, v, v, v});
   View g_oooo = e.tensor("g_oooo", {o, o, o, o});
-  e.einsum("klbx,klab->xa", ONE, e.tensor("tr_R15", {o, o, v, o}), l2, Y1);
-  e.einsum("klbx,kalb->xa", ONE, e.tensor("tr_R2", {o, o, v, o}), g_ovov, Y1);
-  e.einsum("jkbx,kajb->xa", R(-1), e.tensor("tr_R6", {o, o, v, o}), Lov, Y1);
-  e.einsum("xajb,jb->xa", ONE, Lov, e.tensor("tr_Z34", {o, v}), Y1);
-  e.einsum("lidj,jlda->ia", R(-1), e.tensor("tr_R8", {o, o, v, o}), g_oovv, Y1);
-  e.einsum("ildj,dlja->ia", R(-1), e.tensor("tr_R8", {o, o, v, o}), g_voov, Y1);
-  e.einsum("ibde,daeb->ia", ONE, e.tensor("tr_Zi", {o, v, v, v}), g_vvvv, Y1);
-  if (prec_ == RTCC3_PREC_FP64) {
-    e.einsum("lbad,ildb->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_oovv, Y1);
-    e.einsum("lbda,dlib->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_voov, Y1);
-  } else {  // the relayout space of these two, for a later switch to FP64
-    (void)e.scratch(o * v * v * v + oovv + ov);
+  if (amps_) {
+    e.einsum("klbx,klab->xa", ONE, e.tensor("tr_R15", {o, o, v, o}), l2, Y1);
+    e.einsum("klbx,kalb->xa", ONE, e.tensor("tr_R2", {o, o, v, o}), g_ovov, Y1);
+    e.einsum("jkbx,kajb->xa", R(-1), e.tensor("tr_R6", {o, o, v, o}), Lov, Y1);
+    e.einsum("xajb,jb->xa", ONE, Lov, e.tensor("tr_Z34", {o, v}), Y1);
+    e.einsum("lidj,jlda->ia", R(-1), e.tensor("tr_R8", {o, o, v, o}), g_oovv, Y1);
+    e.einsum("ildj,dlja->ia", R(-1), e.tensor("tr_R8", {o, o, v, o}), g_voov, Y1);
+    e.einsum("ibde,daeb->ia", ONE, e.tensor("tr_Zi", {o, v, v, v}), g_vvvv, Y1);
+    if (prec_ == RTCC3_PREC_FP64) {
+      e.einsum("lbad,ildb->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_oovv, Y1);
+      e.einsum("lbda,dlib->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_voov, Y1);
+    } else {  // the relayout space of these two, for a later switch to FP64
+      (void)e.scratch(o * v * v * v + oovv + ov);
+    }
+    e.einsum("xljm,mlaj->xa", ONE, g_oooo, e.tensor("tr_R8", {o, o, v, o}), Y1);
   }
-  e.einsum("xljm,mlaj->xa", ONE, g_oooo, e.tensor("tr_R8", {o, o, v, o}), Y1);
 
   TriplesOut out;
   out.X1 = e.tensor("tr_X1", {o, v});
   out.Y1 = Y1;
   // P_ij^ab symmetrisation of X2 and Y2
   View X2 = e.tensor("tr_X2", {o, o, v, v});
-  e.zero_later(X2);
-  View X2p = e.tensor("tr_X2p", {o, o, v, v});
-  e.axpy(ONE, X2p, X2);
-  e.axpy(ONE, Engine::permute(X2p, {1, 0, 3, 2}), X2);
+  if (amps_) {
+    e.zero_later(X2);
+    View X2p = e.tensor("tr_X2p", {o, o, v, v});
+    e.axpy(ONE, X2p, X2);
+    e.axpy(ONE, Engine::permute(X2p, {1, 0, 3, 2}), X2);
+  }
   View Y2 = e.tensor("tr_Y2", {o, o, v, v});
-  e.zero_later(Y2);
-  View Y2p = e.tensor("tr_Y2p", {o, o, v, v});
-  e.axpy(ONE, Y2p, Y2);
-  e.axpy(ONE, Engine::permute(Y2p, {1, 0, 3, 2}), Y2);
+  if (amps_) {
+    e.zero_later(Y2);
+    View Y2p = e.tensor("tr_Y2p", {o, o, v, v});
+    e.axpy(ONE, Y2p, Y2);
+    e.axpy(ONE, Engine::permute(Y2p, {1, 0, 3, 2}), Y2);
+  }
   out.X2 = X2;
   out.Y2 = Y2;
 

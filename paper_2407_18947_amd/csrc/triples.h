@@ -96,8 +96,10 @@ class Triples {
   // does not wait for it.  ready (optional): an event after which the integral
   // blocks of the CCSD residual that the final contractions read are complete.
   typedef std::function<hipEvent_t(hipEvent_t)> Beside;
+  // want_amplitudes: whether X1, X2, Y1 and Y2 are wanted (else only the density
+  // terms; in the reduced precisions both are formed).
   TriplesOut run(Engine& e, const Dims& d, const CCSDResult& r, const cplx* y, bool want_density,
-                 const Beside& beside = nullptr, hipEvent_t ready = nullptr);
+                 bool want_amplitudes, const Beside& beside = nullptr, hipEvent_t ready = nullptr);
   hipEvent_t side_done() const { return side_done_; }
   void set_precision(int p) { prec_ = p; }
   // All work on the caller's stream, one kernel after another (for timing
@@ -170,6 +172,7 @@ class Triples {
   void build_windows();
   void upload(Window& w);
   void free_windows();
+  bool amps_ = true;  // the current run's want_amplitudes
   void blocks(Engine& e, const CCSDResult& r);
   void window_pass(Engine& e, const Window& w, const cplx* y, bool density_terms);
 };
