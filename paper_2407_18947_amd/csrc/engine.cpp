@@ -67,8 +67,7 @@ cplx* Engine::twin_out(const cplx* p) {
 
 void Engine::start_queue() {
   queue_.clear();
-  // tuning times its products one by one; twins are cleared as they go
-  queueing_ = !tuning_now() && !tangent_;
+  queueing_ = !tuning_now();  // tuning times its products one by one
 }
 
 Engine::Reach Engine::reach_of(const View& v) {
@@ -210,7 +209,7 @@ void Engine::zero_later(const View& v) {
   if (!f) ++ndue_;
   f = true;
   bool& nz = r->kind == 0 ? b.tp_nz : b.tg_nz;
-  if (nz) fill(r->kind == 0 ? b.tp : b.tg, b.n, cplx{0, 0}, stream);
+  if (nz) run_clear(r->kind == 0 ? b.tp : b.tg, b.n);
   nz = false;
 }
 
@@ -462,6 +461,7 @@ void Engine::tape_begin() {
 
 // The gradients' clearing waits for their first use, as in zero_later().
 void Engine::zero_grads() {
+  flush();
   for (auto& b : bufs_)
     if (b.rg && b.g) {
       if (!b.g_due) ++ndue_;
