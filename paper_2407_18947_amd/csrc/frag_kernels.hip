@@ -301,7 +301,10 @@ __device__ __forceinline__ void gather_unit(const FragGather& d, const FragUnit&
   // soon as its step is done, with the block's step D further on or, past its
   // end, with the next block's step that belongs into the slot: one load with
   // scalar selects, so that it never waits.  Rows c >= v of B lie beyond the
-  // block's resource and read as zero; A is masked there.
+  // block's resource and read as zero; A is masked there.  The scalar
+  // offset has to begin inside the resource (the range check takes it off
+  // the size without a sign), so it is always that of a step of the block: where
+  // a block has fewer than D, the slots without one hold the last.
   constexpr int D = 4;
   const int ns = (v + 3) >> 2, rest = v & 3;
   d2v a[D][IB], b[D][JB];
@@ -321,7 +324,7 @@ __device__ __forceinline__ void gather_unit(const FragGather& d, const FragUnit&
   };
   block(p0, pa, pb);
 #pragma unroll
-  for (int u = 0; u < D; ++u) load(u, pa, pb, u);
+  for (int u = 0; u < D; ++u) load(u, pa, pb, min(u, ns - 1));
   for (int p = p0; p < p1; ++p) {
     const bool last = p + 1 == p1;
     const int q = last ? p : p + 1;

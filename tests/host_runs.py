@@ -1,0 +1,52 @@
+"""What the tests of the library's CPU build run, each in its own process:
+python host_runs.py LIBRARY FUNCTION ARGUMENTS."""
+import ctypes
+import os
+import sys
+
+import numpy as np
+
+sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+from paper_2407_18947_amd import _lib  # noqa: E402
+from paper_2407_18947_amd.inputs import make_system, random_state  # noqa: E402
+
+FIELD = np.array([0.01, -0.02, 0.03])
+
+
+def device(a):
+    """A copy of an array in an allocation of its own."""
+    a = np.ascontiguousarray(a, dtype=np.complex128)
+    L = _lib.load()
+    L.emu_alloc.restype, L.emu_alloc.argtypes = ctypes.c_void_p, [ctypes.c_size_t]
+    b = np.frombuffer((ctypes.c_char * a.nbytes).from_address(L.emu_alloc(a.nbytes)), dtype=np.complex128)
+    b = b.reshape(a.shape)
+    b[...] = a
+    return b
+
+
+def evaluate(o, v, precision, blocks, tol):
+    """Terms and right-hand side against the oracle, to tol of a term's largest element."""
+    from oracle import rtcc3 as orc
+    o, v, precision, blocks, tol = int(o), int(v), int(precision), int(blocks), float(tol)
+    s = make_system(o, v, seed=51)
+    y = random_state(o, v, 9)
+    ctx = _lib.Context(s, precision)
+    if blocks:
+        ctx.set_option(_lib.RTCC3_OPT_WINDOW_BLOCKS, blocks)
+    yd, td, dy = device(y), device(np.zeros(ctx.terms_size())), device(np.zeros(y.size))
+    _lib.rtcc3_rhs_terms(ctx.ctx, FIELD, yd, td, 1)
+    got = ctx.split_terms(td)
+    _lib.rtcc3_rhs(ctx.ctx, FIELD, yd, dy)
+    ctx.close()
+    ref = orc.rhs_terms(orc.Model.from_system(s), y, FIELD, triples="explicit")
+    for k in ["R1", "R2", "G1", "G2", "X1", "X2", "Y1", "Y2", "D", "mu"]:
+        b = ref[k].numpy()
+        assert np.abs(got[k] - b).max() <= tol * np.abs(b).max() + 1e-15, (k, np.abs(got[k] - b).max())
+    full = np.concatenate([x.ravel() for x in (-1j * (got["R1"] + got["X1"]), -1j * (got["R2"] + got["X2"]),
+                                               1j * (got["G1"] + got["Y1"]), 1j * (got["G2"] + got["Y2"]))])
+    assert np.abs(dy - full).max() <= tol * np.abs(full).max() + 1e-15
+
+
+if __name__ == "__main__":
+    _lib.LIBPATH = sys.argv[1]
+    globals()[sys.argv[2]](*sys.argv[3:])
