@@ -165,7 +165,7 @@ struct FragSeg {
 template <bool ATOMIC>
 __global__ __launch_bounds__(256, 3) void frag_seg_kernel(FragSeg d) {
   constexpr int IB = 2, JB = 2;
-  __shared__ unsigned ebase[kFragRun];  // first element of the entry's block in C
+  __shared__ int64_t ebase[kFragRun];   // first element of the entry's block in C
   __shared__ int eoff[4][kFragRun];     // byte offset of the entry's A operand from the run's first, per segment
   const int lg = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
   const int4 rt = d.rt[lg / d.ncol];
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(256, 3) void frag_seg_kernel(FragSeg d) {
   const int tid = threadIdx.x;
   if (tid < rt.y) {
     const int dI = e0[4 * tid] - I0, dJ = e0[4 * tid + 1] - J0, dK = e0[4 * tid + 2] - K0;
-    ebase[tid] = (unsigned)(e0[4 * tid + 3] * d.vb);
+    ebase[tid] = e0[4 * tid + 3] * d.vb;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
       if (s < d.nseg) {
@@ -228,12 +228,12 @@ __global__ __launch_bounds__(256, 3) void frag_seg_kernel(FragSeg d) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       if (m < rows) {
-        const unsigned el = ebase[e] + off;
+        cplx* c = d.C + ebase[e];
 #pragma unroll
         for (int j = 0; j < JB; ++j)
           if (cok[j]) {
             const d2v z = acc.value(i, j, r);
-            cplx* p = d.C + (uint64_t)(el + co[j]);
+            cplx* p = c + (off + co[j]);
             if (ATOMIC) {
               unsafeAtomicAdd(&p->re, z[0]);
               unsafeAtomicAdd(&p->im, z[1]);

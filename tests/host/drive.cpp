@@ -1,0 +1,82 @@
+// Entry points of the CPU build for tests of single kernels and host functions.
+#include <cmath>
+#include <random>
+#include <vector>
+
+#include "common.h"
+#include "frag_kernels.h"
+
+using namespace rtcc3;
+
+namespace {
+
+template <class T>
+T* device(size_t n) {
+  T* p = nullptr;
+  RTCC3_HIP(hipMalloc(&p, n * sizeof(T)));
+  return p;
+}
+template <class T>
+T* device(const std::vector<T>& x) {
+  T* p = device<T>(x.size());
+  std::memcpy(p, x.data(), x.size() * sizeof(T));
+  return p;
+}
+std::vector<cplx> random(size_t n, unsigned seed) {
+  std::mt19937 g(seed);
+  std::normal_distribution<double> d;
+  std::vector<cplx> x(n);
+  for (auto& z : x) z = cplx{d(g), d(g)};
+  return x;
+}
+void add(cplx& s, cplx a, cplx b) {
+  s.re += a.re * b.re - a.im * b.im;
+  s.im += a.re * b.im + a.im * b.re;
+}
+
+}  // namespace
+
+// One block of a segmented product at window slot `slot`: the largest error of
+// the block, in place of which nothing else is written.
+extern "C" double drive_seg_slot(int v, int slot) {
+  const int vp = (v + 7) / 8 * 8, len = 5;
+  const int64_t va = (int64_t)v * vp, vb = va * v;
+  const std::vector<cplx> A = random((size_t)v * len, 1), B = random((size_t)len * v * v, 2);
+  cplx* C = device<cplx>((slot + 1) * vb);
+  GemmDesc g;
+  std::memset(&g, 0, sizeof(g));
+  g.M = g.M0 = g.N0 = v;
+  g.N = v * v;
+  g.K = g.K0 = len;
+  g.batch = 1;
+  g.bl = device<int>({0, 0, 0, slot});
+  g.alpha = cplx{1, 0};
+  g.store = 1;
+  g.nseg = 1;
+  g.seg[0].len = len;
+  g.seg[0].A = device(A);
+  g.seg[0].sAm = len;
+  g.seg[0].sAk = 1;
+  g.seg[0].B = device(B);
+  g.seg[0].sBk = v * v;
+  g.seg[0].sBn = 1;
+  g.C = C;
+  g.sCm0 = va;
+  g.sCn1 = vp;
+  g.sCn0 = 1;
+  g.cC[3] = vb;
+  const int nt = (v + kFragRows - 1) / kFragRows;
+  std::vector<int> rt;
+  for (int t = 0; t < nt; ++t) rt.insert(rt.end(), {0, 1, 0, nt});
+  frag_seg(g, device(rt), nt, nullptr);
+  double err = 0;
+  for (int a = 0; a < v; ++a)
+    for (int n = 0; n < v * v; ++n) {
+      cplx s{0, 0};
+      for (int k = 0; k < len; ++k) add(s, A[a * len + k], B[k * v * v + n]);
+      const cplx c = C[slot * vb + a * va + n / v * vp + n % v];
+      err = std::max(err, std::hypot(c.re - s.re, c.im - s.im));
+    }
+  RTCC3_HIP(hipFree(C));
+  return err;
+}

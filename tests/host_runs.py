@@ -47,6 +47,15 @@ def evaluate(o, v, precision, blocks, tol):
     assert np.abs(dy - full).max() <= tol * np.abs(full).max() + 1e-15
 
 
+def seg_slot(v, slot):
+    """A block of a segmented product far up in the window."""
+    f = _lib.load().drive_seg_slot
+    f.restype = ctypes.c_double
+    err = f(int(v), int(slot))
+    # five terms of order one per element
+    assert err <= 1e-13, err
+
+
 if __name__ == "__main__":
     _lib.LIBPATH = sys.argv[1]
     globals()[sys.argv[2]](*sys.argv[3:])
