@@ -156,6 +156,17 @@ void Engine::flush() {
   queue_.clear();
 }
 
+void Engine::drop_queue() {
+  for (const Queued& q : queue_)
+    if (q.kind == 2)
+      for (Buf& b : bufs_) {
+        b.tp_nz = b.tp_nz || b.tp == q.p;
+        b.tg_nz = b.tg_nz || b.tg == q.p;
+      }
+  queue_.clear();
+  queueing_ = false;
+}
+
 bool* Engine::due(const cplx* p, const Range** r) {
   if (ndue_ == 0) return nullptr;
   int64_t off = 0;

@@ -63,16 +63,14 @@ class Engine {
   // write, memory it writes that they read), and the small operations of a
   // level share launches.  Small FP64 products that add to the same output may
   // share a level and add atomically.  Nothing else may use the engine's buffers meanwhile.
-  // What is queued when the returned object goes (an exception) is dropped.
+  // What is queued when the returned object goes (an exception) is dropped, and
+  // the derivatives that it would have cleared count as written again.
   struct Queue {
     Engine& e;
     explicit Queue(Engine& x) : e(x) {}
     Queue(const Queue&) = delete;
     Queue& operator=(const Queue&) = delete;
-    ~Queue() {
-      e.queue_.clear();
-      e.queueing_ = false;
-    }
+    ~Queue() { e.drop_queue(); }
   };
   void start_queue();
   cplx* data(int buf) { return bufs_[buf].p; }
@@ -174,6 +172,7 @@ class Engine {
   void run_axpy(const AxpyDesc& d, const View& X, const View& Y);
   void run_clear(cplx* p, int64_t n);
   void flush();
+  void drop_queue();
   bool* due(const cplx* p, const Range** r);
   void touch(const cplx* p);   // clears the buffer of p if that is due
   bool claim(const View& v);   // the same, or, if v is all of it, leaves it to the caller: true

@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "common.h"
+#include "engine.h"
 #include "frag_kernels.h"
 
 using namespace rtcc3;
@@ -78,5 +79,39 @@ extern "C" double drive_seg_slot(int v, int slot) {
       err = std::max(err, std::hypot(c.re - s.re, c.im - s.im));
     }
   RTCC3_HIP(hipFree(C));
+  return err;
+}
+
+// A derivative evaluation that ends in an error while its clearing is queued,
+// then another one: how far the derivative is from alpha x'.
+extern "C" double drive_dropped_queue(int of_gradient) {
+  Engine e(nullptr);
+  const int64_t n = 6;
+  View x = e.tensor("x", {n}), y = e.tensor("y", {n});
+  View out = y;
+  if (of_gradient) {
+    e.set_requires_grad(y.buf, true);
+    out = e.grad(y);
+  }
+  e.enable_twins();
+  e.set_tangent(true);
+  cplx* xt = e.twin_out(x.p);
+  for (int64_t i = 0; i < n; ++i) xt[i] = cplx{1.0 + i, -2.0};
+  double err = 0;
+  for (int pass = 0; pass < 3; ++pass) {
+    try {
+      Engine::Queue queued(e);
+      e.start_queue();
+      e.zero_later(out);
+      if (pass == 1) throw Error(-3, "a device error");
+      e.axpy(cplx{2, 0}, x, out);
+      e.settle();
+    } catch (const Error&) {
+      continue;
+    }
+    const cplx* t = e.twin(out.p);
+    for (int64_t i = 0; i < n; ++i)
+      err = std::max(err, t ? std::hypot(t[i].re - 2 * xt[i].re, t[i].im - 2 * xt[i].im) : 1.0);
+  }
   return err;
 }

@@ -56,6 +56,14 @@ def seg_slot(v, slot):
     assert err <= 1e-13, err
 
 
+def dropped_queue(of_gradient):
+    """Derivatives after an evaluation that ended in an error."""
+    f = _lib.load().drive_dropped_queue
+    f.restype = ctypes.c_double
+    err = f(int(of_gradient))
+    assert err == 0.0, err
+
+
 if __name__ == "__main__":
     _lib.LIBPATH = sys.argv[1]
     globals()[sys.argv[2]](*sys.argv[3:])
