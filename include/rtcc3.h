@@ -242,8 +242,10 @@ int rtcc3_zgemm_selftest(int M, int N, int K, int precision, const rtcc3_c64 *A,
 int rtcc3_zgemm_selftest_noalloc(int M, int N, int K, int precision, const rtcc3_c64 *A, const rtcc3_c64 *B,
                                  rtcc3_c64 *C);
 
-/* Autotuner summary: out[0] = products tuned, out[1] = those that run with a
- * K split other than the library's heuristic. */
+/* Autotuner summary: out[0] = products tuned, out[1] = those for which a K
+ * split other than the library's heuristic was the fastest.  They run with it,
+ * except small ones that share a launch with others into the same output and
+ * would gain less than a launch of their own costs. */
 int rtcc3_tuning_summary(rtcc3_ctx *ctx, int out[2]);
 
 /* The autotuner's choices: up to max_records rows of 8 doubles into out (host),

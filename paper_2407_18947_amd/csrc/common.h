@@ -62,6 +62,7 @@ struct GemmDesc {
   int64_t cA[4], cB[4], cC[4];
   cplx alpha;
   int atomic;
+  int shared;  // other products add to C at the same time: added with atomics, and otherwise the same product
   int prec;
   // K segments (nseg > 0, block table required): the contraction runs over
   // consecutive segments, segment s covering k in [seg[s].k0, seg[s].k0 + len)
@@ -166,7 +167,7 @@ void tuner_delete(Tuner* t);
 void tuner_set_tuning(Tuner* t, bool on);
 bool tuning_now();  // whether gemm() times its products on this thread
 void tuner_clear(Tuner* t);
-// products tuned, and how many of them run with a split other than the heuristic's
+// products tuned, and for how many of them a split other than the heuristic's was the fastest
 void tuner_counts(const Tuner* t, int& sites, int& changed);
 // The tuner gemm() consults on this thread while the scope lives (null: none).
 struct TunerScope {

@@ -137,7 +137,7 @@ void Engine::flush() {
       if (q.kind == 0) {
         g.push_back(q.g);
         for (const Queued& x : queue_)
-          if (&x != &q && x.level == l && x.adds && q.adds && meet(x.wr, q.wr)) g.back().atomic = 1;
+          if (&x != &q && x.level == l && x.adds && q.adds && meet(x.wr, q.wr)) g.back().shared = 1;
       }
       if (q.kind == 1) a.push_back(q.a);
       if (q.kind == 2) {

@@ -1256,7 +1256,7 @@ void frag_gemm(const GemmDesc& g, int ksplit, hipStream_t s) {
   RTCC3_CHECK(frag_gemm_plan(g, d, t), "frag: bad product");
   d.ksplit = ksplit;
   d.split = Divisor(ksplit);
-  d.mode = g.atomic || ksplit > 1 ? 2 : g.store ? 1 : 0;
+  d.mode = g.atomic || g.shared || ksplit > 1 ? 2 : g.store ? 1 : 0;
   if (t.ib == 2)
     t.kw == 1 ? launch_frag_gemm<2, 2, 1>(d, g.batch, t.two, s) : launch_frag_gemm<2, 2, 4>(d, g.batch, t.two, s);
   else if (t.jb == 4)
@@ -1289,7 +1289,7 @@ void frag_gemm_group(const GemmDesc* g, int n, hipStream_t s) {
       RTCC3_CHECK(frag_gemm_plan(q, d.g[i], t) && t.ib * t.jb == 1, "frag: not a small product");
       d.g[i].ksplit = 1;
       d.g[i].split = Divisor(1);
-      d.g[i].mode = q.atomic ? 2 : q.store ? 1 : 0;
+      d.g[i].mode = q.atomic || q.shared ? 2 : q.store ? 1 : 0;
       d.tail[i] = !t.two ? -1 : (d.g[i].K0 & 3) != 0;
       wg += d.g[i].gm * d.g[i].gn * q.batch;
       d.end[i] = wg;

@@ -1127,6 +1127,7 @@ struct Tuner {
   std::unordered_map<uint64_t, int> best;  // descriptor key -> K split
   std::unordered_map<uint64_t, int> heur;  // the heuristic's split for the same products
   std::unordered_map<uint64_t, TuneRecord> rec;
+  std::unordered_map<uint64_t, float> gain;  // ms that the split saves against none
   bool tuning = false;
   hipEvent_t e0 = nullptr, e1 = nullptr;
 };
@@ -1134,7 +1135,8 @@ struct Tuner {
 namespace {
 thread_local Tuner* g_tuner = nullptr;
 
-// FNV-1a over the fields that define a product's work and layout (not its pointers).
+// FNV-1a over the fields that define a product's work and layout (not its pointers, nor
+// what runs beside it).
 struct KeyHash {
   uint64_t h = 1469598103934665603ull;
   void add(int64_t x) {
@@ -1181,6 +1183,7 @@ bool tuning_now() { return g_tuner && g_tuner->tuning; }
 void tuner_clear(Tuner* t) {
   t->best.clear();
   t->heur.clear();
+  t->gain.clear();
 }
 int tuner_records(const Tuner* t, TuneRecord* out, int cap) {
   int n = 0;
@@ -1250,6 +1253,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
     }
   }
   RTCC3_CHECK(d0.K < (1 << 22) && d0.M < (1 << 22) && d0.N < (1 << 22), "gemm: extent too long");
+  RTCC3_CHECK(!(d0.store || d0.fresh) || !d0.shared, "gemm: an output written over has one product");
   RTCC3_CHECK(!d0.store || !d0.atomic, "gemm: store mode cannot be atomic");
   // A narrow side (at most 16, e.g. one occupied index) goes on N with 64x16
   // tiles; a narrow M is moved there by transposing the product.
@@ -1328,7 +1332,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
       bz *= 2;
     }
     dim3 grid((unsigned)(tiles * ks), (unsigned)by, (unsigned)bz);
-    const bool atomic = d.atomic || ks > 1;
+    const bool atomic = d.atomic || d.shared || ks > 1;
     switch (prec) {
       case RTCC3_PREC_FP64:
         launch_mode<RTCC3_PREC_FP64>(d, grid, s, ks, kchunk, atomic, kfa, nfb, bn);
@@ -1364,7 +1368,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
       const int reps = frag ? 2 : 4;
       const float margin = frag ? 0.97f : 0.975f;
       launch(ksplit, true);  // warm the caches
-      float best_ms = 1e30f, heur_ms = 0.f;
+      float best_ms = 1e30f, heur_ms = 0.f, one_ms = 1e30f;
       int best = ksplit;
       for (int ks : cand) {
         float ms = 1e30f;
@@ -1378,6 +1382,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
           ms = std::min(ms, t);
         }
         if (ks == ksplit) heur_ms = ms;
+        if (ks == 1) one_ms = ms;
         if (ms < margin * best_ms) {  // a new choice must win by more than the noise
           best_ms = ms;
           best = ks;
@@ -1385,6 +1390,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
       }
       tu->best[key] = best;
       tu->heur[key] = ksplit;
+      tu->gain[key] = one_ms - best_ms;
       tu->rec[key] = TuneRecord{d.M, d.N, d.K, d.batch, ksplit, best, heur_ms, best_ms};
       ksplit = best;
     } else {
@@ -1471,8 +1477,14 @@ void gemm_group(const GemmDesc* g, int n, hipStream_t s) {
       GemmDesc x = d.M <= 16 && d.N > 16 ? transposed(d) : d;
       int ks = frag_gemm_split(x);
       if (g_tuner) {
-        auto it = g_tuner->best.find(desc_key(x));
+        const uint64_t key = desc_key(x);
+        auto it = g_tuner->best.find(key);
         if (it != g_tuner->best.end()) ks = it->second;
+        // Products that add to one output come several to a level: one stays
+        // unless its split, timed by itself, saves more than the launch of its own
+        // that it then takes (10 steps at o=5, v=19: 27.5 ms with none of these
+        // splits, 30.0 with all of them, 27.8 with those that save 4 us).
+        if (ks > 1 && d.shared && it != g_tuner->best.end() && g_tuner->gain[key] < 0.004f) ks = 1;
       }
       in = ks == 1 && !(d.fresh && d.atomic);
     }

@@ -9,6 +9,10 @@
 
 using namespace rtcc3;
 
+extern "C" long emu_launches(const char* name);
+extern "C" void emu_reset_launches();
+extern "C" void emu_trial_ms(double of_one_workgroup);
+
 namespace {
 
 template <class T>
@@ -113,5 +117,50 @@ extern "C" double drive_dropped_queue(int of_gradient) {
     for (int64_t i = 0; i < n; ++i)
       err = std::max(err, t ? std::hypot(t[i].re - 2 * xt[i].re, t[i].im - 2 * xt[i].im) : 1.0);
   }
+  return err;
+}
+
+// Products C += A B and C += D E of M x K by K x N, tuned one by one and then
+// queued into one level: launches of a product by itself and of several
+// together, and the largest error.  ms: what the trial of one workgroup takes,
+// of more of them less (0: not tuned).
+extern "C" double drive_tuned_level(int M, int N, int K, double ms, long launches[2]) {
+  Engine e(nullptr);
+  View X[4], C = e.tensor("C", {M, N});
+  std::vector<cplx> h[4];
+  for (int q = 0; q < 4; ++q) {
+    const int r = q % 2 == 0 ? M : K, c = q % 2 == 0 ? K : N;
+    X[q] = e.tensor(std::string(1, 'p' + q), {r, c});
+    h[q] = random((size_t)r * c, 7 + q);
+    std::memcpy(X[q].p, h[q].data(), h[q].size() * sizeof(cplx));
+  }
+  Tuner* t = tuner_new();
+  TunerScope scope(t);
+  emu_trial_ms(ms);
+  auto evaluate = [&]() {
+    Engine::Queue queued(e);
+    e.zero(C);
+    e.start_queue();
+    e.einsum("mk,kn->mn", cplx{1, 0}, X[0], X[1], C);
+    e.einsum("mk,kn->mn", cplx{1, 0}, X[2], X[3], C);
+    e.settle();
+  };
+  tuner_set_tuning(t, ms > 0);
+  evaluate();
+  tuner_set_tuning(t, false);
+  emu_reset_launches();
+  evaluate();
+  launches[0] = emu_launches("frag_gemm_kernel");
+  launches[1] = emu_launches("frag_group_kernel");
+  double err = 0;
+  for (int m = 0; m < M; ++m)
+    for (int n = 0; n < N; ++n) {
+      cplx s{0, 0};
+      for (int q = 0; q < 4; q += 2)
+        for (int k = 0; k < K; ++k) add(s, h[q][m * K + k], h[q + 1][k * N + n]);
+      const cplx c = C.p[m * N + n];
+      err = std::max(err, std::hypot(c.re - s.re, c.im - s.im));
+    }
+  tuner_delete(t);
   return err;
 }

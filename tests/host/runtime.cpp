@@ -31,7 +31,7 @@ std::map<std::string, long> g_launches;
 std::string g_kernel;
 unsigned g_last_grid = 1;
 size_t g_live = 0;
-bool g_prefer_splits = false;
+double g_trial_ms = 0;
 
 // ---------------------------------------------------------------- coroutines
 extern "C" void emu_switch(void** save, void* to);
@@ -189,9 +189,9 @@ hipError_t hipMemGetInfo(size_t* free_b, size_t* total_b) {
   *free_b = *total_b = (size_t)8 << 30;
   return hipSuccess;
 }
-// What a product's trials measure: nothing, or (emu_prefer_splits) the more workgroups, the faster.
+// What a product's trials measure: all the same, or (emu_trial_ms) the more workgroups, the faster.
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
-  *ms = g_prefer_splits ? 1.0f / (float)g_last_grid : 1.0f;
+  *ms = g_trial_ms > 0 ? (float)(g_trial_ms / g_last_grid) : 1.0f;
   return hipSuccess;
 }
 
@@ -216,7 +216,7 @@ extern "C" long emu_launches(const char* name) {
   return n;
 }
 extern "C" void emu_reset_launches() { g_launches.clear(); }
-extern "C" void emu_prefer_splits(int on) { g_prefer_splits = on != 0; }
+extern "C" void emu_trial_ms(double of_one_workgroup) { g_trial_ms = of_one_workgroup; }
 extern "C" size_t emu_memory_in_use() { return g_live; }
 extern "C" void* emu_alloc(size_t n) {
   void* p = nullptr;

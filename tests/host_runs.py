@@ -64,6 +64,18 @@ def dropped_queue(of_gradient):
     assert err == 0.0, err
 
 
+def tuned_level(M, N, K, ms, apart):
+    """Two products into one output: launches of their own where their split saves enough."""
+    f = _lib.load().drive_tuned_level
+    f.restype = ctypes.c_double
+    n = (ctypes.c_long * 2)()
+    f.argtypes = [ctypes.c_int] * 3 + [ctypes.c_double, ctypes.c_void_p]
+    err = f(int(M), int(N), int(K), float(ms), n)
+    # 2K products of order one each in both parts
+    assert err <= 1e-13 * int(K), err
+    assert list(n) == ([2, 0] if int(apart) else [0, 1]), list(n)
+
+
 if __name__ == "__main__":
     _lib.LIBPATH = sys.argv[1]
     globals()[sys.argv[2]](*sys.argv[3:])

@@ -9,3 +9,12 @@ def test_derivatives_after_a_dropped_queue(host_library, of_gradient):  # noqa: 
     """An error drops the operations that are queued, the clearing of a
     derivative among them: the next evaluation clears it again."""
     host_run(host_library, "dropped_queue", of_gradient)
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 16, 128), (5, 33, 150)])
+@pytest.mark.parametrize("ms,apart", [(0, 0), (0.004, 0), (0.1, 1)])
+def test_tuned_split_of_products_in_one_level(host_library, M, N, K, ms, apart):  # noqa: F811
+    """Products that share a level with others into the same output run with the
+    split that the tuner found for them by themselves, if it saves more than a
+    launch."""
+    host_run(host_library, "tuned_level", M, N, K, ms, apart)
