@@ -104,7 +104,7 @@ void Engine::run_gemm(const GemmDesc& g, const View& A, const View& B, const Vie
   if (!queueing_) return gemm(g, stream);
   Reach w = reach_of(C);
   if (g.fresh) w = Reach{g.fresh_p, g.fresh_p + g.fresh_n};
-  const bool adds = !g.fresh && g.prec == RTCC3_PREC_FP64 && frag_gemm_small(g);
+  const bool adds = !g.fresh && frag_gemm_small(g);
   enqueue(0, adds, reach_of(A), reach_of(B), w).g = g;
 }
 
@@ -689,12 +689,12 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     return bx.size() >= by.size() ? 1 : 2;
   };
 
-  // A sum over three runs of indices (FP64): one of them becomes a batch whose
+  // A sum over three runs of indices: one of them becomes a batch whose
   // entries add to the same output, rather than one operand copied into
   // another order.  (ibde,daeb->ia with 1.4 GB of daeb, o=4, v=96: copy and
   // product 3.2 ms, as a batch over d 0.3.)
   bool summed = false;
-  if (prec == RTCC3_PREC_FP64 && gb.empty()) {
+  if (gb.empty()) {
     int sm, sn;
     std::vector<int> u = breaks(oa, gk, ext);
     for (int b : breaks(ob, gk, ext))
@@ -717,7 +717,6 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
       gb = gk.substr(cut[best], cut[best + 1] - cut[best]);
       gk.erase(cut[best], cut[best + 1] - cut[best]);
       summed = true;
-      (void)scratch(need);  // what the copy takes, for a later switch of the precision
     }
   }
 
@@ -835,7 +834,7 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
   g.B = B.p;
   g.C = C.p;
   g.alpha = alpha;
-  g.prec = prec;
+  g.prec = RTCC3_PREC_FP64;
   g.atomic = summed;
   if (g.K == 0) return;
   // host-side guard: the GEMM must not reach beyond the extent of its views

@@ -33,7 +33,6 @@ class Engine {
   Engine& operator=(const Engine&) = delete;
 
   hipStream_t stream;
-  int prec = 0;  // GEMM precision used by einsum (0 = FP64)
 
   // Once sealed, a request that would allocate device memory (a new named
   // buffer, a larger scratch, a first gradient) throws ESTATE instead: the

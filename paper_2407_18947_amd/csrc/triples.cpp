@@ -1631,8 +1631,6 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
     if (prec_ == RTCC3_PREC_FP64) {
       e.einsum("lbad,ildb->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_oovv, Y1);
       e.einsum("lbda,dlib->ia", R(-1), e.tensor("tr_Zi", {o, v, v, v}), g_voov, Y1);
-    } else {  // the relayout space of these two, for a later switch to FP64
-      (void)e.scratch(o * v * v * v + oovv + ov);
     }
     e.einsum("xljm,mlaj->xa", ONE, g_oooo, e.tensor("tr_R8", {o, o, v, o}), Y1);
   }

@@ -11,6 +11,7 @@ using namespace rtcc3;
 
 extern "C" long emu_launches(const char* name);
 extern "C" void emu_reset_launches();
+extern "C" size_t emu_memory_in_use();
 extern "C" void emu_trial_ms(double of_one_workgroup);
 
 namespace {
@@ -162,5 +163,28 @@ extern "C" double drive_tuned_level(int M, int N, int K, double ms, long launche
       err = std::max(err, std::hypot(c.re - s.re, c.im - s.im));
     }
   tuner_delete(t);
+  return err;
+}
+
+// A sum over three runs of indices, Y[i][a] = sum_bde Z[i][b][d][e] W[d][a][e][b]:
+// the device memory it takes beside its operands, and the largest error.
+extern "C" double drive_three_runs(int o, int v, size_t* extra) {
+  Engine e(nullptr);
+  View Z = e.tensor("Z", {o, v, v, v}), W = e.tensor("W", {v, v, v, v}), Y = e.tensor("Y", {o, v});
+  const std::vector<cplx> z = random(Z.numel(), 3), w = random(W.numel(), 4);
+  std::memcpy(Z.p, z.data(), z.size() * sizeof(cplx));
+  std::memcpy(W.p, w.data(), w.size() * sizeof(cplx));
+  const size_t before = emu_memory_in_use();
+  e.einsum("ibde,daeb->ia", cplx{1, 0}, Z, W, Y);
+  *extra = emu_memory_in_use() - before;
+  double err = 0;
+  for (int i = 0; i < o; ++i)
+    for (int a = 0; a < v; ++a) {
+      cplx s{0, 0};
+      for (int b = 0; b < v; ++b)
+        for (int d = 0; d < v; ++d)
+          for (int x = 0; x < v; ++x) add(s, z[((i * v + b) * v + d) * v + x], w[((d * v + a) * v + x) * v + b]);
+      err = std::max(err, std::hypot(Y.p[i * v + a].re - s.re, Y.p[i * v + a].im - s.im));
+    }
   return err;
 }

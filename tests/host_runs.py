@@ -76,6 +76,37 @@ def tuned_level(M, N, K, ms, apart):
     assert list(n) == ([2, 0] if int(apart) else [0, 1]), list(n)
 
 
+def three_runs(o, v):
+    """A sum over three runs of indices needs no copy, and reserves none."""
+    f = _lib.load().drive_three_runs
+    f.restype = ctypes.c_double
+    extra = ctypes.c_size_t()
+    err = f(int(o), int(v), ctypes.byref(extra))
+    # v^3 products of order one
+    assert err <= 1e-14 * int(v) ** 3, err
+    assert extra.value == 0, extra.value
+
+
+def precision_switch(o, v, first, then):
+    """A context switched to another precision evaluates, with what it allocated
+    when it was created, like one created with it."""
+    o, v = int(o), int(v)
+    s, y = make_system(o, v, seed=41), device(random_state(o, v, 5))
+    terms = []
+    for precision in (int(first), int(then)):
+        ctx = _lib.Context(s, precision)
+        if precision != int(then):
+            ctx.set_option(_lib.RTCC3_OPT_PRECISION, int(then))
+        td = device(np.zeros(ctx.terms_size()))
+        _lib.rtcc3_rhs_terms(ctx.ctx, FIELD, y, td, 1)
+        terms.append(ctx.split_terms(td))
+        ctx.close()
+    for name in terms[0]:
+        a, b = terms[0][name], terms[1][name]
+        # the same arithmetic; FP64 sums in another order
+        assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max() + 1e-15, name
+
+
 if __name__ == "__main__":
     _lib.LIBPATH = sys.argv[1]
     globals()[sys.argv[2]](*sys.argv[3:])

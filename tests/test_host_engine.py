@@ -18,3 +18,8 @@ def test_tuned_split_of_products_in_one_level(host_library, M, N, K, ms, apart):
     split that the tuner found for them by themselves, if it saves more than a
     launch."""
     host_run(host_library, "tuned_level", M, N, K, ms, apart)
+
+
+@pytest.mark.parametrize("o,v", [(2, 3), (3, 9), (1, 4)])
+def test_sum_over_three_runs_takes_no_memory(host_library, o, v):  # noqa: F811
+    host_run(host_library, "three_runs", o, v)

@@ -20,3 +20,9 @@ def test_reduced_precisions(host_library, o, v, precision):  # noqa: F811
     # FP32 keeps 24 bits, three bf16 slices as many, two 16; sums of up to 1e4
     # terms of either sign lose a few more
     host_run(host_library, "evaluate", o, v, precision, 0, 2e-3 if precision == 3 else 1e-4)
+
+
+@pytest.mark.parametrize("o,v", [(1, 1), (1, 3), (3, 1), (2, 4)])
+@pytest.mark.parametrize("first,then", [(2, 0), (1, 0), (0, 2), (0, 1)])
+def test_precision_switch(host_library, o, v, first, then):  # noqa: F811
+    host_run(host_library, "precision_switch", o, v, first, then)
