@@ -217,7 +217,8 @@ int rtcc3_set_option(rtcc3_ctx *ctx, int option, int value);
 
 /* Timing of the last rtcc3_propagate (milliseconds, from HIP events on the
  * context's stream): total and the part spent in the triples kernels.
- * kernel_ms[0] = total, [1] = triples, [2] = triples launches counted,
+ * kernel_ms[0] = total, [1] = triples, [2] = kernels launched over the windows of
+ * triples (builds, symmetrisations and contractions; a captured step counts once),
  * [3] = milliseconds in the segmented products that build t3 and lambda3
  * (eq. cc3-t3 and eq. cc3-l3 before symmetrisation) and, in the reduced
  * precisions, the S intermediate of Y1, [4] = their launches, [5] = their

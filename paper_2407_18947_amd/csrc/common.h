@@ -145,7 +145,7 @@ struct GemmDesc {
   int ncs;
   ColSeg cs[4];
 };
-void gemm(const GemmDesc& d, hipStream_t s);
+int gemm(const GemmDesc& d, hipStream_t s);  // returns the number of kernels launched
 
 // Autotuner of the products' K split.  While tuning, gemm() launches a product
 // whose grid is small enough for splitting K to matter once per feasible split

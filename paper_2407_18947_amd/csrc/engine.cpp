@@ -101,7 +101,7 @@ Engine::Queued& Engine::enqueue(int kind, bool adds, Reach r0, Reach r1, Reach w
 }
 
 void Engine::run_gemm(const GemmDesc& g, const View& A, const View& B, const View& C) {
-  if (!queueing_) return gemm(g, stream);
+  if (!queueing_) return (void)gemm(g, stream);
   Reach w = reach_of(C);
   if (g.fresh) w = Reach{g.fresh_p, g.fresh_p + g.fresh_n};
   const bool adds = !g.fresh && frag_gemm_small(g);

@@ -13,9 +13,11 @@ namespace rtcc3 {
 constexpr int kFragRows = 64;
 constexpr int kFragRun = 64;  // most entries of a run
 
+// The products over blocks below return the number of kernels they launched.
+
 // The FP64 form of a segmented product (GemmDesc::seg, alpha = 1), plain store
 // or atomic accumulation, with C contiguous rows of N0 elements at stride sCn1.
-void frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s);
+int frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s);
 
 // Products that read the blocks of a window as rows c of v^2 columns and sum
 // over c and over blocks,
@@ -34,7 +36,7 @@ struct FragJob {
 // bl: nblk block table entries (I, J, K, slot), in an order that keeps each
 // job's output in place over long stretches; group: the usual length of the
 // shortest such stretches.
-void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
+int frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
                  hipStream_t s);
 
 // Products that read the blocks of a window as rows k < v^2 of v columns b, and
@@ -55,7 +57,7 @@ struct ColsJob {
 };
 // pack: space for frag_cols_pack() elements, used on s only until the product is
 // done; o: the extent of K.
-void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int nstream, int v, int vp,
+int frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int nstream, int v, int vp,
                const int* part, const int* bl, const int* frags, int nfrag, int o, cplx* pack, hipStream_t s);
 int64_t frag_cols_pack(const int* rows, int njob, int o, int v);
 
@@ -83,7 +85,7 @@ struct BlockTrace {
 constexpr int kMaxBlockCols = 4;
 // pack: space for frag_block_pack() elements, used on s only until the product
 // is done; o: the extent of I, J and K.
-void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
+int frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
                 int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s);
 int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v);
 

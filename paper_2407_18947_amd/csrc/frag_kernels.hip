@@ -1039,9 +1039,9 @@ int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v) {
   return (int64_t)block_panels(groups, ng, o, panel) * (((int64_t)v * v + 3) / 4 * 4 * n);
 }
 
-void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
+int frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
                 int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s) {
-  if (nblk <= 0 || ng <= 0) return;
+  if (nblk <= 0 || ng <= 0) return 0;
   RTCC3_CHECK(ng <= kMaxBlockCols && ntr <= kMaxBlockCols && n >= 1 && v >= 1 && vp >= v &&
                   (int64_t)v * v * vp < (1LL << 27) && ((int64_t)v * v + 3) * n < (1LL << 27),
               "frag: bad block product");
@@ -1049,6 +1049,7 @@ void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, in
   const int64_t plen = ((int64_t)v * v + 3) / 4 * 4 * n;
   if (ng > 1 && (block_panels(groups, ng, o, d.panel) + 1) * plen * (int64_t)sizeof(cplx) > (1LL << 32)) {
     // a fragment's panels have to lie within 2^32 bytes: with one group it has one
+    int launches = 0;
     for (int q = 0; q < ng; ++q) {
       std::vector<BlockTrace> own;
       for (int t = 0; t < ntr; ++t)
@@ -1056,9 +1057,9 @@ void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, in
           own.push_back(tr[t]);
           own.back().group = 0;
         }
-      frag_block(groups + q, 1, n, own.data(), (int)own.size(), X, perm, o, v, vp, part, bl, nblk, pack, s);
+      launches += frag_block(groups + q, 1, n, own.data(), (int)own.size(), X, perm, o, v, vp, part, bl, nblk, pack, s);
     }
-    return;
+    return launches;
   }
   block_panels(groups, ng, o, d.panel);
   d.ng = ng;
@@ -1080,6 +1081,7 @@ void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, in
   hipLaunchKernelGGL(block_pack_kernel, dim3((unsigned)std::min<int64_t>((packed + 255) / 256, 65536)), dim3(256), 0, s,
                      pk);
   RTCC3_HIP(hipGetLastError());
+  int launches = 1;
   d.X = X;
   d.pack = pack;
   d.bl = bl;
@@ -1105,7 +1107,9 @@ void frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, in
     RTCC3_CHECK(nw < (1LL << 31), "frag: product too large");
     hipLaunchKernelGGL(frag_block_kernel, dim3((unsigned)((nw + 3) / 4)), dim3(256), 0, s, d);
     RTCC3_HIP(hipGetLastError());
+    ++launches;
   }
+  return launches;
 }
 
 namespace {
@@ -1305,9 +1309,9 @@ int64_t frag_cols_pack(const int* rows, int njob, int o, int v) {
   return o * nrb * (((int64_t)v * v + 3) / 4) * 64;
 }
 
-void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int nstream, int v, int vp,
+int frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int nstream, int v, int vp,
                const int* part, const int* bl, const int* frags, int nfrag, int o, cplx* pack, hipStream_t s) {
-  if (nfrag <= 0 || njob <= 0) return;
+  if (nfrag <= 0 || njob <= 0) return 0;
   RTCC3_CHECK(njob <= 2 && (nstream == 1 || nstream == 3) && v >= 1 && vp >= v, "frag: bad column product");
   RTCC3_CHECK((int64_t)v * v * vp < (1LL << 27), "frag: product too large");
   FragCols d;
@@ -1344,6 +1348,7 @@ void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, in
   hipLaunchKernelGGL(cols_pack_kernel, dim3((unsigned)std::min<int64_t>((packed + 255) / 256, 65536)), dim3(256), 0, s,
                      pk);
   RTCC3_HIP(hipGetLastError());
+  int launches = 1;
   d.pack = pack;
   d.npanel = (int)rb.size();
   // Row blocks in groups as large as the registers allow (the sums of a B
@@ -1368,6 +1373,7 @@ void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, in
     else
       hipLaunchKernelGGL(frag_cols_kernel<3>, grid, dim3(256), 0, s, d);
     RTCC3_HIP(hipGetLastError());
+    ++launches;
     d.nunit = 0;
   };
   d.nunit = 0;
@@ -1383,11 +1389,12 @@ void frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, in
     if (d.nunit == kMaxColsUnits) launch();
   }
   if (d.nunit > 0) launch();
+  return launches;
 }
 
-void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
+int frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
                  hipStream_t s) {
-  if (nblk <= 0 || njob <= 0) return;
+  if (nblk <= 0 || njob <= 0) return 0;
   RTCC3_CHECK(njob <= 2 && v >= 1 && vp >= v && group >= 1, "frag: bad gathered product");
   RTCC3_CHECK((int64_t)v * v * vp < (1LL << 27) && (int64_t)v * v < (1 << 22), "frag: product too large");
   FragGather d;
@@ -1408,6 +1415,7 @@ void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, co
     d.job[j] = jobs[j];
     for (int m = 0; m < jobs[j].M; m += 16) rb.push_back({j, m});
   }
+  int launches = 0;
   auto launch = [&]() {
     // Chunks of whole groups (stretches with one output of a job: fewer flushes)
     // for at least eight rounds of the chip's 2048 waves; below one group a
@@ -1420,6 +1428,7 @@ void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, co
     RTCC3_CHECK(nw < (1LL << 31), "frag: product too large");
     hipLaunchKernelGGL(frag_gather_kernel, dim3((unsigned)((nw + 3) / 4)), dim3(256), 0, s, d);
     RTCC3_HIP(hipGetLastError());
+    ++launches;
     d.nunit = 0;
   };
   for (size_t q = 0; q < rb.size();) {
@@ -1437,10 +1446,11 @@ void frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, co
     if (d.nunit + 2 > kMaxUnits) launch();
   }
   if (d.nunit > 0) launch();
+  return launches;
 }
 
-void frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s) {
-  if (nrt <= 0) return;
+int frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s) {
+  if (nrt <= 0) return 0;
   RTCC3_CHECK(g.nseg >= 1 && g.nseg <= 4 && g.bl && row_tiles && g.M0 == g.M && g.sCn0 == 1 && g.alpha.re == 1.0 &&
                   g.alpha.im == 0.0 && (g.store != 0) != (g.atomic != 0) && g.cC[0] == 0 && g.cC[1] == 0 &&
                   g.cC[2] == 0 && g.sCm0 == (int64_t)(g.N / g.N0) * g.sCn1 && g.N == g.M * g.N0 && g.N0 == g.M,
@@ -1470,6 +1480,7 @@ void frag_seg(const GemmDesc& g, const int* row_tiles, int nrt, hipStream_t s) {
   else
     hipLaunchKernelGGL(frag_seg_kernel<false>, grid, dim3(256), 0, s, d);
   RTCC3_HIP(hipGetLastError());
+  return 1;
 }
 
 }  // namespace rtcc3

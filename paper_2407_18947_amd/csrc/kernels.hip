@@ -1204,7 +1204,7 @@ void tuner_counts(const Tuner* t, int& sites, int& changed) {
 TunerScope::TunerScope(Tuner* t) : prev(g_tuner) { g_tuner = t; }
 TunerScope::~TunerScope() { g_tuner = prev; }
 
-void gemm(const GemmDesc& d_in, hipStream_t s) {
+int gemm(const GemmDesc& d_in, hipStream_t s) {
   // A bf16-split run takes the split kernel for its segmented products only.
   // Its other products run in FP32, except the 16-wide gathered ones, whose FP64
   // kernel was the faster one (1.95 against 2.51 ms at o=15, v=57) and is more
@@ -1214,8 +1214,8 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
       !((dsel.nseg > 0 || dsel.force_prec) && !dsel.comb_n && !dsel.gk_start && !dsel.ncs))
     dsel.prec = dsel.gk_start && dsel.N <= 16 ? RTCC3_PREC_FP64 : RTCC3_PREC_FP32;
   const GemmDesc& d0 = dsel;
-  if (d0.M <= 0 || d0.N <= 0 || d0.batch <= 0) return;
-  if (d0.K <= 0) return;
+  if (d0.M <= 0 || d0.N <= 0 || d0.batch <= 0) return 0;
+  if (d0.K <= 0) return 0;
   RTCC3_CHECK(d0.M0 >= 1 && d0.N0 >= 1 && d0.K0 >= 1, "gemm: inner extents must be >= 1");
   if (d0.comb_n > 0) {
     RTCC3_CHECK((d0.comb_n == 3 || (d0.comb_n == 1 && d0.comb_on == 1)) && d0.bl && d0.part && d0.nseg == 0 &&
@@ -1312,7 +1312,9 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
   // 6.1 from fragments; o=5, v=18: 2.0 and 0.6).
   const bool frag = prec == RTCC3_PREC_FP64 && frag_gemm_fits(d);
   if (frag) ksplit = frag_gemm_split(d);
+  int launches = 0;
   auto launch = [&](int ks, bool trial = false) {
+    ++launches;
     // In FP32 the trials add in any case: which split is the fastest by itself
     // decides, since the split is also how far the sums are formed in FP32.
     d.store = d_in.store;
@@ -1320,7 +1322,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
       if (ks == 1 && !d.atomic)
         d.store = 1;
       else
-        fill(d.fresh_p, d.fresh_n, cplx{0, 0}, s);
+        fill(d.fresh_p, d.fresh_n, cplx{0, 0}, s), ++launches;
     }
     if (frag) return frag_gemm(d, ks, s);
     const int kchunk = (int)((((int64_t)d.K + ks - 1) / ks + BKMAX - 1) / BKMAX * BKMAX);
@@ -1399,6 +1401,7 @@ void gemm(const GemmDesc& d_in, hipStream_t s) {
     }
   }
   launch(ksplit);
+  return launches;
 }
 
 namespace {

@@ -58,8 +58,8 @@ int64_t span(int64_t X, int64_t X0, int64_t s1, int64_t s0) {
 
 // Launch a GEMM after checking, on the host, that every batch entry stays
 // inside the operand buffers (lengths in elements).
-void checked_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
-  if (g.batch <= 0) return;
+int checked_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
+  if (g.batch <= 0) return 0;
   const int64_t eA = span(g.M, g.M0, g.sAm1, g.sAm0) + span(g.K, g.K0, g.sAk1, g.sAk0);
   const int64_t eB = span(g.K, g.K0, g.sBk1, g.sBk0) + span(g.N, g.N0, g.sBn1, g.sBn0);
   const int64_t eC = span(g.M, g.M0, g.sCm1, g.sCm0) + span(g.N, g.N0, g.sCn1, g.sCn0);
@@ -79,15 +79,15 @@ void checked_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t l
     RTCC3_CHECK(oB >= 0 && oB + eB < lenB, "triples: B operand out of bounds");
     RTCC3_CHECK(oC >= 0 && oC + eC < lenC, "triples: C operand out of bounds");
   }
-  gemm(g, s);
+  return gemm(g, s);
 }
 
 // A gathered-K product (GemmDesc::gk_*) over one grouping of a window's
 // contraction blocks after the same check for every gathered block and every
 // group's output.
-void checked_gather_gemm(GemmDesc& g, const Groups& gr, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
+int checked_gather_gemm(GemmDesc& g, const Groups& gr, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
   const int ng = (int)gr.key.size() / 4;
-  if (ng == 0) return;
+  if (ng == 0) return 0;
   g.batch = ng;
   g.bl = gr.d_key;
   g.gk_start = gr.d_start;
@@ -106,15 +106,15 @@ void checked_gather_gemm(GemmDesc& g, const Groups& gr, int64_t lenA, int64_t le
       RTCC3_CHECK(oB >= 0 && oB + eB < lenB, "triples: B operand out of bounds");
     }
   }
-  gemm(g, s);
+  return gemm(g, s);
 }
 
 // A K-segmented product (GemmDesc::seg) after the same check per segment;
 // lenA[s], lenB[s]: lengths of segment s's operand tensors.  FP64 products go
 // to the fragment kernel with the row tiles of their block table.
-void checked_seg_gemm(const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
+int checked_seg_gemm(const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
                       const int64_t* lenB, int64_t lenC, hipStream_t s) {
-  if (g.batch <= 0) return;
+  if (g.batch <= 0) return 0;
   RTCC3_CHECK(g.bl && g.nseg >= 1 && g.nseg <= 4, "triples: segmented product needs a block table");
   const int64_t eC = span(g.M, g.M0, g.sCm1, g.sCm0) + span(g.N, g.N0, g.sCn1, g.sCn0);
   for (int b = 0; b < g.batch; ++b) {
@@ -134,17 +134,16 @@ void checked_seg_gemm(const GemmDesc& g, const int* bl_host, const RowTiles& rt,
     }
   }
   if (g.prec == RTCC3_PREC_FP64)
-    frag_seg(g, rt.d, (int)rt.h.size() / 4, s);
-  else
-    gemm(g, s);
+    return frag_seg(g, rt.d, (int)rt.h.size() / 4, s);
+  return gemm(g, s);
 }
 
 // A column-segment product (GemmDesc::cs) after the same check per segment;
 // lenB[s], lenC[s]: lengths of segment s's B and C tensors, lenB[4 + s],
 // lenC[4 + s] those of its tail column's (when it has one).
-void checked_colseg_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB, const int64_t* lenC,
+int checked_colseg_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB, const int64_t* lenC,
                          hipStream_t s) {
-  if (g.batch <= 0) return;
+  if (g.batch <= 0) return 0;
   RTCC3_CHECK(g.bl && g.ncs >= 1 && g.ncs <= 4, "triples: column segments need a block table");
   const int64_t eA = span(g.M, g.M0, g.sAm1, g.sAm0) + span(g.K, g.K0, g.sAk1, g.sAk0);
   auto dot = [](const int64_t* c, const int* q) { return c[0] * q[0] + c[1] * q[1] + c[2] * q[2] + c[3] * q[3]; };
@@ -166,7 +165,7 @@ void checked_colseg_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, co
       }
     }
   }
-  gemm(g, s);
+  return gemm(g, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -177,40 +176,44 @@ void checked_colseg_gemm(const GemmDesc& g, const int* bl_host, int64_t lenA, co
 // accumulates the others; if every twin is zero it clears C' instead.
 // ---------------------------------------------------------------------------
 
-void tangent_gemm(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t lenB, int64_t lenC,
+int tangent_gemm(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t lenB, int64_t lenC,
                   hipStream_t s) {
   const cplx* at = e.twin(g.A);
   const cplx* bt = e.twin(g.B);
   RTCC3_CHECK(!g.store, "triples: derivative of a plain store-mode product");
-  if (!at && !bt) return;
+  if (!at && !bt) return 0;
   cplx* ct = e.twin_out(g.C);
+  int launches = 0;
   for (int q = 0; q < 2; ++q) {
     const cplx* x = q == 0 ? at : bt;
     if (!x) continue;
     GemmDesc h = g;
     (q == 0 ? h.A : h.B) = x;
     h.C = ct;
-    checked_gemm(h, bl_host, lenA, lenB, lenC, s);
+    launches += checked_gemm(h, bl_host, lenA, lenB, lenC, s);
   }
+  return launches;
 }
 
-void tangent_gather(Engine& e, const GemmDesc& g, const Groups& gr, int64_t lenA, int64_t lenB, int64_t lenC,
+int tangent_gather(Engine& e, const GemmDesc& g, const Groups& gr, int64_t lenA, int64_t lenB, int64_t lenC,
                     hipStream_t s) {
   const cplx* at = e.twin(g.A);
   const cplx* bt = e.twin(g.B);
-  if (!at && !bt) return;
+  if (!at && !bt) return 0;
   cplx* ct = e.twin_out(g.C);
+  int launches = 0;
   for (int q = 0; q < 2; ++q) {
     const cplx* x = q == 0 ? at : bt;
     if (!x) continue;
     GemmDesc h = g;
     (q == 0 ? h.A : h.B) = x;
     h.C = ct;
-    checked_gather_gemm(h, gr, lenA, lenB, lenC, s);
+    launches += checked_gather_gemm(h, gr, lenA, lenB, lenC, s);
   }
+  return launches;
 }
 
-void tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
+int tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
                  const int64_t* lenB, int64_t lenC, hipStream_t s) {
   struct Term {
     GemmDesc::Seg sg;
@@ -232,8 +235,9 @@ void tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTile
   cplx* ct = e.twin_out(g.C);
   if (terms.empty()) {
     if (g.store) fill(ct, lenC, cplx{0, 0}, s);
-    return;
+    return g.store ? 1 : 0;
   }
+  int launches = 0;
   for (size_t p0 = 0; p0 < terms.size(); p0 += 4) {
     GemmDesc h = g;
     h.C = ct;
@@ -252,13 +256,15 @@ void tangent_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTile
       h.store = 0;
       h.atomic = 1;
     }
-    checked_seg_gemm(h, bl_host, rt, la, lb, lenC, s);
+    launches += checked_seg_gemm(h, bl_host, rt, la, lb, lenC, s);
   }
+  return launches;
 }
 
-void tangent_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB,
+int tangent_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB,
                     const int64_t* lenC, hipStream_t s) {
   const cplx* at = e.twin(g.A);
+  int launches = 0;
   if (at) {  // A' with every segment's B (and tail)
     GemmDesc h = g;
     h.A = at;
@@ -266,7 +272,7 @@ void tangent_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t le
       h.cs[t].C = e.twin_out(g.cs[t].C);
       if (g.cs[t].tB) h.cs[t].tC = e.twin_out(g.cs[t].tC);
     }
-    checked_colseg_gemm(h, bl_host, lenA, lenB, lenC, s);
+    launches += checked_colseg_gemm(h, bl_host, lenA, lenB, lenC, s);
   }
   // A with the segments' B' (and tails'); a segment whose B' is zero but whose
   // tail's is not runs with a zero scale
@@ -298,36 +304,37 @@ void tangent_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t le
     lc[4 + ns] = lenC[4 + t];
     ++ns;
   }
-  if (ns == 0) return;
+  if (ns == 0) return launches;
   h.ncs = ns;
   h.N = h.N0 = 16 * ns;
-  checked_colseg_gemm(h, bl_host, lenA, lb, lc, s);
+  return launches + checked_colseg_gemm(h, bl_host, lenA, lb, lc, s);
 }
 
-// The products with their derivatives in tangent mode.
-void prod(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
-  checked_gemm(g, bl_host, lenA, lenB, lenC, s);
-  if (e.tangent()) tangent_gemm(e, g, bl_host, lenA, lenB, lenC, s);
+// The products with their derivatives in tangent mode; they return the number
+// of kernels launched.
+int prod(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
+  const int launches = checked_gemm(g, bl_host, lenA, lenB, lenC, s);
+  return e.tangent() ? launches + tangent_gemm(e, g, bl_host, lenA, lenB, lenC, s) : launches;
 }
-void prod_gather(Engine& e, GemmDesc& g, const Groups& gr, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
-  checked_gather_gemm(g, gr, lenA, lenB, lenC, s);
-  if (e.tangent()) tangent_gather(e, g, gr, lenA, lenB, lenC, s);
+int prod_gather(Engine& e, GemmDesc& g, const Groups& gr, int64_t lenA, int64_t lenB, int64_t lenC, hipStream_t s) {
+  const int launches = checked_gather_gemm(g, gr, lenA, lenB, lenC, s);
+  return e.tangent() ? launches + tangent_gather(e, g, gr, lenA, lenB, lenC, s) : launches;
 }
-void prod_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
+int prod_seg(Engine& e, const GemmDesc& g, const int* bl_host, const RowTiles& rt, const int64_t* lenA,
               const int64_t* lenB, int64_t lenC, hipStream_t s) {
-  checked_seg_gemm(g, bl_host, rt, lenA, lenB, lenC, s);
-  if (e.tangent()) tangent_seg(e, g, bl_host, rt, lenA, lenB, lenC, s);
+  const int launches = checked_seg_gemm(g, bl_host, rt, lenA, lenB, lenC, s);
+  return e.tangent() ? launches + tangent_seg(e, g, bl_host, rt, lenA, lenB, lenC, s) : launches;
 }
-void prod_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB,
+int prod_colseg(Engine& e, const GemmDesc& g, const int* bl_host, int64_t lenA, const int64_t* lenB,
                  const int64_t* lenC, hipStream_t s) {
-  checked_colseg_gemm(g, bl_host, lenA, lenB, lenC, s);
-  if (e.tangent()) tangent_colseg(e, g, bl_host, lenA, lenB, lenC, s);
+  const int launches = checked_colseg_gemm(g, bl_host, lenA, lenB, lenC, s);
+  return e.tangent() ? launches + tangent_colseg(e, g, bl_host, lenA, lenB, lenC, s) : launches;
 }
 
 // Jobs over the blocks of a window (FragJob), after the same check per job and
 // block, with their derivatives in tangent mode.  lenA, lenC: lengths of each
 // job's tensors; lenB that of the window buffer.
-void prod_frag_gather(Engine& e, const std::vector<FragJob>& jobs, const int64_t* lenA, const int64_t* lenC,
+int prod_frag_gather(Engine& e, const std::vector<FragJob>& jobs, const int64_t* lenA, const int64_t* lenC,
                       const cplx* B, int64_t lenB, int v, int vp, const std::vector<int>& bl_host, const int* bl,
                       int group, hipStream_t s) {
   const int nblk = (int)bl_host.size() / 4;
@@ -344,8 +351,8 @@ void prod_frag_gather(Engine& e, const std::vector<FragJob>& jobs, const int64_t
       RTCC3_CHECK(q[3] >= 0 && (q[3] + 1) * vb <= lenB, "triples: B operand out of bounds");
     }
   }
-  frag_gather(jobs.data(), (int)jobs.size(), B, v, vp, bl, nblk, group, s);
-  if (!e.tangent()) return;
+  int launches = frag_gather(jobs.data(), (int)jobs.size(), B, v, vp, bl, nblk, group, s);
+  if (!e.tangent()) return launches;
   const cplx* bt = e.twin(B);
   std::vector<const cplx*> at;
   for (const FragJob& g : jobs) at.push_back(e.twin(g.A));
@@ -360,13 +367,13 @@ void prod_frag_gather(Engine& e, const std::vector<FragJob>& jobs, const int64_t
       ja.push_back(h);
     }
   }
-  if (bt) frag_gather(jb.data(), (int)jb.size(), bt, v, vp, bl, nblk, group, s);
-  frag_gather(ja.data(), (int)ja.size(), B, v, vp, bl, nblk, group, s);
+  if (bt) launches += frag_gather(jb.data(), (int)jb.size(), bt, v, vp, bl, nblk, group, s);
+  return launches + frag_gather(ja.data(), (int)ja.size(), B, v, vp, bl, nblk, group, s);
 }
 
 // Column products (ColsJob) after the same check, with their derivatives in
 // tangent mode.
-void prod_frag_cols(Engine& e, const std::vector<ColsJob>& jobs, const int64_t* lenA, const int64_t* lenC,
+int prod_frag_cols(Engine& e, const std::vector<ColsJob>& jobs, const int64_t* lenA, const int64_t* lenC,
                     const cplx* B, int64_t lenB, const int* perm, int nstream, int o, int v, int vp, const Window& w,
                     const ColTable& ct, hipStream_t s) {
   const int64_t vb = (int64_t)v * v * vp, v2 = (int64_t)v * v;
@@ -389,8 +396,9 @@ void prod_frag_cols(Engine& e, const std::vector<ColsJob>& jobs, const int64_t* 
   std::vector<int> rows;
   for (const ColsJob& g : jobs) rows.push_back(g.M);
   cplx* pack = e.scratch(frag_cols_pack(rows.data(), (int)rows.size(), o, v), s);
-  frag_cols(jobs.data(), (int)jobs.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
-  if (!e.tangent()) return;
+  int launches =
+      frag_cols(jobs.data(), (int)jobs.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+  if (!e.tangent()) return launches;
   const cplx* bt = e.twin(B);
   std::vector<ColsJob> jb, ja;
   for (const ColsJob& g : jobs) {
@@ -404,13 +412,16 @@ void prod_frag_cols(Engine& e, const std::vector<ColsJob>& jobs, const int64_t* 
       ja.push_back(h);
     }
   }
-  frag_cols(jb.data(), (int)jb.size(), bt, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
-  frag_cols(ja.data(), (int)ja.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+  launches +=
+      frag_cols(jb.data(), (int)jb.size(), bt, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+  launches +=
+      frag_cols(ja.data(), (int)ja.size(), B, perm, nstream, v, vp, w.d_part, ct.d_bl, ct.d_frag, nf, o, pack, s);
+  return launches;
 }
 
 // Block products (BlockCols, BlockTrace) after the same check, with their
 // derivatives in tangent mode.
-void prod_frag_block(Engine& e, const std::vector<BlockCols>& groups, const std::vector<BlockTrace>& traces, int o,
+int prod_frag_block(Engine& e, const std::vector<BlockCols>& groups, const std::vector<BlockTrace>& traces, int o,
                      const int64_t* lenB, const int64_t* lenC, const int64_t* lenT, const cplx* X, int64_t lenX,
                      int perm, int v, int vp, const Window& w, const std::vector<int>& bl_host, const int* bl,
                      hipStream_t s) {
@@ -430,12 +441,13 @@ void prod_frag_block(Engine& e, const std::vector<BlockCols>& groups, const std:
       RTCC3_CHECK(traces[t].sC * q[traces[t].row] + v <= lenT[t], "triples: C segment out of bounds");
   }
   auto run = [&](const std::vector<BlockCols>& g, const std::vector<BlockTrace>& t, const cplx* x) {
-    if (g.empty()) return;
+    if (g.empty()) return 0;
     cplx* pack = e.scratch(frag_block_pack(g.data(), (int)g.size(), o, o, v), s);
-    frag_block(g.data(), (int)g.size(), o, t.data(), (int)t.size(), x, perm, o, v, vp, w.d_part, bl, nblk, pack, s);
+    return frag_block(g.data(), (int)g.size(), o, t.data(), (int)t.size(), x, perm, o, v, vp, w.d_part, bl, nblk, pack,
+                      s);
   };
-  run(groups, traces, X);
-  if (!e.tangent()) return;
+  int launches = run(groups, traces, X);
+  if (!e.tangent()) return launches;
   // d(X B) = dX B + X dB
   const cplx* xt = e.twin(X);
   for (int side = 0; side < 2; ++side) {
@@ -454,8 +466,9 @@ void prod_frag_block(Engine& e, const std::vector<BlockCols>& groups, const std:
       g.back().C = e.twin_out(g.back().C);
       if (side == 1) g.back().B = bt;
     }
-    run(g, t, side == 0 ? xt : X);
+    launches += run(g, t, side == 0 ? xt : X);
   }
+  return launches;
 }
 
 // The innermost index of a window block padded to a multiple of 8.
@@ -1028,14 +1041,15 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     set4(g.cC, 0, 0, 0, vb);
     const int64_t lA[2] = {lT2, lOOOV}, lB[2] = {lOVVV_, lT2};
     build_event(s);
-    prod_seg(e, g, w.bk_t3.data(), w.rt_t3, lA, lB, winlen, s);
+    launches_ += prod_seg(e, g, w.bk_t3.data(), w.rt_t3, lA, lB, winlen, s);
     build_event(s);
     build_flop_ += 8.0 * nw * v * v2 * (v + o);
   }
   RTCC3_HIP(hipEventRecord(ev_t3b_, s));
-  launch_sym_cube(T, w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, nullptr, nullptr, s);
+  launches_ += launch_sym_cube(T, w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, nullptr, nullptr, s);
   if (e.tangent())  // the symmetrisation and the denominator are linear in W'
-    launch_sym_cube(e.twin_out(T), w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, nullptr, nullptr, s);
+    launches_ += launch_sym_cube(e.twin_out(T), w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, nullptr,
+                                 nullptr, s);
   RTCC3_HIP(hipEventRecord(ev_t_, s));  // t3 blocks ready
 
   // Contractions run over the blocks this window is responsible for: all of
@@ -1068,7 +1082,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       const int64_t lS = (int64_t)max_nw_ * v2 * o;
       const int64_t lA[2] = {t2len, t2len}, lB[2] = {lOOVV, lOOVV};
       build_event(s2);  // same kernel as the builds: timed with them
-      prod_seg(e, g, sblh, w.rt_l3, lA, lB, lS, s2);
+      launches_ += prod_seg(e, g, sblh, w.rt_l3, lA, lB, lS, s2);
       build_event(s2);
       build_flop_ += 8.0 * cn * v * (o * v) * (2 * v);
     }
@@ -1099,7 +1113,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     const int64_t lA[4] = {lLC, lLC, l2len, l2len}, lB[4] = {l2len, l2len, lOVVV_, lOVVV_};
     RTCC3_HIP(hipStreamWaitEvent(s2, ev_t3b_, 0));  // after the t3 build (a no-op when S went first)
     build_event(s2);
-    prod_seg(e, g, w.bk_l3.data(), w.rt_l3, lA, lB, winlen, s2);
+    launches_ += prod_seg(e, g, w.bk_l3.data(), w.rt_l3, lA, lB, winlen, s2);
     build_event(s2);
     build_flop_ += 8.0 * nw * v * v2 * (2 * o + 2 * v);
     RTCC3_HIP(hipEventRecord(ev_l3b_, s2));
@@ -1110,18 +1124,17 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
   }
   {  // P_ijk^abc and the denominator; the terms without a summation index are added per source
     LamElem le{Lov, F, l1, l2};
-    launch_sym_cube(L, w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, &le, nullptr, s2);
+    launches_ += launch_sym_cube(L, w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, &le, nullptr, s2);
     if (e.tangent()) {
       // the bracket terms' derivative: L l1' + f~' l2 + f~ l2' (L is invariant
       // under the T1 transformation: its twin is zero)
       RTCC3_CHECK(!e.twin(Lov), "triples: L_iajb has a derivative");
       LamElem d0{Lov, e.twin(F), e.twin(l1), l2}, d1{nullptr, F, nullptr, e.twin(l2)};
-      launch_sym_cube(e.twin_out(L), w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, &d0,
-                      d1.l2 ? &d1 : nullptr, s2);
+      launches_ += launch_sym_cube(e.twin_out(L), w.d_canon, (int)w.canon.size() / 4, w.d_part, eps_, o, v, vp, &d0,
+                                   d1.l2 ? &d1 : nullptr, s2);
     }
   }
   RTCC3_HIP(hipEventRecord(ev_l_, s2));  // lambda3 blocks ready
-  launches_ += 4;
 
   {  // the contractions of the right-hand side
     cplx* X1 = P("tr_X1", {o, v});
@@ -1145,7 +1158,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     const bool frag16 = pr == RTCC3_PREC_FP64 || (pr != RTCC3_PREC_FP32 && o <= 16);
     RTCC3_CHECK(o <= 15 || !e.tangent(), "triples: derivatives need o <= 15");
     if (!tails) {
-      launch_small_t3(T, cbl, cn, Lov, F, l2, X1, X2p, Z34, o, v, vp, 3, s);
+      launches_ += launch_small_t3(T, cbl, cn, Lov, F, l2, X1, X2p, Z34, o, v, vp, 3, s);
     }
     // the t3 side's products are bound by the matrix cores like the lambda3
     // build: they start once it is done
@@ -1173,8 +1186,8 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       // not wanted
     } else if (pr != RTCC3_PREC_FP32) {
       const int perm[3] = {2, 0, 4};
-      prod_frag_cols(e, {{gX2a, v3, v2, v, X2p, {(int64_t)o * v2, v2}, v, 1}}, &lOVVV, &oovv, T, winlen, perm, 3, o, v, vp,
-                     w, w.cols_t3, s);
+      launches_ += prod_frag_cols(e, {{gX2a, v3, v2, v, X2p, {(int64_t)o * v2, v2}, v, 1}}, &lOVVV, &oovv, T, winlen,
+                                  perm, 3, o, v, vp, w, w.cols_t3, s);
     } else {  // with (c,e) contiguous
       GemmDesc g = base(v, v, (int)v2, cn, obl, pr);
       g.atomic = 1;
@@ -1194,7 +1207,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.sCm0 = v;
       g.sCn0 = 1;
       set4(g.cC, (int64_t)o * v2, v2, 0, 0);
-      prod(e, g, oblh, lOVVV, winlen, oovv, s);
+      launches_ += prod(e, g, oblh, lOVVV, winlen, oovv, s);
     }
     // X2 -= sum_c Zh[(a,b)][c] G[K][I][c][x] into X2p[x][J], G[k][m][c][x] = (kx|mc)~.
     // The contraction set holds every ordering of its triples, so each term of
@@ -1212,7 +1225,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       const std::vector<FragJob> jobs = {{gX2c, {oov, ovl, 0}, v, ovl, o, X2p, {0, 0, v2}, ov2, 1.0},
                                          {gX2b, {0, oov, ovl}, v, ovl, o, X2p, {v2, 0, 0}, ov2, 1.0}};
       const int64_t lA[2] = {lOOOV, lOOOV}, lC[2] = {oovv, oovv};
-      prod_frag_gather(e, jobs, lA, lC, T, winlen, v, vp, w.gat_t3, w.d_gat_t3, o, s);
+      launches_ += prod_frag_gather(e, jobs, lA, lC, T, winlen, v, vp, w.gat_t3, w.d_gat_t3, o, s);
     } else {
       // two gathered products, over the blocks of each J and of each K, without atomics
       auto x2b = [&](const cplx* Bp, const int64_t* cb, const int64_t* cc, const Groups& gr) {
@@ -1233,7 +1246,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
         g.sCm0 = 1;
         g.sCn0 = (int64_t)o * v2;
         std::memcpy(g.cC, cc, sizeof(g.cC));
-        prod_gather(e, g, gr, winlen, lOOOV, oovv, s);
+        launches_ += prod_gather(e, g, gr, winlen, lOOOV, oovv, s);
       };
       {
         // (G[K][I] - 2 G[I][K]) is tb_X2c at [K][I]; G[I][J] is tb_X2b at [I][J]
@@ -1253,7 +1266,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
                                    {t2, v2, (int64_t)o * v2, o, R8, {(int64_t)o * v * o, (int64_t)v * o}, 1, o}};
       const int skip = amps_ ? 0 : 1;
       jobs.erase(jobs.begin(), jobs.begin() + skip);
-      prod_frag_cols(e, jobs, lA + skip, lC + skip, L, winlen, perm, 1, o, v, vp, w, w.cols_l3, s2);
+      launches_ += prod_frag_cols(e, jobs, lA + skip, lC + skip, L, winlen, perm, 1, o, v, vp, w, w.cols_l3, s2);
     } else {  // lambda_IJK[d][b][e] = lambda_JIK[b][d][e], read with (d,e) contiguous
       GemmDesc g = base(v, v, (int)v2, cn, cbl, pr);
       g.atomic = 1;
@@ -1277,7 +1290,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.sCm0 = v;
       g.sCn0 = 1;
       set4(g.cC, (int64_t)o * v2, v2, 0, 0);
-      prod(e, g, cblh, lOVVV, winlen, oovv, s2);
+      launches_ += prod(e, g, cblh, lOVVV, winlen, oovv, s2);
     }
     // Y2: -sum_d lambda[(a,b)][d] (xI|dK)~ into Y2p[x][J] and
     // Zi[J][b][(d,e)] += sum_c t2[K][I][b][c] lambda[c][(d,e)] (block (k,i,j) = (I,J,K)) for term 11, and in FP64
@@ -1291,9 +1304,9 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       // not wanted
     } else if (pr == RTCC3_PREC_FP64) {
       const int64_t lA[2] = {t2len, lOOOV}, lC[2] = {lOVVV, oovv};
-      prod_frag_gather(e, {jZ, jY}, lA, lC, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
+      launches_ += prod_frag_gather(e, {jZ, jY}, lA, lC, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
     } else if (frag16) {
-      prod_frag_gather(e, {jY}, &lOOOV, &oovv, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
+      launches_ += prod_frag_gather(e, {jY}, &lOOOV, &oovv, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
     } else {  // summed over the blocks of each J
       GemmDesc g = base((int)v2, o, v * w.gJ.max, 0, nullptr, pr);
       g.K0 = v;
@@ -1313,7 +1326,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.sCm0 = 1;
       g.sCn0 = (int64_t)o * v2;
       set4(g.cC, 0, v2, 0, 0);
-      prod_gather(e, g, w.gJ, winlen, lOOOV, oovv, s2);
+      launches_ += prod_gather(e, g, w.gJ, winlen, lOOOV, oovv, s2);
     }
     // Products that read one block of the window as A[m][(k,l)] (M = v,
     // K = v^2, unit stride along (k,l)) and differ in B and C run as column
@@ -1357,7 +1370,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
           lenB[4 + t] = q.tlenB;
           lenC[4 + t] = q.tlenC;
         }
-        prod_colseg(e, g, cblh, winlen, lenB, lenC, st);
+        launches_ += prod_colseg(e, g, cblh, winlen, lenB, lenC, st);
       }
     };
     auto cseg = [&](const cplx* Bp, std::initializer_list<int64_t> cb, int64_t sbk, int64_t sbn, cplx* Cp,
@@ -1413,7 +1426,8 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
           traces.erase(traces.begin(), traces.begin() + 2);
           for (BlockTrace& t : traces) t.group = 0;
         }
-        prod_frag_block(e, groups, traces, o, lB + first, lC + first, lT, T, winlen, 5, v, vp, w, pairwin ? w.owned : w.bl, cbl, s);
+        launches_ += prod_frag_block(e, groups, traces, o, lB + first, lC + first, lT, T, winlen, 5, v, vp, w,
+                                     pairwin ? w.owned : w.bl, cbl, s);
       } else {
         GemmDesc::ColSeg c1 = cseg(gG1, {ov2, 0, 0, 0}, 1, v2, R15, {0, ovo, vo, 0}, o, 1, 1.0);   // term 1: (xc|Id)
         GemmDesc::ColSeg c5 = cseg(gG5, {0, ov2, 0, 0}, 1, v2, R15, {vo, 0, ovo, 0}, o, 1, -1.0);  // term 5: L_Ibxc
@@ -1461,9 +1475,8 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.sCn1 = v;
       g.sCn0 = 1;
       set4(g.cC, 0, v3, 0, 0);
-      prod_gather(e, g, w.gJ, t2len, winlen, lOVVV, s2);
+      launches_ += prod_gather(e, g, w.gJ, t2len, winlen, lOVVV, s2);
     }
-    launches_ += tails ? 8 : 9;
   }
 
   // the density terms read t3 and lambda3: join the lambda3 side's blocks
@@ -1492,7 +1505,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.C = Dab;
       g.sCm0 = v;
       g.sCn0 = 1;
-      prod(e, g, w.slabs.data(), winlen, winlen, v2, s);
+      launches_ += prod(e, g, w.slabs.data(), winlen, winlen, v2, s);
     } else {  // D_ab += 1/2 sum_{(d,c)} lambda[a][(d,c)] t[b][(d,c)]
       GemmDesc g = base(v, v, (int)v2, no, w.d_owned, pr);
       g.atomic = 1;
@@ -1511,7 +1524,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.C = Dab;
       g.sCm0 = v;
       g.sCn0 = 1;
-      prod(e, g, w.owned.data(), winlen, winlen, v2, s);
+      launches_ += prod(e, g, w.owned.data(), winlen, winlen, v2, s);
     }
     // D_ia: its first term is the Y1 intermediate Z34, its second is contracted from R8
   }
@@ -1526,13 +1539,13 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
         RTCC3_CHECK(w.slabs[4 * q + 3] >= 0 && (int64_t)(w.slabs[4 * q + 3] + o) * vb <= winlen,
                     "triples: slab out of bounds");
       // whole padded blocks: the padding is zero and adds nothing
-      launch_gram(T, L, w.d_slabs, nslab, o, vb, R(-0.5), Dij, s2);
+      launches_ += launch_gram(T, L, w.d_slabs, nslab, o, vb, R(-0.5), Dij, s2);
       if (e.tangent()) {
         const cplx *Tt = e.twin(T), *Lt = e.twin(L);
         if (Tt || Lt) {
           cplx* Dt = e.twin_out(Dij);
-          if (Tt) launch_gram(Tt, L, w.d_slabs, nslab, o, vb, R(-0.5), Dt, s2);
-          if (Lt) launch_gram(T, Lt, w.d_slabs, nslab, o, vb, R(-0.5), Dt, s2);
+          if (Tt) launches_ += launch_gram(Tt, L, w.d_slabs, nslab, o, vb, R(-0.5), Dt, s2);
+          if (Lt) launches_ += launch_gram(T, Lt, w.d_slabs, nslab, o, vb, R(-0.5), Dt, s2);
         }
       }
     } else {
@@ -1550,7 +1563,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       g.C = Dij;
       g.sCm0 = o;
       g.sCn0 = 1;
-      prod(e, g, w.slabs.data(), winlen, winlen, (int64_t)o * o, s2);
+      launches_ += prod(e, g, w.slabs.data(), winlen, winlen, (int64_t)o * o, s2);
     }
   }
   // the next window reuses every window buffer: join the lambda3 side

@@ -123,6 +123,7 @@ class Triples {
   // (call after the caller's stream has been synchronised; also done by run()
   // itself when an event pool is full).
   void fold_timing();
+  // Milliseconds of the runs, and kernels launched over their windows.
   void timing(double& ms, double& launches) const {
     ms = ms_;
     launches = (double)launches_;

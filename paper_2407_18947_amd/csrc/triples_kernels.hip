@@ -421,11 +421,11 @@ __global__ __launch_bounds__(256) void gram_kernel(const cplx* __restrict__ A, c
 }
 }  // namespace
 
-void launch_sym_cube(cplx* W, const int* canon, int ncanon, const int* part, const double* eps, int o, int v, int vp,
+int launch_sym_cube(cplx* W, const int* canon, int ncanon, const int* part, const double* eps, int o, int v, int vp,
                      const LamElem* le, const LamElem* le2, hipStream_t s) {
   RTCC3_CHECK(vp >= v, "sym: row stride below v");
   RTCC3_CHECK(le || !le2, "sym: a second set of bracket inputs needs a first");
-  if (ncanon <= 0) return;
+  if (ncanon <= 0) return 0;
   const int nc = (v + CB - 1) / CB;
   const dim3 grid((unsigned)(nc * nc * nc), (unsigned)ncanon);
   LamPair lp;
@@ -438,11 +438,12 @@ void launch_sym_cube(cplx* W, const int* canon, int ncanon, const int* part, con
   else
     hipLaunchKernelGGL(sym_cube_kernel<0>, grid, dim3(256), 0, s, W, canon, part, eps, o, v, vp, lp);
   RTCC3_HIP(hipGetLastError());
+  return 1;
 }
 
-void launch_gram(const cplx* A, const cplx* B, const int* slabs, int nslab, int o, int64_t K, cplx alpha, cplx* D,
+int launch_gram(const cplx* A, const cplx* B, const int* slabs, int nslab, int o, int64_t K, cplx alpha, cplx* D,
                  hipStream_t s) {
-  if (nslab <= 0 || K <= 0) return;
+  if (nslab <= 0 || K <= 0) return 0;
   RTCC3_CHECK(o >= 1 && o <= 16, "gram: at most 16 rows");
   // About 2048 workgroups over the slabs, K ranges in whole LDS stages, of 16 or
   // more: each adds to the same o^2 elements, some 45 ns a workgroup (o=5, v=18:
@@ -453,12 +454,13 @@ void launch_gram(const cplx* A, const cplx* B, const int* slabs, int nslab, int 
   RTCC3_CHECK(nslab < 65536, "gram: too many slabs");
   hipLaunchKernelGGL(gram_kernel, dim3(nx, (unsigned)nslab), dim3(256), 0, s, A, B, slabs, o, K, kchunk, alpha, D);
   RTCC3_HIP(hipGetLastError());
+  return 1;
 }
 
-void launch_small_t3(const cplx* T, const int* bl, int nb, const cplx* Lov, const cplx* F, const cplx* l2, cplx* X1,
+int launch_small_t3(const cplx* T, const int* bl, int nb, const cplx* Lov, const cplx* F, const cplx* l2, cplx* X1,
                      cplx* X2p, cplx* Z, int o, int v, int vp, int flags, hipStream_t s) {
   RTCC3_CHECK(vp >= v, "small_t3: row stride below v");
-  if (nb <= 0) return;
+  if (nb <= 0) return 0;
   const unsigned nyc = (unsigned)((v + SW_NW - 1) / SW_NW);
   if (v <= 64) {
     hipLaunchKernelGGL(small_t3_wave_kernel<1>, dim3((unsigned)nb, nyc), dim3(64 * SW_NW), 0, s, T, bl, Lov, F, l2, X1,
@@ -471,6 +473,7 @@ void launch_small_t3(const cplx* T, const int* bl, int nb, const cplx* Lov, cons
                        X2p, Z, o, v, vp, flags);
   }
   RTCC3_HIP(hipGetLastError());
+  return 1;
 }
 
 }  // namespace rtcc3

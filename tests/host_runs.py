@@ -107,6 +107,30 @@ def precision_switch(o, v, first, then):
         assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max() + 1e-15, name
 
 
+def launch_count(o, v, precision, steps, tangent):
+    """rtcc3_last_timing()[2] against the launches themselves: two numbers of
+    windows of one system differ by the kernels of the windows alone."""
+    o, v, precision, steps, tangent = int(o), int(v), int(precision), int(steps), int(tangent)
+    L = _lib.load()
+    ctx = _lib.Context(make_system(o, v, seed=3), precision)
+    if tangent:
+        ctx.set_option(_lib.RTCC3_OPT_TANGENT, 1)
+    ctx.set_state(random_state(o, v, 2))
+    field = np.zeros((2 * steps + 1, 3))
+    seen = []
+    for blocks in (0, 6):
+        ctx.set_option(_lib.RTCC3_OPT_WINDOW_BLOCKS, blocks)
+        L.emu_reset_launches()
+        if tangent:
+            ctx.propagate_tangent(steps, 0.05, field, np.ones_like(field))
+        else:
+            ctx.propagate(steps, 0.05, field)
+        seen.append((L.emu_launches(b""), _lib.rtcc3_last_timing(ctx.ctx)[2]))
+    ctx.close()
+    assert seen[1][0] > seen[0][0], seen
+    assert seen[1][0] - seen[0][0] == seen[1][1] - seen[0][1], seen
+
+
 if __name__ == "__main__":
     _lib.LIBPATH = sys.argv[1]
     globals()[sys.argv[2]](*sys.argv[3:])

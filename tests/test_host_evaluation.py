@@ -26,3 +26,10 @@ def test_reduced_precisions(host_library, o, v, precision):  # noqa: F811
 @pytest.mark.parametrize("first,then", [(2, 0), (1, 0), (0, 2), (0, 1)])
 def test_precision_switch(host_library, o, v, first, then):  # noqa: F811
     host_run(host_library, "precision_switch", o, v, first, then)
+
+
+@pytest.mark.parametrize("o,v,precision,steps,tangent", [
+    (3, 3, 0, 0, 0), (3, 3, 0, 1, 0), (3, 3, 1, 0, 0), (3, 3, 2, 0, 0), (3, 2, 0, 0, 1), (3, 2, 2, 0, 1)])
+def test_launches_counted(host_library, o, v, precision, steps, tangent):  # noqa: F811
+    """The dipole's pass alone, steps, each kind of precision and derivatives."""
+    host_run(host_library, "launch_count", o, v, precision, steps, tangent)
