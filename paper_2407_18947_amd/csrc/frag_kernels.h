@@ -37,7 +37,7 @@ struct FragJob {
 // job's output in place over long stretches; group: the usual length of the
 // shortest such stretches.
 int frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
-                 hipStream_t s);
+                hipStream_t s);
 
 // Products that read the blocks of a window as rows k < v^2 of v columns b, and
 // whose other operand depends on the block table's K only,
@@ -84,9 +84,11 @@ struct BlockTrace {
 };
 constexpr int kMaxBlockCols = 4;
 // pack: space for frag_block_pack() elements, used on s only until the product
-// is done; o: the extent of I, J and K.
+// is done; o: the extent of I, J and K; reach: the most bytes from the first to
+// past the last panel of the groups that one launch takes (32-bit offsets).
 int frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
-                int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s);
+               int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s,
+               int64_t reach = (int64_t)1 << 32);
 int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v);
 
 // A plain FP64 product (no segments, gathered K or combined operands) with its

@@ -1040,15 +1040,15 @@ int64_t frag_block_pack(const BlockCols* groups, int ng, int n, int o, int v) {
 }
 
 int frag_block(const BlockCols* groups, int ng, int n, const BlockTrace* tr, int ntr, const cplx* X, int perm, int o,
-                int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s) {
+               int v, int vp, const int* part, const int* bl, int nblk, cplx* pack, hipStream_t s, int64_t reach) {
   if (nblk <= 0 || ng <= 0) return 0;
   RTCC3_CHECK(ng <= kMaxBlockCols && ntr <= kMaxBlockCols && n >= 1 && v >= 1 && vp >= v &&
                   (int64_t)v * v * vp < (1LL << 27) && ((int64_t)v * v + 3) * n < (1LL << 27),
               "frag: bad block product");
   FragBlock d;
   const int64_t plen = ((int64_t)v * v + 3) / 4 * 4 * n;
-  if (ng > 1 && (block_panels(groups, ng, o, d.panel) + 1) * plen * (int64_t)sizeof(cplx) > (1LL << 32)) {
-    // a fragment's panels have to lie within 2^32 bytes: with one group it has one
+  if (ng > 1 && (block_panels(groups, ng, o, d.panel) + 1) * plen * (int64_t)sizeof(cplx) > reach) {
+    // a fragment's panels have to lie within reach: with one group it has one
     int launches = 0;
     for (int q = 0; q < ng; ++q) {
       std::vector<BlockTrace> own;
@@ -1393,7 +1393,7 @@ int frag_cols(const ColsJob* jobs, int njob, const cplx* B, const int* perm, int
 }
 
 int frag_gather(const FragJob* jobs, int njob, const cplx* B, int v, int vp, const int* bl, int nblk, int group,
-                 hipStream_t s) {
+                hipStream_t s) {
   if (nblk <= 0 || njob <= 0) return 0;
   RTCC3_CHECK(njob <= 2 && v >= 1 && vp >= v && group >= 1, "frag: bad gathered product");
   RTCC3_CHECK((int64_t)v * v * vp < (1LL << 27) && (int64_t)v * v < (1 << 22), "frag: product too large");

@@ -1,4 +1,5 @@
 // Entry points of the CPU build for tests of single kernels and host functions.
+#include <algorithm>
 #include <cmath>
 #include <random>
 #include <vector>
@@ -186,5 +187,208 @@ extern "C" double drive_three_runs(int o, int v, size_t* extra) {
           for (int x = 0; x < v; ++x) add(s, z[((i * v + b) * v + d) * v + x], w[((d * v + a) * v + x) * v + b]);
       err = std::max(err, std::hypot(Y.p[i * v + a].re - s.re, Y.p[i * v + a].im - s.im));
     }
+  return err;
+}
+
+namespace {
+
+// A plain product whose indices m, n and k are split in two levels each, with
+// the dimensions of its operands in any order, dense or with gaps, several
+// entries with an output each or one for all.
+struct Product {
+  GemmDesc g;
+  std::vector<cplx> A, B, before;
+  int64_t nC = 0;
+  bool adds;
+};
+
+// Strides of the dimensions of x, the one listed first in `order` slowest, each
+// slower one with `gap` more than it needs; returns the elements spanned.
+int64_t lay(const int* x, int64_t* stride, const int* order, int nd, int gap) {
+  int64_t s = 1;
+  for (int q = nd - 1; q >= 0; --q) {
+    stride[order[q]] = s;
+    s *= x[order[q]] + (q > 0 ? gap : 0);
+  }
+  return s;
+}
+
+Product make(std::mt19937& r, const int* e, int batch, int form) {  // e: M1, M0, N1, N0, K1, K0
+  Product p;
+  GemmDesc& g = p.g;
+  std::memset(&g, 0, sizeof(g));
+  g.M = e[0] * e[1];
+  g.M0 = e[1];
+  g.N = e[2] * e[3];
+  g.N0 = e[3];
+  g.K = e[4] * e[5];
+  g.K0 = e[5];
+  g.batch = batch;
+  auto order = [&](int* o) {
+    for (int q = 0; q < 5; ++q) o[q] = q;
+    std::shuffle(o, o + 5, r);
+  };
+  int o[5];
+  int64_t s[5];
+  const int a[5] = {e[0], e[1], e[4], e[5], batch}, b[5] = {e[4], e[5], e[2], e[3], batch};
+  const bool one = form & 1;  // one output for all entries
+  const int c[5] = {e[0], e[1], e[2], e[3], one ? 1 : batch};
+  order(o);
+  p.A = random(lay(a, s, o, 5, form >> 1 & 1), r());
+  g.sAm1 = s[0], g.sAm0 = s[1], g.sAk1 = s[2], g.sAk0 = s[3], g.sAb = s[4];
+  order(o);
+  p.B = random(lay(b, s, o, 5, form >> 2 & 1), r());
+  g.sBk1 = s[0], g.sBk0 = s[1], g.sBn1 = s[2], g.sBn0 = s[3], g.sBb = s[4];
+  order(o);
+  const bool fresh = form >> 3 & 1;
+  p.nC = lay(c, s, o, 5, fresh ? 0 : form >> 4 & 1);
+  g.sCm1 = s[0], g.sCm0 = s[1], g.sCn1 = s[2], g.sCn0 = s[3], g.sCb = one ? 0 : s[4];
+  p.before = random(p.nC, r());
+  if (fresh)
+    for (auto& z : p.before) z = cplx{std::nan(""), std::nan("")};
+  g.A = device(p.A);
+  g.B = device(p.B);
+  g.C = device(p.before);
+  g.alpha = cplx{0.5, form & 32 ? -1.5 : 0.0};
+  g.atomic = one && batch > 1;
+  g.fresh = fresh;
+  g.fresh_p = g.C;
+  g.fresh_n = p.nC;
+  g.prec = RTCC3_PREC_FP64;
+  p.adds = !fresh;
+  return p;
+}
+
+// The largest error of C in units of the bound on rounding; other elements of C stay.
+double check(const Product& p) {
+  const GemmDesc& g = p.g;
+  std::vector<cplx> want(p.nC), size(p.nC);
+  std::vector<char> mine(p.nC);
+  for (int b = 0; b < g.batch; ++b)
+    for (int m = 0; m < g.M; ++m)
+      for (int n = 0; n < g.N; ++n) {
+        const int64_t at = b * g.sCb + m / g.M0 * g.sCm1 + m % g.M0 * g.sCm0 + n / g.N0 * g.sCn1 + n % g.N0 * g.sCn0;
+        cplx s{0, 0};
+        for (int k = 0; k < g.K; ++k) {
+          const cplx x = p.A[b * g.sAb + m / g.M0 * g.sAm1 + m % g.M0 * g.sAm0 + k / g.K0 * g.sAk1 + k % g.K0 * g.sAk0];
+          const cplx y = p.B[b * g.sBb + n / g.N0 * g.sBn1 + n % g.N0 * g.sBn0 + k / g.K0 * g.sBk1 + k % g.K0 * g.sBk0];
+          add(s, x, y);
+          size[at].re += std::hypot(x.re, x.im) * std::hypot(y.re, y.im);
+        }
+        add(want[at], s, g.alpha);
+        mine[at] = 1;
+      }
+  double worst = 0;
+  for (int64_t i = 0; i < p.nC; ++i) {
+    if (p.adds || !mine[i]) want[i].re += p.before[i].re, want[i].im += p.before[i].im;
+    const double err = std::hypot(g.C[i].re - want[i].re, g.C[i].im - want[i].im);
+    // each term passes as many roundings of sums of at most twice its size as
+    // there are terms (three real products per complex one), and alpha's
+    const double before = p.adds ? std::hypot(p.before[i].re, p.before[i].im) : 0.0;
+    const double bound =
+        mine[i] ? 8 * (g.K * g.batch + 8) * 2.3e-16 * (std::hypot(g.alpha.re, g.alpha.im) * size[i].re + before) : 0.0;
+    if (!(err <= bound)) worst = std::max(worst, std::isfinite(err) && bound > 0 ? err / bound : 1e300);
+  }
+  return worst;
+}
+
+void drop(const Product& p) {
+  (void)hipFree(const_cast<cplx*>(p.g.A));
+  (void)hipFree(const_cast<cplx*>(p.g.B));
+  (void)hipFree(p.g.C);
+}
+
+}  // namespace
+
+// `count` products of random forms, one by one and four to a level; the largest error.
+extern "C" double drive_products(int seed, int count) {
+  std::mt19937 r(seed);
+  const int outer[] = {1, 1, 2, 3, 5}, inner[] = {1, 2, 3, 4, 7, 8, 15, 16, 17, 33}, steps[] = {1, 2, 3, 4, 5, 8, 13, 32};
+  double worst = 0;
+  std::vector<Product> level;
+  for (int i = 0; i < count; ++i) {
+    const int e[6] = {outer[r() % 5], inner[r() % 10], outer[r() % 5], inner[r() % 10], outer[r() % 5], steps[r() % 8]};
+    Product p = make(r, e, r() % 3 == 0 ? 2 + r() % 3 : 1, (int)(r() % 64));
+    RTCC3_CHECK(frag_gemm_fits(p.g), "not a product for the kernel");
+    if (i % 2) {
+      level.push_back(std::move(p));
+      if (level.size() < 4) continue;
+      std::vector<GemmDesc> g;
+      for (auto& q : level) g.push_back(q.g);
+      gemm_group(g.data(), (int)g.size(), nullptr);
+      for (auto& q : level) worst = std::max(worst, check(q)), drop(q);
+      level.clear();
+    } else {
+      gemm(p.g, nullptr);
+      worst = std::max(worst, check(p));
+      drop(p);
+    }
+  }
+  for (auto& q : level) drop(q);
+  return worst;
+}
+
+// One product of given extents (M1, M0, N1, N0, K1, K0), split of k as given (0: the kernel's choice).
+extern "C" double drive_product(const int* e, int batch, int form, int ksplit) {
+  std::mt19937 r(17);
+  Product p = make(r, e, batch, form);
+  if (ksplit > 0)
+    frag_gemm(p.g, ksplit, nullptr);
+  else
+    gemm(p.g, nullptr);
+  const double worst = check(p);
+  drop(p);
+  return worst;
+}
+
+// Block products of four groups with traces, all groups in a launch and (reach
+// of a panel) one group at a time; the launches and the largest error.
+extern "C" double drive_block(int o, int v, int one_by_one, long* launches) {
+  const int vp = (v + 7) / 8 * 8, nb = o * o * o;
+  const int64_t v2 = (int64_t)v * v, vb = v2 * vp, ov2 = o * v2;
+  std::vector<int> bl, part;
+  for (int i = 0; i < o; ++i)
+    for (int j = 0; j < o; ++j)
+      for (int k = 0; k < o; ++k) {
+        const int n = (int)bl.size() / 4;
+        bl.insert(bl.end(), {i, j, k, n});
+        for (int q = 0; q < 6; ++q) part.push_back((n + q) % nb);
+      }
+  const std::vector<cplx> X = random(nb * vb, 1), B0 = random(o * ov2, 2), B1 = random(o * ov2, 3);
+  const cplx *d0 = device(B0), *d1 = device(B1);
+  const int64_t nC = (int64_t)o * o * v * o;
+  std::vector<cplx*> C;
+  for (int q = 0; q < 4; ++q) C.push_back(device<cplx>(nC));
+  cplx *t0 = device<cplx>(o * v), *t1 = device<cplx>(o * v);
+  const int64_t vo = (int64_t)v * o, ovo = o * vo;
+  const BlockCols groups[4] = {{d0, 0, ov2, v2, C[0], {0, ovo, vo}, o, 1, 1.0},
+                               {d1, 1, ov2, v2, C[1], {vo, 0, ovo}, o, 1, -1.0},
+                               {d0, 0, v2, ov2, C[2], {0, ovo, vo}, o, 1, 0.5},
+                               {d0, 2, v2, ov2, C[3], {ovo, vo, 0}, o, 1, 2.0}};
+  const BlockTrace traces[4] = {{1, 2, 0, t0, v, 1.0}, {1, 0, 2, t0, v, -1.0}, {3, 1, 0, t1, v, 0.25}, {3, 0, 1, t1, v, -1.0}};
+  cplx* pack = device<cplx>(frag_block_pack(groups, 4, o, o, v));
+  const int perm = 5;
+  *launches = frag_block(groups, 4, o, traces, 4, device(X), perm, o, v, vp, device(part), device(bl), nb, pack, nullptr,
+                         one_by_one ? 1 : (int64_t)1 << 32);
+  std::vector<std::vector<cplx>> want(6, std::vector<cplx>(nC));
+  for (int n = 0; n < nb; ++n)
+    for (int g = 0; g < 4; ++g)
+      for (int x = 0; x < o; ++x)
+        for (int b = 0; b < v; ++b) {
+          const int* q = &bl[4 * n];
+          const BlockCols& c = groups[g];
+          const std::vector<cplx>& src = c.B == d0 ? B0 : B1;
+          cplx s{0, 0};
+          for (int k = 0; k < v2; ++k) add(s, X[part[6 * n + perm] * vb + (int64_t)k * vp + b], src[q[c.key] * c.sKey + x * c.sB + k]);
+          add(want[g][c.cC[0] * q[0] + c.cC[1] * q[1] + c.cC[2] * q[2] + b * c.sCm + x * c.sCx], s, cplx{c.alpha, 0});
+          for (const BlockTrace& t : traces)
+            if (t.group == g && x == q[t.col]) add(want[t.C == t0 ? 4 : 5][q[t.row] * t.sC + b], s, cplx{t.alpha, 0});
+        }
+  double err = 0;
+  for (int g = 0; g < 6; ++g) {
+    const cplx* c = g < 4 ? C[g] : g == 4 ? t0 : t1;
+    for (int64_t i = 0; i < (g < 4 ? nC : o * v); ++i)
+      err = std::max(err, std::hypot(c[i].re - want[g][i].re, c[i].im - want[g][i].im));
+  }
   return err;
 }

@@ -131,6 +131,34 @@ def launch_count(o, v, precision, steps, tangent):
     assert seen[1][0] - seen[0][0] == seen[1][1] - seen[0][1], seen
 
 
+def products(seed, count):
+    """Plain products of random forms; errors in units of their bound."""
+    f = _lib.load().drive_products
+    f.restype = ctypes.c_double
+    err = f(int(seed), int(count))
+    assert err <= 1.0, err
+
+
+def product(*args):
+    """One plain product: its six extents, batch, form and split of k."""
+    a = [int(x) for x in args]
+    f = _lib.load().drive_product
+    f.restype = ctypes.c_double
+    err = f((ctypes.c_int * 6)(*a[:6]), *a[6:])
+    assert err <= 1.0, err
+
+
+def block(o, v, one_by_one):
+    """Block products with all groups in a launch, or one group at a time."""
+    f = _lib.load().drive_block
+    f.restype = ctypes.c_double
+    n = ctypes.c_long()
+    err = f(int(o), int(v), int(one_by_one), ctypes.byref(n))
+    # o^2 v^2 products of order one
+    assert err <= 1e-14 * int(o) ** 2 * int(v) ** 2, err
+    assert n.value == (8 if int(one_by_one) else 2), n.value
+
+
 if __name__ == "__main__":
     _lib.LIBPATH = sys.argv[1]
     globals()[sys.argv[2]](*sys.argv[3:])
