@@ -700,6 +700,8 @@ void Engine::einsum_exec(const std::string& spec, cplx alpha, const View& A0, co
     for (int b : breaks(ob, gk, ext))
       if (std::find(u.begin(), u.end(), b) == u.end()) u.push_back(b);
     if (u.size() == 2 && split_of(oa, oc, gm, sm) == 0 && split_of(ob, oc, gn, sn) == 0) {
+      // gemm()'s limit of the extents holds for the whole sum (v >= 162 is refused by it)
+      RTCC3_CHECK(extent(gk, ext) < (1 << 22), "gemm: extent too long");
       std::sort(u.begin(), u.end());
       const int cut[4] = {0, u[0], u[1], (int)gk.size()};
       int best = 0;

@@ -392,3 +392,15 @@ extern "C" double drive_block(int o, int v, int one_by_one, long* launches) {
   }
   return err;
 }
+
+// The error code of a sum over three runs of indices of the given extents (0: none).
+extern "C" int drive_three_runs_extent(int b, int d, int x) {
+  Engine e(nullptr);
+  View Z = e.tensor("Z", {1, b, d, x}), W = e.tensor("W", {d, 2, x, b}), Y = e.tensor("Y", {1, 2});
+  try {
+    e.einsum("ibde,daeb->ia", cplx{1, 0}, Z, W, Y);
+  } catch (const Error& err) {
+    return err.code;
+  }
+  return 0;
+}

@@ -87,6 +87,12 @@ def three_runs(o, v):
     assert extra.value == 0, extra.value
 
 
+def three_runs_extent(b, d, e, code):
+    """Sums longer than a product takes are refused, also where a run becomes a batch."""
+    got = _lib.load().drive_three_runs_extent(int(b), int(d), int(e))
+    assert got == int(code), got
+
+
 def precision_switch(o, v, first, then):
     """A context switched to another precision evaluates, with what it allocated
     when it was created, like one created with it."""

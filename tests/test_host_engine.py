@@ -23,3 +23,10 @@ def test_tuned_split_of_products_in_one_level(host_library, M, N, K, ms, apart):
 @pytest.mark.parametrize("o,v", [(2, 3), (3, 9), (1, 4)])
 def test_sum_over_three_runs_takes_no_memory(host_library, o, v):  # noqa: F811
     host_run(host_library, "three_runs", o, v)
+
+
+@pytest.mark.parametrize("extents,code", [((2, 31, 17), 0), ((4, 1024, 1024), -1), ((128, 256, 256), -1)])
+def test_extent_of_a_sum_over_three_runs(host_library, extents, code):  # noqa: F811
+    """The limit of 2^22 terms holds for the whole sum: more than 161 virtual
+    orbitals are refused when a context is created."""
+    host_run(host_library, "three_runs_extent", *extents, code)
