@@ -1013,11 +1013,11 @@ void launch_comb_gemm(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit, i
     hipLaunchKernelGGL((zgemm_kernel<T, ATOMIC, true, false, BN, false, 2>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
 }
 
-// Gathered-K products, FP64 or FP32, for the layouts they are used with.
-template <int MODE, bool ATOMIC>
+// Gathered-K products, FP32, for the layouts they are used with.
+template <bool ATOMIC>
 void launch_gather_gemm(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit, int kchunk, bool kfa, bool nfb,
                         int bn) {
-  typedef typename std::conditional<MODE == RTCC3_PREC_FP64, double, float>::type T;
+  typedef float T;
   if (kfa && nfb) {
     if (bn == 16)
       hipLaunchKernelGGL((zgemm_kernel<T, ATOMIC, true, true, 16, false, 3>), grid, dim3(NT), 0, s, d, ksplit, kchunk);
@@ -1050,7 +1050,10 @@ void launch_layout(const GemmDesc& d, dim3 grid, hipStream_t s, int ksplit, int 
     return;
   }
   if (d.gk_start) {
-    if (MODE == RTCC3_PREC_FP64 || MODE == RTCC3_PREC_FP32) launch_gather_gemm<MODE, ATOMIC>(d, grid, s, ksplit, kchunk, kfa, nfb, bn);
+    if constexpr (MODE == RTCC3_PREC_FP32)
+      launch_gather_gemm<ATOMIC>(d, grid, s, ksplit, kchunk, kfa, nfb, bn);
+    else
+      RTCC3_CHECK(false, "gemm: gathered products run in FP32");
   } else if (d.comb_n > 0) {
     if constexpr (MODE == RTCC3_PREC_FP32) {
       if (bn == 16)
@@ -1205,14 +1208,12 @@ TunerScope::TunerScope(Tuner* t) : prev(g_tuner) { g_tuner = t; }
 TunerScope::~TunerScope() { g_tuner = prev; }
 
 int gemm(const GemmDesc& d_in, hipStream_t s) {
-  // A bf16-split run takes the split kernel for its segmented products only.
-  // Its other products run in FP32, except the 16-wide gathered ones, whose FP64
-  // kernel was the faster one (1.95 against 2.51 ms at o=15, v=57) and is more
-  // accurate.
+  // A bf16-split run takes the split kernel for its segmented products only;
+  // its other products that come here run in FP32.
   GemmDesc dsel = d_in;
   if ((dsel.prec == RTCC3_PREC_BF16X3 || dsel.prec == RTCC3_PREC_BF16X2) &&
       !((dsel.nseg > 0 || dsel.force_prec) && !dsel.comb_n && !dsel.gk_start && !dsel.ncs))
-    dsel.prec = dsel.gk_start && dsel.N <= 16 ? RTCC3_PREC_FP64 : RTCC3_PREC_FP32;
+    dsel.prec = RTCC3_PREC_FP32;
   const GemmDesc& d0 = dsel;
   if (d0.M <= 0 || d0.N <= 0 || d0.batch <= 0) return 0;
   if (d0.K <= 0) return 0;
@@ -1293,10 +1294,8 @@ int gemm(const GemmDesc& d_in, hipStream_t s) {
     kmin = std::max<int64_t>(kmin, (d.K + 4095) / 4096);
     ksplit = (int)std::max<int64_t>(ksplit, kmin);
   }
-  if (d.gk_start) {  // a workgroup's K range spans at most GK_MAXSEG - 4 gathered blocks,
-                     // and at most 16 when it accumulates in FP32
-    const int64_t nblk = d.prec == RTCC3_PREC_FP64 ? GK_MAXSEG - 4 : 16;
-    const int64_t span_k = std::max<int64_t>(BKMAX, nblk * d.K0 / BKMAX * BKMAX);
+  if (d.gk_start) {  // a workgroup's FP32 sum spans at most 16 gathered blocks
+    const int64_t span_k = std::max<int64_t>(BKMAX, 16 * (int64_t)d.K0 / BKMAX * BKMAX);
     kmin = std::max<int64_t>(kmin, (d.K + span_k - 1) / span_k);
     ksplit = (int)std::max<int64_t>(ksplit, kmin);
   }

@@ -595,7 +595,8 @@ void finish_window(Window& w, const std::vector<std::array<int, 3>>& blocks) {
 void Triples::build_windows() {
   const int o = d_.o;
   // Two window buffers of nw blocks each (t3 and lambda3, each built and then
-  // symmetrised in place) and S; larger windows mean fewer, larger launches.
+  // symmetrised in place) and S, which the reduced precisions form (allocated in
+  // FP64 too, for a switch); larger windows mean fewer, larger launches.
   // Budget: half the free device memory, at most 48 GiB (of the 288 GB of
   // HBM); when all o^3 blocks fit, one window serves both passes and nothing
   // is built twice.
@@ -1154,7 +1155,10 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     // tail columns of the Y1 product below; the f~ term inside tb_X2c); else one
     // sweep per block
     const bool tails = o <= 15 || pr == RTCC3_PREC_FP64;
-    // the 16-wide gathered products in FP64 (the split precisions too)
+    // The products with an occupied index as one side, from fragments in FP64: the
+    // split precisions too where they fit the one 16-wide tile (o <= 16) that ran
+    // in FP64 before; wider ones stay FP32 there, as their results were (which is
+    // faster has not been measured above o = 16).
     const bool frag16 = pr == RTCC3_PREC_FP64 || (pr != RTCC3_PREC_FP32 && o <= 16);
     RTCC3_CHECK(o <= 15 || !e.tangent(), "triples: derivatives need o <= 15");
     if (!tails) {
@@ -1300,14 +1304,17 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
     const FragJob jZ{t2, {v2, 0, ov2l}, v, v2, v, Zi, {0, v3, 0}, v2, 1.0};
     // the first reads the block as lambda_KIJ[d][(a,b)]
     const FragJob jY{gY2b, {(int64_t)o * v, (int64_t)o * o * v, 0}, v, ov, o, Y2p, {0, 0, v2}, ov2l, -1.0};
-    if (!amps_) {
-      // not wanted
-    } else if (pr == RTCC3_PREC_FP64) {
-      const int64_t lA[2] = {t2len, lOOOV}, lC[2] = {lOVVV, oovv};
-      launches_ += prod_frag_gather(e, {jZ, jY}, lA, lC, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
-    } else if (frag16) {
-      launches_ += prod_frag_gather(e, {jY}, &lOOOV, &oovv, L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
-    } else {  // summed over the blocks of each J
+    // In FP64 from one pass over the blocks; the split precisions run the second up to o = 16, and the first up to
+    // 16 columns (v = 4), in FP64 too, as wide as the FP64 tiles that these precisions had for them.
+    const bool zi64 = pr == RTCC3_PREC_FP64 || (pr != RTCC3_PREC_FP32 && v2 <= 16);
+    if (amps_) {
+      std::vector<FragJob> jobs;
+      std::vector<int64_t> lA, lC;
+      if (zi64) jobs.push_back(jZ), lA.push_back(t2len), lC.push_back(lOVVV);
+      if (frag16) jobs.push_back(jY), lA.push_back(lOOOV), lC.push_back(oovv);
+      launches_ += prod_frag_gather(e, jobs, lA.data(), lC.data(), L, winlen, v, vp, w.gat_l3, w.d_gat_l3, o, s2);
+    }
+    if (!frag16) {  // summed over the blocks of each J
       GemmDesc g = base((int)v2, o, v * w.gJ.max, 0, nullptr, pr);
       g.K0 = v;
       g.M0 = v;  // m = (a,b)
@@ -1457,7 +1464,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
                        0, 0});
       seg_product(L, specs, s2);
     }
-    if (pr != RTCC3_PREC_FP64) {  // Zi, summed over the blocks of each J
+    if (!zi64) {  // Zi, summed over the blocks of each J
       GemmDesc g = base(v, (int)v2, v * w.gJ.max, 0, nullptr, pr);
       g.K0 = v;
       g.A = t2;
