@@ -70,8 +70,8 @@ enum {
  *   RTCC3_BF16X2  two bf16 slices (16 bits), three slice products
  * The bf16 splits apply to the segmented products (the builds of t3 and
  * lambda3 and the S intermediate of Y1); the other triples products of such a
- * run use FP32, except the X2 product over virtual pairs and, up to o = 16, the
- * products with an occupied index as one side, which use FP64 (faster there).
+ * run use FP32, except the X2 product over virtual pairs, the products with an
+ * occupied index as one side up to o = 16 and Z_i up to v = 4, which use FP64.
  * The CCSD part is FP64 in every precision. */
 enum { RTCC3_FP64 = 0, RTCC3_FP32 = 1, RTCC3_BF16X3 = 2, RTCC3_BF16X2 = 3 };
 

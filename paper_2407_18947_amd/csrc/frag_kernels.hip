@@ -153,8 +153,8 @@ struct FragSeg {
   int ncol;
 };
 
-// The builds of t3 and lambda3 (o=15, v=57: t3 7.7 -> 5.6 ms, lambda3 12.5 ->
-// 9.8 ms a launch, alone; 0.77 -> 0.36 ms for t3 at o=10, v=38, where an
+// The builds of t3 and lambda3 (o=15, v=57: t3 6.9 -> 6.3 ms, lambda3 12.3 ->
+// 10.1 ms a launch, alone; 0.77 -> 0.40 ms for t3 at o=10, v=38, where an
 // entry's 38 rows filled a tile of 64).  What bounds them: the matrix cores,
 // then the stores (10 GB of 256-byte pieces of rows that are padded to whole
 // lines, 4.1 ms alone).  A workgroup computes 64 rows by 64 columns, a wave 32 by
@@ -384,8 +384,8 @@ __device__ __forceinline__ void gather_unit(const FragGather& d, const FragUnit&
 // once and from the caches for the other units; waves are numbered through, so
 // that four of them fill a workgroup whatever the number of units (as
 // workgroups of a chunk's units, five at o=15, v=57, only one would fit on a
-// CU: 8.5 ms).  At o=15, v=57 Z_i and the Y2 product, 6.9 ms apart, take 5.9 ms,
-// the two X2 products 3.1 instead of 3.85 ms; 0.71 -> 0.48 and 0.39 -> 0.26 ms at
+// CU: 8.5 ms).  At o=15, v=57 Z_i and the Y2 product, 6.9 ms apart, take 5.8 ms,
+// the two X2 products 2.9 instead of 3.85 ms; 0.71 -> 0.49 and 0.39 -> 0.28 ms at
 // o=10, v=38.  Bound by the matrix cores (4.0 ms of MFMAs) and, for the X2
 // pair, by the 10 GB it reads.
 __global__ __launch_bounds__(256, 2) void frag_gather_kernel(FragGather d) {
@@ -545,8 +545,8 @@ __device__ __forceinline__ void cols_unit(const FragCols& d, const ColsUnit& u, 
 
 // X2 (three streams) and Y2 with R8 (one).  Bound by the matrix cores (Y2: MFMA
 // busy 0.88 of the SIMD cycles) and, for X2, by the three orderings of each
-// block that pass through the L2.  o=15, v=57, alone: X2 5.9 -> 5.3 ms, Y2 and R8
-// 7.6 -> 5.2; o=10, v=38: 0.73 -> 0.43 and 0.85 -> 0.45, since columns of all
+// block that pass through the L2.  o=15, v=57, alone: X2 5.9 -> 5.2 ms, Y2 and R8
+// 7.6 -> 5.3; o=10, v=38: 0.73 -> 0.46 and 0.85 -> 0.51, since columns of all
 // entries of a K are numbered through and rows come in blocks of 16.  A read
 // straight from the integrals (64-byte pieces of rows 52 KB apart) instead of
 // packed panels made that 9.6 and 7.8 ms.
@@ -698,12 +698,12 @@ __device__ __forceinline__ void block_unit(const FragBlock& d, int e, int f, int
 }
 
 // Terms 1, 2, 5 and 6 of Y1 with X1 and terms 3 and 4 as traces of them.  Bound
-// by the matrix cores.  o=15, v=57, alone: 5.95 -> 4.54 ms; o=10, v=38: 0.76 ->
-// 0.45; o=16, v=66: 26.4 (16-wide columns of each segment, X1 and terms 3 and 4
-// in a sweep of their own) -> 8.2.  The columns of all groups are numbered
+// by the matrix cores.  o=15, v=57, alone: 5.95 -> 4.7 ms; o=10, v=38: 0.76 ->
+// 0.49; o=16, v=66: 26.4 (16-wide columns of each segment, X1 and terms 3 and 4
+// in a sweep of their own) -> 8.7.  The columns of all groups are numbered
 // through (4 o of them, so that little of the 16-wide fragments is padding) and
 // packed: read where they lie, as 16 pieces of 64 bytes v^2 apart each step, they
-// made that 6.56, 0.78 and 14.2 ms.
+// made that 6.6, 0.78 and 14.2 ms.
 // One wave per block, 16 columns, group of row blocks and split of k; the
 // waves of a block follow each other, so that they share its rows in the L1.
 __global__ __launch_bounds__(256, 2) void frag_block_kernel(FragBlock d) {
@@ -777,10 +777,11 @@ struct FragGemm {
 // contraction is long (o=4, v=96, the two ladders over 9216 virtual pairs with
 // 300 rows: 51 and 75 TFLOP/s, k-fast against n-fast columns), by C where it is
 // short (3249 x 3249 x 216: 338 MB of C, 0.33 ms at 55 TFLOP/s), by latency and
-// launch below some 10^8 terms.  A right-hand side's 110 products, kernel time:
-// o=15, v=57 8.2 -> 6.1 ms, o=4, v=96 16.5 -> 15.1, o=5, v=18 2.0 -> 0.69 (an
-// 18 us LDS-tiled product with its split added by atomics becomes one of 6 us:
-// a workgroup's waves split k down to a few steps each).  Steps in pairs with k
+// launch below some 10^8 terms.  A right-hand side's products, kernel time, one
+// launch each: o=15, v=57 8.2 -> 6.1 ms, o=4, v=96 16.5 -> 15.1, o=5, v=18 2.0 ->
+// 0.69 (an 18 us LDS-tiled product with its split added by atomics becomes one
+// of 6 us: a workgroup's waves split k down to a few steps each); queued in
+// levels 6.0, 14.3 and, at o=5, v=19, 0.30.  Steps in pairs with k
 // next to each other (8u + 2 (l/16) + 0, 1) made k-fast operands read half lines
 // twice as often: 6.6 ms at o=15.  Where a workgroup has one block, its thread's
 // element of C is loaded before the product and indexes are divided by

@@ -523,8 +523,9 @@ void Triples::fold_timing() {
 void Triples::free_windows() {
   for (auto* ws : {&rhs_windows_, &den_windows_}) {
     for (auto& w : *ws) {
-      for (int* p : {w.d_bl, w.d_part, w.d_owned, w.d_canon, w.d_slabs, w.d_orb, w.d_orb_owned, w.d_bk_t3,
-                     w.d_bk_l3, w.d_bk_own, w.d_gat_t3, w.d_gat_l3, w.rt_t3.d, w.rt_l3.d, w.cols_t3.d_bl, w.cols_t3.d_frag, w.cols_l3.d_bl, w.cols_l3.d_frag})
+      for (int* p : {w.d_bl, w.d_part, w.d_owned, w.d_canon, w.d_slabs, w.d_orb, w.d_orb_owned, w.d_bk_t3, w.d_bk_l3,
+                     w.d_bk_own, w.d_gat_t3, w.d_gat_l3, w.rt_t3.d, w.rt_l3.d, w.cols_t3.d_bl, w.cols_t3.d_frag,
+                     w.cols_l3.d_bl, w.cols_l3.d_frag})
         if (p) (void)hipFree(p);
       for (Groups* gr : {&w.gJ, &w.gK})
         for (int* p : {gr->d_key, gr->d_start, gr->d_bl})
@@ -770,8 +771,8 @@ void Triples::upload(Window& w) {
   // The products with an operand of K alone: groups of whole permutation orbits
   // follow each other, within a group the entries of a K are numbered through.
   // X2 reads three orderings of each triple: with one orbit a group the waves
-  // that run together on an XCD share them (o=15, v=57: groups of 6, 30 and 120
-  // blocks take 5.6, 6.7 and 7.6 ms).  The products over lambda3 read one, and
+  // that run together on an XCD share them (o=15, v=57, with k in one piece: groups
+  // of 6, 30 and 120 blocks take 5.6, 6.7 and 7.6 ms).  The products over lambda3 read one, and
   // larger groups leave fewer fragments part empty (5.8, 5.4 and 5.4 ms).
   auto columns = [&](size_t orbit_group, ColTable& out) {
     std::map<std::array<int, 3>, std::vector<std::array<int, 4>>> by;
@@ -1497,7 +1498,7 @@ void Triples::window_pass(Engine& e, const Window& w, const cplx* y, bool densit
       // slab (., l, k), with the labels of each reversed (t_IJK[b][d][c] = t_KJI[c][d][b]): the o
       // blocks of a slab are o v^2 rows (c,d) whose columns are contiguous, so one product per slab
       // reads lines in order and adds once to D_ab (per block and along its rows it took 7.5 ms at
-      // o=15, v=57, where reading both takes 4.7, and 0.77 at o=10, v=38).
+      // o=15, v=57, where reading both takes 4.7, and 0.77 at o=10, v=38; now 5.0 and 0.58).
       GemmDesc g = base(v, v, (int)(o * v2), (int)w.slabs.size() / 4, w.d_slabs, pr);
       g.atomic = 1;
       g.alpha = R(0.5);
@@ -1589,7 +1590,7 @@ TriplesOut Triples::run(Engine& e, const Dims& d, const CCSDResult& r, const cpl
                         bool want_amplitudes, const Beside& beside, hipEvent_t ready) {
   // A dipole by itself needs t3, lambda3, the sum R8 of terms 7, 8 and 12 of Y1
   // and terms 3 and 4 of it, not X2, Y2, Z_i and the other intermediates (o=10,
-  // v=38: 5.7 ms with them).
+  // v=38: 5.7 ms with them, 4.2 without).
   amps_ = want_amplitudes || !want_density || prec_ != RTCC3_PREC_FP64;
   const int64_t o = d.o, v = d.v;
   const int64_t ov = o * v, oovv = o * o * v * v;
